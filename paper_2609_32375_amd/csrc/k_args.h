@@ -14,7 +14,6 @@ struct BkgArgs {
     float clip, crowd, mode_a, mode_b;
     int32_t max_iter;
     int32_t fsize;
-    int32_t skip_u16;   // the float kernel leaves uint16 meshes to the integer kernel
 };
 
 // matched-filter and detection arguments, stored in the workspace

@@ -1,13 +1,9 @@
 // k_background.hip -- mesh background for gfx950.
 //
-//  k_mesh_stats   one workgroup per mesh.  The mesh's pixels stay in VGPRs for
-//                 the whole kappa-sigma loop.  Each clipping pass tests every
-//                 surviving pixel against |v - med| <= kappa*sigma, accumulates
-//                 the shifted sums of the new set (compensated) and bins it into
-//                 an LDS histogram over the clip window; the exact median is the
-//                 order statistic found through the histogram's prefix sums and
-//                 a gather of the (few) pixels in the target bin.  All float
-//                 reductions run in a fixed order, so a mesh gives bit-identical
+//  k_mesh_stats   one workgroup per mesh.  The values of a mesh are grouped by
+//                 bins in LDS once; a clipping pass then takes the dropped ends
+//                 off exact sums and finds the median in its bin, all in one
+//                 wavefront.  Every sum is exact, so a mesh gives bit-identical
 //                 results wherever it is scheduled.
 //  k_spline_y_pcr, k_spline_x_pcr (and the *_blk variants)
 //                 grids of at most 127 knots per axis: the f x f median over
@@ -29,524 +25,154 @@
 
 namespace gpk {
 
-constexpr int kBins = 4096;
-constexpr int kMaxWaves = 16;     // up to 1024 threads per mesh
-
-constexpr int kBuf = 4096;        // sorted window of ranks around the median
-constexpr int kHalf = 512;        // half-width of that window, in ranks
-constexpr int kRankSmall = 16;    // first-level bins up to this size are ordered by rank counting
-constexpr int kRankMax = 256;     // second-level bins beyond this size go to the merge sort
-
-template <int NB>
-struct MeshShared {
-    static constexpr int kNB = NB;
-    union {
-        uint32_t hist[NB];
-        float buf2[kBuf];     // second buffer of the window sort
-    };
-    float buf[kBuf];
-    double pd[2][kMaxWaves][2];                // block_stats partials, double-buffered
-    int32_t pi[2][kMaxWaves][2];
-    float pmin[2][kMaxWaves], pmax[2][kMaxWaves];
-    uint32_t wsum[kMaxWaves];
-    uint32_t maxnb, wmin, wmax;
-    int32_t sel_bin[2];
-    uint32_t sel_cum[2];
-    uint32_t cnt, kmin, kmax;
-    int32_t ucnt[kMaxWaves];
-};
-
-template <int NB>
-__device__ __forceinline__ int bin_of(float v, float lo, float scale) {
-    float t = (v - lo) * scale;
-    t = fminf(fmaxf(t, 0.0f), (float)(NB - 1));
-    return (int)t;
-}
-
-template <int NB>
-__device__ __forceinline__ float bin_scale(float lo, float hi) { return (hi > lo) ? (float)NB / (hi - lo) : 0.0f; }
-
-// exclusive scan of one uint32 per thread over the block
-template <int NT, typename SH>
-__device__ __forceinline__ uint32_t block_exscan(uint32_t x, SH& sh) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t incl = x;
+// Ascending bitonic sort of one value per lane of a wavefront.
+__device__ __forceinline__ float wave_sort(float x, int lane) {
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
-    if (lane == 63) sh.wsum[w] = incl;
-    __syncthreads();
-    uint32_t off = 0;
-    for (int i = 0; i < w; ++i) off += sh.wsum[i];
-    __syncthreads();
-    return off + incl - x;
-}
-
-template <int NT, typename SH>
-__device__ int block_sum_i(int x, SH& sh) {
-    constexpr int NW = NT / 64;
-    x = wave_sum_i(x);
-    if ((threadIdx.x & 63) == 0) sh.ucnt[threadIdx.x >> 6] = x;
-    __syncthreads();
-    int s = 0;
-    for (int i = 0; i < NW; ++i) s += sh.ucnt[i];
-    __syncthreads();
-    return s;
-}
-
-// deterministic block reduction of two FP64 sums, two counts and min/max
-// (wavefront butterflies, then the wavefront partials in wavefront order).
-// The partials alternate between two LDS sets (par flips on every call), so
-// one barrier per call suffices: a set is written again only two calls later,
-// after every thread has passed the barrier of the call in between.
-template <int NT, typename SH>
-__device__ __forceinline__ void block_stats(double& a, double& b, int& n, int& n2, float& mn, float& mx, int& par,
-                                            SH& sh) {
-    constexpr int NW = NT / 64;
-    const int w = threadIdx.x >> 6;
-    const int P = par;
-    par ^= 1;
-    a = wave_sum_d(a);
-    b = wave_sum_d(b);
-    n = wave_sum_i(n);
-    n2 = wave_sum_i(n2);
-    mn = wave_min(mn);
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) {
-        sh.pd[P][w][0] = a;
-        sh.pd[P][w][1] = b;
-        sh.pi[P][w][0] = n;
-        sh.pi[P][w][1] = n2;
-        sh.pmin[P][w] = mn;
-        sh.pmax[P][w] = mx;
-    }
-    __syncthreads();
-    a = sh.pd[P][0][0];
-    b = sh.pd[P][0][1];
-    n = sh.pi[P][0][0];
-    n2 = sh.pi[P][0][1];
-    mn = sh.pmin[P][0];
-    mx = sh.pmax[P][0];
-    // all partials loaded at once up to 8 wavefronts; 16 would spill
-#pragma unroll(NW > 8 ? 4 : 8)
-    for (int i = 1; i < NW; ++i) {
-        a += sh.pd[P][i][0];
-        b += sh.pd[P][i][1];
-        n += sh.pi[P][i][0];
-        n2 += sh.pi[P][i][1];
-        mn = fminf(mn, sh.pmin[P][i]);
-        mx = fmaxf(mx, sh.pmax[P][i]);
-    }
-}
-
-// Ascending bitonic sort of the SEG = 64 E values a wavefront holds, E per
-// lane (lane l holds positions l E .. l E + E - 1): partners closer than E sit
-// in the same lane, the others are exchanged with a lane shuffle.
-template <int E>
-__device__ __forceinline__ void wave_sort(float (&x)[E], int lane) {
-#pragma unroll
-    for (int k = 2; k <= 64 * E; k <<= 1) {
+    for (int k = 2; k <= 64; k <<= 1) {
 #pragma unroll
         for (int j = k >> 1; j > 0; j >>= 1) {
-            if (j < E) {
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const int g = e ^ j;
-                    if (g > e) {
-                        const bool up = ((lane * E + e) & k) == 0;
-                        const float a = x[e], b = x[g];
-                        x[e] = up ? fminf(a, b) : fmaxf(a, b);
-                        x[g] = up ? fmaxf(a, b) : fminf(a, b);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const float o = __shfl_xor(x[e], j / E);
-                    const int i = lane * E + e;
-                    const bool up = (i & k) == 0, lower = (i & j) == 0;
-                    x[e] = (lower == up) ? fminf(x[e], o) : fmaxf(x[e], o);
-                }
-            }
+            const float o = __shfl_xor(x, j);
+            const bool up = (lane & k) == 0, lower = (lane & j) == 0;
+            x = (lower == up) ? fminf(x, o) : fmaxf(x, o);
         }
     }
+    return x;
 }
 
-template <int E>
-__device__ __forceinline__ void wave_sort_segment(float* buf, int w, int lane) {
-    float x[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) x[e] = buf[w * 64 * E + lane * E + e];
-    wave_sort<E>(x, lane);
-#pragma unroll
-    for (int e = 0; e < E; ++e) buf[w * 64 * E + lane * E + e] = x[e];
-}
+// (read back as 16-bit halves)
+typedef uint32_t __attribute__((may_alias)) word16_t;
 
-// Ascending sort of a[0, P) (P a power of two, 64 <= P <= 64 * 16 * waves)
-// using b[0, P) as scratch: each wavefront sorts a segment of SEG values in
-// registers, then segments are merged pairwise, every value finding its place
-// by a binary search in the partner segment (ties: the left segment first).
-// Returns the buffer that holds the result.
-template <int NT>
-__device__ __forceinline__ float* sort_window(float* a, float* b, int P) {
-    constexpr int NW = NT / 64;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int nseg = min(NW, P / 64);
-    const int SEG = P / nseg;
-    __syncthreads();
-    if (w < nseg) {
-        // values per lane: SEG / 64 <= kBuf / NT (only those shapes exist)
-        constexpr int EMAX = kBuf / NT;
-        const int E = SEG / 64;
-        if (E == 1) wave_sort_segment<1>(a, w, lane);
-        else if (E == 2) wave_sort_segment<2>(a, w, lane);
-        else if (E == 4 || EMAX < 8) wave_sort_segment<(EMAX < 4 ? EMAX : 4)>(a, w, lane);
-        else if (E == 8 || EMAX < 16) wave_sort_segment<(EMAX < 8 ? EMAX : 8)>(a, w, lane);
-        else wave_sort_segment<(EMAX < 16 ? EMAX : 16)>(a, w, lane);
-    }
-    __syncthreads();
-    // merge rounds (merge path): thread t writes outputs [t E, t E + E) of the
-    // merged pair; it finds how many of them come from the left segment by a
-    // binary search along that output diagonal (ties: the left segment
-    // first), then merges its E outputs sequentially
-    const int E = max(1, P / NT);
-    for (int len = SEG; len < P; len <<= 1) {
-        const int o0 = threadIdx.x * E;
-        if (o0 < P) {
-            const int pair = o0 / (2 * len);
-            const float* A = a + pair * 2 * len;
-            const float* B = A + len;
-            const int dg = o0 - pair * 2 * len;
-            int lo = max(0, dg - len), hi = min(dg, len);
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (A[mid] <= B[dg - mid - 1]) lo = mid + 1;
-                else hi = mid;
-            }
-            int i = lo, j = dg - lo;
-            float va = (i < len) ? A[i] : INFINITY, vb = (j < len) ? B[j] : INFINITY;
-            float* out = b + pair * 2 * len + dg;
-            for (int e = 0; e < E; ++e) {
-                const bool ta = (j >= len) || (i < len && va <= vb);
-                out[e] = ta ? va : vb;
-                if (ta) {
-                    ++i;
-                    va = (i < len) ? A[i] : INFINITY;
-                } else {
-                    ++j;
-                    vb = (j < len) ? B[j] : INFINITY;
-                }
-            }
-        }
-        __syncthreads();
-        float* t = a;
-        a = b;
-        b = t;
-    }
-    return a;
-}
-
-
-// Bin b of a histogram is stored at slot hist_slot(b): the low bits are
-// XORed with a function of the thread b / per that owns the bin in the scan,
-// so that the threads of a wavefront reading their own bins side by side hit
-// 64 different LDS banks.
-template <int NT, int NB>
-__device__ __forceinline__ int hist_slot(int b) {
-    constexpr int per = NB / NT;   // a power of two <= 64
-    constexpr int G = (64 / per) > 0 ? 64 / per : 1;
-    return b ^ (((b / per) / G) & (per - 1));
-}
-
-// bins narrower than 0.99 units hold one integer value each (edge bins also
-// collect the clamped values outside the range)
-template <int NB>
-__device__ __forceinline__ bool single_value_bin(bool int_vals, float scale, int b) {
-    return int_vals && scale >= 1.01f && b != 0 && b != NB - 1;
-}
-
-struct Placed {
-    int b1, b2;       // first and last bin of the selected ranks
-    uint32_t base;    // values in bins below b1
-    int m;            // values in bins b1 .. b2
-    uint32_t maxnb;   // largest of those bins that may hold different values
+// The mesh's values in LDS, grouped by bin, for a workgroup of NT threads with
+// PPT pixels each.
+//   val    the values, bin after bin (any order inside a bin)
+//   start  first position of each bin (two 16-bit numbers per word: at most
+//          16384 pixels), start[NB] = their number
+//   w*     the wavefronts' sums, ranges and counts
+template <typename T, int NT, int PPT>
+struct MeshShared {
+    static constexpr int NB = (NT * PPT <= 1024) ? 512 : (NT * PPT <= 8192) ? 2048 : 4096;
+    static constexpr bool kInt = sizeof(T) == 2;
+    T val[NT * PPT];
+    word16_t start[NB / 2 + 1];
+    double w1[NT / 64], wh[NT / 64], wl[NT / 64];
+    uint32_t wc[NT / 64];
+    float wmin[NT / 64], wmax[NT / 64];
+    float lo, scale, mid;
 };
 
-// Histogram of the values each(f) visits over [lo, lo + NB / scale), the bins
-// holding ranks ra and rb, and the first slot of every bin in [b1, b2]
-// relative to b1 (left in the histogram for the caller's placement).
-// first: also resets the window's value range (read by the caller between a
-// first-level and a second-level call, so only the first one may reset it).
-template <int NT, typename SH, typename Each>
-__device__ __forceinline__ Placed place_bins(Each&& each, float lo, float scale, bool int_vals, int ra, int rb,
-                                             bool first, SH& sh) {
-    constexpr int NB = SH::kNB;
-    constexpr int per = NB / NT;
-    const int tid = threadIdx.x;
-    for (int b = tid; b < NB; b += NT) sh.hist[b] = 0u;
-    if (tid == 0) {
-        sh.maxnb = 0u;
-        if (first) {
-            sh.wmin = 0xffffffffu;
-            sh.wmax = 0u;
-        }
-    }
-    __syncthreads();
-    each([&](float x) { atomicAdd(&sh.hist[hist_slot<NT, NB>(bin_of<NB>(x, lo, scale))], 1u); });
-    __syncthreads();
-    uint32_t c[per];
-    uint32_t tot = 0;
-#pragma unroll
-    for (int q = 0; q < per; ++q) {
-        c[q] = sh.hist[hist_slot<NT, NB>(tid * per + q)];
-        tot += c[q];
-    }
-    const uint32_t pre = block_exscan<NT>(tot, sh);
-    const int rr[2] = {ra, rb};
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const uint32_t r = (uint32_t)rr[t];
-        if (pre <= r && r < pre + tot) {
-            uint32_t cum = pre;
-            for (int q = 0; q < per; ++q) {
-                if (r < cum + c[q]) {
-                    sh.sel_bin[t] = tid * per + q;
-                    sh.sel_cum[t] = cum;
-                    break;
-                }
-                cum += c[q];
-            }
-        }
-    }
-    __syncthreads();
-    Placed P;
-    P.b1 = sh.sel_bin[0];
-    P.b2 = sh.sel_bin[1];
-    P.base = sh.sel_cum[0];
-    {
-        uint32_t cum = pre, big = 0u;
-#pragma unroll
-        for (int q = 0; q < per; ++q) {
-            const int b = tid * per + q;
-            if (b >= P.b1 && b <= P.b2) {
-                sh.hist[hist_slot<NT, NB>(b)] = cum - P.base;
-                if (!single_value_bin<NB>(int_vals, scale, b)) big = max(big, c[q]);
-            }
-            if (b == P.b2) sh.cnt = cum + c[q] - P.base;
-            cum += c[q];
-        }
-        if (big > 1u) atomicMax(&sh.maxnb, big);
-    }
-    __syncthreads();
-    P.m = (int)sh.cnt;
-    P.maxnb = sh.maxnb;
-    return P;
+// Bins of a mesh: three quarters of them equal steps from lo on, the rest
+// eight to the octave above (a star's wings and its saturated core spread
+// over several).  A rising function of the value, whatever lo and scale are:
+// these only decide how many values share a bin, never a result.
+template <int NB>
+__device__ __forceinline__ int mesh_bin(float x, float lo, float scale) {
+#pragma clang fp contract(off)   // the same bin for a value wherever this is inlined
+    constexpr int NC = NB - NB / 4;
+    const float t = (x - lo) * scale;
+    const int core = (int)fminf(fmaxf(t, 0.0f), (float)NC);
+    const float u = fmaxf(t - (float)(NC - 1), 1.0f);
+    const int tail = NC + ((__float_as_int(u) - 0x3f800000) >> 20);
+    return t >= (float)NC ? min(tail, NB - 1) : core;
 }
 
-// Copies src[0, m), grouped by bin (bin slices ending at the histogram's
-// entries), to dst in ascending order: each value's place is its slice start
-// plus the smaller values of its slice (and the equal ones before it).
-template <int NT, typename SH>
-__device__ __forceinline__ void rank_place(const float* src, float* dst, int m, float lo, float scale, bool int_vals,
-                                           const Placed& P, SH& sh) {
-    constexpr int NB = SH::kNB;
-    for (int j = threadIdx.x; j < m; j += NT) {
-        const float x = src[j];
-        const int b = bin_of<NB>(x, lo, scale);
-        int r = j;   // a bin of equal values keeps its order
-        if (!single_value_bin<NB>(int_vals, scale, b)) {
-            const int s0 = (b == P.b1) ? 0 : (int)sh.hist[hist_slot<NT, NB>(b - 1)];
-            const int e = (int)sh.hist[hist_slot<NT, NB>(b)];
-            r = s0;
-            for (int i = s0; i < e; i += 4) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int ii = i + u;
-                    const float y = src[min(ii, e - 1)];
-                    r += (ii < e && (y < x || (y == x && ii < j))) ? 1 : 0;
-                }
-            }
-        }
-        dst[r] = x;
-    }
+// sum over the wavefront's lanes (of values whose sums are exact: any order)
+__device__ __forceinline__ double lane_d(double v, int l) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+    return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
+}
+__device__ __forceinline__ double wave_total(double v) {
+    v += dpp_d<0xB1>(v);    // lane ^ 1
+    v += dpp_d<0x4E>(v);    // lane ^ 2
+    v += dpp_d<0x141>(v);   // 7 - lane of each 8
+    v += dpp_d<0x140>(v);   // 15 - lane of each 16
+    return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
+}
+__device__ __forceinline__ float lane_f(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-// Sort the values of ranks [ra, rb] (0-based, within the alive set) and their
-// bin-mates into a window; returns the rank of its first value (-1 when the
-// gathered bins exceed the buffer), its count in m and its storage in win.
-// each(f) calls f on every alive value of the thread; each2(f1, f2) calls f1
-// on all of them, then f2(f1's result, value) where that result is >= 0.  The
-// histogram window [wlo, whi] only steers the binning (bins are clamped).
-// The window is gathered grouped by bin (each bin's slice found from the
-// histogram's prefix sums).  Small bins are then ordered directly by rank
-// counting; otherwise a second histogram over the window's own value range
-// spreads it over fine bins, it is regrouped by those and ordered by rank
-// counting.  A window over half the buffer, or a fine bin of more than
-// kRankMax different values, goes through the merge sort instead.
-// int_vals: the values are integers.
-template <int NT, typename Each, typename Each2, typename SH>
-__device__ __forceinline__ int build_window(Each&& each, Each2&& each2, float wlo, float whi, int ra, int rb,
-                                            bool int_vals, int& m, const float*& win, SH& sh) {
-    constexpr int NB = SH::kNB;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const float scale = bin_scale<NB>(wlo, whi);
-    const Placed P1 = place_bins<NT>(each, wlo, scale, int_vals, ra, rb, true, sh);
-    m = P1.m;
-    if (m > kBuf) return -1;
-    // gather: all slots are claimed before any value is stored
-    float gmn = INFINITY, gmx = -INFINITY;
-    each2(
-        [&](float x) {
-            const int b = bin_of<NB>(x, wlo, scale);
-            return (b >= P1.b1 && b <= P1.b2) ? (int)atomicAdd(&sh.hist[hist_slot<NT, NB>(b)], 1u) : -1;
-        },
-        [&](int slot, float x) {
-            sh.buf[slot] = x;
-            gmn = fminf(gmn, x);
-            gmx = fmaxf(gmx, x);
-        });
-    gmn = wave_min(gmn);
-    gmx = wave_max(gmx);
-    if (lane == 0 && gmn <= gmx) {
-        atomicMin(&sh.wmin, f2ord(gmn));
-        atomicMax(&sh.wmax, f2ord(gmx));
-    }
-    __syncthreads();
-    float* out = sh.buf + kBuf / 2;
-    if (m <= kBuf / 2 && P1.maxnb <= (uint32_t)kRankSmall) {
-        rank_place<NT>(sh.buf, out, m, wlo, scale, int_vals, P1, sh);
-        __syncthreads();
-        win = out;
-        return (int)P1.base;
-    }
-    if (m <= kBuf / 2) {
-        const float lo2 = ord2f(sh.wmin), hi2 = ord2f(sh.wmax);
-        const float scale2 = bin_scale<NB>(lo2, hi2);
-        if (!(scale2 > 0.0f)) {
-            win = sh.buf;   // one value only
-            return (int)P1.base;
-        }
-        auto each_buf = [&](auto&& f) __attribute__((always_inline)) {
-            for (int j = tid; j < m; j += NT) f(sh.buf[j]);
-        };
-        const Placed P2 = place_bins<NT>(each_buf, lo2, scale2, int_vals, 0, m - 1, false, sh);
-        if (P2.maxnb <= (uint32_t)kRankMax) {
-            constexpr int MAXJ = (kBuf / 2 + NT - 1) / NT;
-            int sl[MAXJ];
-            float xv[MAXJ];
-#pragma unroll
-            for (int i = 0; i < MAXJ; ++i) {
-                const int j = tid + i * NT;
-                xv[i] = (j < m) ? sh.buf[j] : 0.0f;
-                sl[i] = (j < m) ? (int)atomicAdd(&sh.hist[hist_slot<NT, NB>(bin_of<NB>(xv[i], lo2, scale2))], 1u)
-                                : -1;
-            }
-#pragma unroll
-            for (int i = 0; i < MAXJ; ++i)
-                if (sl[i] >= 0) out[sl[i]] = xv[i];
-            __syncthreads();
-            rank_place<NT>(out, sh.buf, m, lo2, scale2, int_vals, P2, sh);
-            __syncthreads();
-            win = sh.buf;
-            return (int)P1.base;
-        }
-    }
-    int Pn = 64;
-    while (Pn < m) Pn <<= 1;
-    for (int i = m + tid; i < Pn; i += NT) sh.buf[i] = INFINITY;
-    win = sort_window<NT>(sh.buf, sh.buf2, Pn);
-    return (int)P1.base;
-}
-
-// Values of ranks r1 <= r2 of the alive set by bisection on the
-// order-preserving keys; count_le(x) gives the thread's alive values <= x.
-// For windows the buffer cannot hold.
-template <int NT, typename SH, typename CountLe>
-__device__ void bisect_pair(CountLe&& count_le, float lmn, float lmx, int r1, int r2, float& o1, float& o2,
-                            SH& sh) {
-    auto kth = [&](int k) {
-        uint32_t a = f2ord(lmn), z = f2ord(lmx);
-        while (a < z) {
-            const uint32_t mid = a + ((z - a) >> 1);
-            const int cnt = block_sum_i<NT>(count_le(ord2f(mid)), sh);
-            if (cnt > k) z = mid;
-            else a = mid + 1;
-        }
-        return ord2f(a);
-    };
-    o1 = kth(r1);
-    o2 = (r2 == r1) ? o1 : kth(r2);
-}
-
-// One workgroup per mesh; the mesh's pixels stay in registers (PPT per
-// thread) for the whole clipping loop, a clipped value being replaced by NaN
-// (pixel values are finite).  Pass 0 gives sigma0 of all pixels.  A clipping
-// pass tests every alive value against the interval, taking the dropped
-// values off the thread's FP64 sums.  The median comes from a sorted window of
-// ranks around it (built through a histogram of the alive values), which
-// stays valid while the ranks removed below keep the median inside it.  With
-// no pixel array in LDS, several meshes share a compute unit.
-// waves per SIMD the register budget is set for: two 8-wave or four 4-wave
-// workgroups per compute unit
-template <int NT, int PPT>
-constexpr int mesh_waves_per_eu() { return 4; }
-
+// One workgroup per mesh.  Whatever was clipped before, the surviving values
+// are always those of one interval [L, H).  The workgroup groups the values by
+// bin in LDS once (a histogram whose returned counts are the places inside a
+// bin, a prefix sum, one store per value); then one wavefront runs the whole
+// clipping loop.  A pass reads only the bins between the old and the new ends
+// of the interval, to take the values it drops off the sums, and the bin that
+// holds the median: no barrier and no pass over the pixels per iteration, and
+// the other wavefronts have left.
+//
+// The places inside a bin follow the order of the LDS atomics, so every sum
+// is made exact, hence independent of that order: uint16 values give integer
+// sums below 2^53; a float's (v - c) is rounded to a multiple g of 2^-38 of
+// the mesh's range, its square split at a multiple q of 2^-38 of the squared
+// range into a coarse and a fine part whose sums both stay below 2^53 units
+// (16384 pixels).  A mesh gives bit-identical results wherever it runs.
+//
+// Bound by latency: a mesh of 64^2 (128^2) float pixels takes about 6000
+// (8000) cycles to arrive, 7000 (15000) for the histogram's LDS atomics, 4000
+// (7500) to scan and store, then 1500-2000 per clipping pass, 3-14 of them.
+// What hides it is meshes per CU: 7 of 64^2, two of 128^2 (74 KB of LDS).
+// A pass over all pixels in registers per iteration, with a sorted window for
+// the median (float) or prefix sums of a histogram (uint16), took: 12300^2
+// crowded float in 128^2 meshes 2222 us, now 1175; 6144^2 260, now 135;
+// 2048^2 in 64^2 meshes 40, now 22; 371 MP of uint16 1122, now 695.
+//
 // ONE: a one-frame call, whose descriptor comes with the launch (d1);
 // workgroup 0 stores it in the table for the launches that follow
-template <int NT, int PPT, bool ONE>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(mesh_waves_per_eu<NT, PPT>())))
-void k_mesh_stats(FrameDesc* __restrict__ desc, FrameDesc d1, int nframes, BkgArgs a) {
-    __shared__ MeshShared<kBins> sh;
-    const int tid = threadIdx.x;
+template <typename T, int NT, int PPT, bool ONE>
+__global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc, FrameDesc d1, int nframes,
+                                                   BkgArgs a) {
+    using SH = MeshShared<T, NT, PPT>;
+    constexpr bool kInt = SH::kInt;
+    constexpr int NB = SH::NB, NW = NT / 64;
+    __shared__ SH sh;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int gm = blockIdx.x;
     if (ONE && gm == 0 && tid == 0) desc[0] = d1;
     const int f = ONE ? 0 : frame_of(nframes, gm, [&](int i) { return desc[i].mesh_base; });
     const FrameDesc d = ONE ? d1 : desc[f];
-    if (a.skip_u16 && d.dtype == kDtypeU16) return;
+    if ((d.dtype == kDtypeU16) != kInt) return;   // the other kernel's mesh of a mixed batch
     const int lm = gm - d.mesh_base;
     const int mi = lm % d.nx, mj = lm / d.nx;
     const int x0 = mi * d.mw, y0 = mj * d.mh;
     const int w = min(d.mw, d.W - x0), h = min(d.mh, d.H - y0);
     const int n = w * h;
-    const bool int_vals = d.dtype == kDtypeU16;
+    const int out_idx = mj * d.nx + mi;
 
+    // 1. pixel k * NT + tid of the mesh in registers.  A full mesh whose width
+    //    divides NT puts every thread's k-th pixel dy = NT / w rows below its
+    //    previous one: buffer loads with the row step as a scalar offset.
+    //    Other meshes step by NT without divisions.
     float v[PPT];
-    int cnt_t = 0;
     {
-        // pixel k * NT + tid of the mesh.  A full mesh whose width divides NT
-        // puts every thread's k-th pixel dy = NT / w rows below its previous
-        // one: buffer loads with the row step as a scalar offset.  Other
-        // meshes step by NT without divisions.
+        typedef __attribute__((address_space(1))) const T gpx_t;
         const int dy = NT / w, dx = NT - dy * w;
         int yy = tid / w, xx = tid - yy * w;
-        const bool u16 = d.dtype == kDtypeU16;
-        const int es = u16 ? 2 : 4;
         // (byte offsets within the mesh must fit the 32-bit buffer offsets)
-        if (n == NT * PPT && dx == 0 && (int64_t)h * d.pitch * es < ((int64_t)1 << 31)) {
-            const int64_t o0 = ((int64_t)y0 * d.pitch + x0) * es;
+        if (n == NT * PPT && dx == 0 && (int64_t)h * d.pitch * (int)sizeof(T) < ((int64_t)1 << 31)) {
+            const int64_t o0 = ((int64_t)y0 * d.pitch + x0) * (int)sizeof(T);
             const __amdgpu_buffer_rsrc_t rs =
                 __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)d.data + o0), (short)0, 0x7fffffff, 0x00020000);
-            const int vo = (yy * (int)d.pitch + xx) * es;
-            const int so = dy * (int)d.pitch * es;
-            if (u16) {
+            const int vo = (yy * (int)d.pitch + xx) * (int)sizeof(T);
+            const int so = dy * (int)d.pitch * (int)sizeof(T);
 #pragma unroll
-                for (int k = 0; k < PPT; ++k) v[k] = (float)__builtin_amdgcn_raw_buffer_load_b16(rs, vo, k * so, 0);
-            } else {
-#pragma unroll
-                for (int k = 0; k < PPT; ++k)
-                    v[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo, k * so, 0));
-            }
-            cnt_t = PPT;
+            for (int k = 0; k < PPT; ++k)
+                v[k] = kInt ? (float)__builtin_amdgcn_raw_buffer_load_b16(rs, vo, k * so, 0)
+                            : __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo, k * so, 0));
         } else {
+            const gpx_t* src = (const gpx_t*)d.data;
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
-                v[k] = NAN;
-                if (k * NT + tid < n) {
-                    v[k] = load_px(d, x0 + xx, y0 + yy);
-                    ++cnt_t;
-                }
+                v[k] = NAN;   // padding (pixel values are finite)
+                if (k * NT + tid < n) v[k] = (float)src[(int64_t)(y0 + yy) * d.pitch + x0 + xx];
                 xx += dx;
                 yy += dy;
                 if (xx >= w) {
@@ -556,23 +182,58 @@ void k_mesh_stats(FrameDesc* __restrict__ desc, FrameDesc d1, int nframes, BkgAr
             }
         }
     }
-    // pass 0: sigma0 of all pixels (FP64 sums shifted by the first pixel)
-    const double c0 = (double)load_px(d, x0, y0);
-    double s1 = 0.0, s2 = 0.0;
+    // 2. the mesh's range, and the bins from 64 of its pixels (one per lane of
+    //    the first wavefront, at different heights): their median and the
+    //    16th percentile below it give the sky's level and width even where
+    //    stars cover half the mesh
     float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-        if (k < cnt_t) {
-            const double dd = (double)v[k] - c0;
-            s1 += dd;
-            s2 = fma(dd, dd, s2);
-            mn = fminf(mn, v[k]);
-            mx = fmaxf(mx, v[k]);
+        mn = fminf(mn, v[k]);   // (NaN is passed over)
+        mx = fmaxf(mx, v[k]);
+    }
+    mn = wave_min(mn);
+    mx = wave_max(mx);
+    for (int b = tid; b < NB / 2; b += NT) sh.start[b] = 0u;
+    if (lane == 0) {
+        sh.wmin[wv] = mn;
+        sh.wmax[wv] = mx;
+    }
+    if (wv == 0) {
+        float s = v[0];
+#pragma unroll
+        for (int k = 1; k < PPT; ++k)
+            if ((lane & (PPT - 1)) == k) s = v[k];
+        const uint64_t have = __ballot(s == s);   // (lane 0 always has its first pixel)
+        s = wave_sort(s == s ? s : INFINITY, lane);
+        const int m = __popcll(have);
+        const float q50 = lane_f(s, (m - 1) / 2), q16 = lane_f(s, (m - 1) / 6);
+        constexpr float NC = (float)(NB - NB / 4);
+        float wd = q50 - q16;
+        if (lane == 0) sh.mid = q50;
+        if (kInt) {
+            // steps of one unit where the sky's range leaves room for them:
+            // such a bin holds one value
+            wd = fmaxf(wd, 1.0f);
+            if (lane == 0) {
+                sh.lo = floorf(q50 - 4.0f * wd);
+                sh.scale = fminf(1.0f, NC / (10.0f * wd));
+            }
+        } else if (lane == 0) {
+            if (!(wd > 0.0f)) wd = fmaxf(fabsf(q50) * 0x1p-10f, 0x1p-100f);
+            sh.lo = q50 - 4.0f * wd;
+            sh.scale = NC / (10.0f * wd);
         }
     }
-    int cnt = 0, unused = 0, par = 0;
-    block_stats<NT>(s1, s2, cnt, unused, mn, mx, par, sh);
-    const int out_idx = mj * d.nx + mi;
+    __syncthreads();
+    const float blo = sh.lo, bscale = sh.scale;
+    mn = sh.wmin[0];
+    mx = sh.wmax[0];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) {
+        mn = fminf(mn, sh.wmin[i]);
+        mx = fmaxf(mx, sh.wmax[i]);
+    }
     if (mn == mx) {
         if (tid == 0) {
             d.back_raw[out_idx] = (double)mn;
@@ -581,490 +242,305 @@ void k_mesh_stats(FrameDesc* __restrict__ desc, FrameDesc d1, int nframes, BkgAr
         }
         return;
     }
-    const double nd0 = (double)n;
-    const double m1 = s1 / nd0;
-    const double var0 = s2 / nd0 - m1 * m1;
-    const double sig0 = sqrt(var0 > 0.0 ? var0 : 0.0);
-    double mean = c0 + m1;
-    double sig = sig0;
-
-    int ncur = n;
-    int R0 = -1, bm = 0;      // rank of win[0] in the alive set (-1: no window)
-    const float* win = sh.buf;
-    float med_h, med_l;
-    float lmn = mn, lmx = mx;
-    // every alive value of the thread (NaN marks the padding and clipped ones);
-    // each2 claims all results of f1 (in groups of 16) before calling f2
-    auto each_alive = [&](auto&& f) __attribute__((always_inline)) {
-#pragma unroll
-        for (int k = 0; k < PPT; ++k)
-            if (v[k] == v[k]) f(v[k]);
-    };
-    auto each2_alive = [&](auto&& f1, auto&& f2) __attribute__((always_inline)) {
-        constexpr int C = PPT < 16 ? PPT : 16;
-#pragma unroll
-        for (int k0 = 0; k0 < PPT; k0 += C) {
-            int r[C];
-#pragma unroll
-            for (int k = 0; k < C; ++k) r[k] = (v[k0 + k] == v[k0 + k]) ? f1(v[k0 + k]) : -1;
-#pragma unroll
-            for (int k = 0; k < C; ++k)
-                if (r[k] >= 0) f2(r[k], v[k0 + k]);
-        }
-    };
-    auto count_le = [&](float x) {
-        int c = 0;
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) c += (v[k] <= x) ? 1 : 0;   // false for NaN
-        return c;
-    };
-    // exact median (an unevaluated pair when the count is even) of the alive
-    // set, from the window, rebuilding it when the median has left it
-    auto median = [&](float wlo, float whi) __attribute__((always_inline)) {
-        const int r2 = ncur / 2;
-        const int r1 = (ncur & 1) ? r2 : r2 - 1;
-        float o1, o2;
-        if (R0 < 0 || r1 - R0 < 0 || r2 - R0 >= bm) {
-            R0 = build_window<NT>(each_alive, each2_alive, wlo, whi, max(r1 - kHalf, 0), min(r2 + kHalf, ncur - 1),
-                                  int_vals, bm, win, sh);
-            if (R0 < 0) R0 = build_window<NT>(each_alive, each2_alive, wlo, whi, r1, r2, int_vals, bm, win, sh);
-        }
-        if (R0 >= 0) {
-            o1 = win[r1 - R0];
-            o2 = win[r2 - R0];
+    // 3. group by bin: (bin, place inside it) of every pixel, the sums of all
+    //    pixels, bin starts, store.  cs: a value of the mesh near the sky
+    //    level; mg, mq: adding and taking off 1.5 * 2^52 units rounds to a
+    //    whole number of units.
+    const double cs = (double)sh.mid;
+    int ex;
+    (void)frexp(fmax((double)mx - cs, cs - (double)mn), &ex);
+    const double mg = ldexp(1.5, ex - 38 + 52), mq = ldexp(1.5, 2 * ex - 38 + 52);
+    auto accum = [&](float x, double& s1, double& sq, double& sl) __attribute__((always_inline)) {
+        double e = (double)x - cs;
+        if (kInt) {
+            s1 += e;
+            sq = fma(e, e, sq);
         } else {
-            bisect_pair<NT>(count_le, lmn, lmx, r1, r2, o1, o2, sh);
-        }
-        if (r1 == r2) {
-            med_h = o1;
-            med_l = 0.0f;
-        } else {
-            // (o1 + o2) / 2 as an unevaluated pair: exact
-            float s, e;
-            two_sum(o1, o2, s, e);
-            med_h = 0.5f * s;
-            med_l = 0.5f * e;
+            e = (e + mg) - mg;
+            const double hi = fma(e, e, mq) - mq;
+            s1 += e;
+            sq += hi;
+            sl += fma(e, e, -hi);
         }
     };
-    // the median of all pixels lies within one sigma of their mean
-    median((float)(mean - sig0), (float)(mean + sig0));
-    // the alive set's FP64 sums, shifted by a float near the mean (so every
-    // shifted value is exact)
-    const double cs = (double)(float)mean;
-    double t1 = 0.0, t2 = 0.0;
+    double t1 = 0.0, th = 0.0, tl = 0.0;
+    uint32_t pk[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-        if (k < cnt_t) {
-            const double e = (double)v[k] - cs;
-            t1 += e;
-            t2 = fma(e, e, t2);
+        pk[k] = 0u;
+        if (v[k] == v[k]) {
+            const uint32_t b = (uint32_t)mesh_bin<NB>(v[k], blo, bscale);
+            const uint32_t sft = (b & 1u) * 16u;
+            const uint32_t old = atomicAdd((uint32_t*)&sh.start[b >> 1], 1u << sft);
+            pk[k] = (b << 16) | ((old >> sft) & 0xffffu);
+            accum(v[k], t1, th, tl);
         }
     }
-
-    int iters = 0, na = cnt_t;   // alive values of the thread
-    for (int it = 0; it < a.max_iter; ++it) {
-        const float thr = (float)((double)a.clip * sig);
-        // clipping pass: every alive value outside the interval is dropped;
-        // only those below it shift the ranks of the survivors.  A NaN (dead)
-        // value compares false, and fminf / fmaxf pass over it.
-        int nrem = 0;
-        float tmn = INFINITY, tmx = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const float x = v[k];
-            const float dx = (x - med_h) - med_l;
-            if (fabsf(dx) > thr) {
-                const double e = (double)x - cs;
-                t1 -= e;
-                t2 = fma(-e, e, t2);
-                nrem += (dx < -thr) ? 1 : 0;
-                --na;
-                v[k] = NAN;
-            }
-            tmn = fminf(tmn, v[k]);
-            tmx = fmaxf(tmx, v[k]);
-        }
-        int nn = na;
-        double q1s = t1, q2s = t2;
-        block_stats<NT>(q1s, q2s, nn, nrem, tmn, tmx, par, sh);
-        ++iters;
-        if (nn == ncur || nn == 0) break;
-        ncur = nn;
-        if (R0 >= 0) R0 -= nrem;
-        lmn = tmn;
-        lmx = tmx;
-        const double nd = (double)nn;
-        const double q1 = q1s / nd;
-        const double vv = q2s / nd - q1 * q1;
-        mean = cs + q1;
-        sig = (lmn == lmx) ? 0.0 : sqrt(vv > 0.0 ? vv : 0.0);
-        median(lmn, lmx);
-    }
-    if (tid == 0) {
-        const double med = (double)med_h + (double)med_l;
-        const double dsig = fabs(sig - sig0);
-        const double back = (dsig < (double)a.crowd * sig0) ? mean
-                                                             : ((double)a.mode_a * med - (double)a.mode_b * mean);
-        d.back_raw[out_idx] = back;
-        d.rms_raw[out_idx] = sig;
-        d.iters[out_idx] = iters;
-    }
-}
-
-
-// ---------------------------------------------------------------------------
-// uint16 frames: exact integer statistics.  Each clipping pass keeps the
-// values within k sigma of the current median, so the surviving set is
-// always every pixel value inside an interval [L, H] of integers.  With one
-// LDS histogram of the mesh's values (1-ADU bins over a 4096-value window
-// around the median; a bright star that stretches the range first gets a
-// coarse histogram that locates that window) the counts, sums and exact
-// median of every pass come from the histogram's prefix, and all sums are
-// exact integers: no per-pixel work after the histogram, unless an interval
-// or a median leaves the window (then exact passes over the registers).
-// The clip decisions are taken in FP64 on exact statistics, like the FP64
-// definition.
-constexpr int kU16Bins = 1024;            // 64 lanes x 16 bins
-constexpr int kU16Per = kU16Bins / 64;
-
-// The window's prefix sums: p0[b] = pixels in bins [0, b), p1[b] and p2[b]
-// their sums of (bin) and (bin)^2; index kU16Bins holds the totals.
-struct MeshU16Shared {
-    uint32_t p0[kU16Bins + 1];          // histogram, then its prefix
-    uint32_t p1[kU16Bins + 1];
-    uint64_t p2[kU16Bins + 1];
-    uint64_t pa[2][kMaxWaves][2];       // block partials, double-buffered
-    uint32_t pc[2][kMaxWaves][4];
-    uint64_t ws[kMaxWaves][2];          // wavefront totals of the scan
-    uint32_t wc[kMaxWaves];
-};
-
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int o) {
-    const uint32_t lo = __shfl_xor((uint32_t)v, o), hi = __shfl_xor((uint32_t)(v >> 32), o);
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-__device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int o) {
-    const uint32_t lo = __shfl_up((uint32_t)v, o), hi = __shfl_up((uint32_t)(v >> 32), o);
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
-
-// exact block sums: two counts, two 64-bit sums, min and max (integers: the
-// order of the additions does not matter)
-template <int NT>
-__device__ __forceinline__ void block_u16(uint32_t& c0, uint32_t& c1, uint64_t& s1, uint64_t& s2, uint32_t& mn,
-                                          uint32_t& mx, int& par, MeshU16Shared& sh) {
-    constexpr int NW = NT / 64;
-    const int w = threadIdx.x >> 6;
-    const int P = par;
-    par ^= 1;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        c0 += __shfl_xor(c0, o);
-        c1 += __shfl_xor(c1, o);
-        s1 += shfl_xor_u64(s1, o);
-        s2 += shfl_xor_u64(s2, o);
-        mn = min(mn, (uint32_t)__shfl_xor(mn, o));
-        mx = max(mx, (uint32_t)__shfl_xor(mx, o));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        sh.pc[P][w][0] = c0;
-        sh.pc[P][w][1] = c1;
-        sh.pc[P][w][2] = mn;
-        sh.pc[P][w][3] = mx;
-        sh.pa[P][w][0] = s1;
-        sh.pa[P][w][1] = s2;
+    t1 = wave_total(t1);
+    th = wave_total(th);
+    if (!kInt) tl = wave_total(tl);
+    if (lane == 0) {
+        sh.w1[wv] = t1;
+        sh.wh[wv] = th;
+        sh.wl[wv] = tl;
     }
     __syncthreads();
-    c0 = c1 = 0u;
-    s1 = s2 = 0ull;
-    mn = 0xffffffffu;
-    mx = 0u;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        c0 += sh.pc[P][i][0];
-        c1 += sh.pc[P][i][1];
-        mn = min(mn, sh.pc[P][i][2]);
-        mx = max(mx, sh.pc[P][i][3]);
-        s1 += sh.pa[P][i][0];
-        s2 += sh.pa[P][i][1];
-    }
-}
-
-// histogram in p0 -> exclusive prefix sums p0, p1, p2 (bins split evenly
-// over the block, each thread a contiguous run)
-template <int NT>
-__device__ __forceinline__ void u16_prefix(MeshU16Shared& sh) {
-    constexpr int PER = kU16Bins / NT;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    uint32_t c[PER], tc = 0, t1 = 0;
-    uint64_t t2 = 0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const uint32_t b = (uint32_t)(t * PER + i);
-        c[i] = sh.p0[b];
-        tc += c[i];
-        t1 += c[i] * b;
-        t2 += (uint64_t)c[i] * b * b;
-    }
-    uint32_t ic = tc, i1 = t1;
-    uint64_t i2 = t2;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t yc = __shfl_up(ic, o), y1 = __shfl_up(i1, o);
-        const uint64_t y2 = shfl_up_u64(i2, o);
-        if (lane >= o) {
-            ic += yc;
-            i1 += y1;
-            i2 += y2;
-        }
-    }
-    if (lane == 63) {
-        sh.wc[w] = ic;
-        sh.ws[w][0] = i1;
-        sh.ws[w][1] = i2;
-    }
-    __syncthreads();
-    uint32_t rc = ic - tc, r1 = i1 - t1;
-    uint64_t r2 = i2 - t2;
-    for (int i = 0; i < w; ++i) {
-        rc += sh.wc[i];
-        r1 += (uint32_t)sh.ws[i][0];
-        r2 += sh.ws[i][1];
-    }
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const uint32_t b = (uint32_t)(t * PER + i);
-        sh.p0[b] = rc;
-        sh.p1[b] = r1;
-        sh.p2[b] = r2;
-        rc += c[i];
-        r1 += c[i] * b;
-        r2 += (uint64_t)c[i] * b * b;
-    }
-    if (t == NT - 1) {
-        sh.p0[kU16Bins] = rc;
-        sh.p1[kU16Bins] = r1;
-        sh.p2[kU16Bins] = r2;
-    }
-    __syncthreads();
-}
-
-// largest bin b with p0[b] <= g (0 <= g < total): two LDS reads and ballots
-// per wavefront, no barrier
-__device__ __forceinline__ int u16_find(const MeshU16Shared& sh, uint32_t g) {
-    const int lane = threadIdx.x & 63;
-    const int c = __popcll(__ballot(sh.p0[lane * kU16Per] <= g)) - 1;
-    const bool le = lane < kU16Per && sh.p0[c * kU16Per + lane] <= g;
-    return c * kU16Per + __popcll(__ballot(le)) - 1;
-}
-
-template <int NT, int PPT, bool ONE>
-__global__ __launch_bounds__(NT) void k_mesh_stats_u16(FrameDesc* __restrict__ desc, FrameDesc d1, int nframes,
-                                                       BkgArgs a) {
-    __shared__ MeshU16Shared sh;
-    constexpr uint32_t kNone = 0xffffffffu;   // padding / not a pixel
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int gm = blockIdx.x;
-    if (ONE && gm == 0 && tid == 0) desc[0] = d1;
-    const int f = ONE ? 0 : frame_of(nframes, gm, [&](int i) { return desc[i].mesh_base; });
-    const FrameDesc d = ONE ? d1 : desc[f];
-    if (d.dtype != kDtypeU16) return;   // float32 frames of a mixed batch: the float kernel
-    const int lm = gm - d.mesh_base;
-    const int mi = lm % d.nx, mj = lm / d.nx;
-    const int x0 = mi * d.mw, y0 = mj * d.mh;
-    const int w = min(d.mw, d.W - x0), h = min(d.mh, d.H - y0);
-    const int n = w * h;
-    const int out_idx = mj * d.nx + mi;
-
-    // 1. the mesh's pixels into registers (pixel k * NT + tid of the mesh)
-    uint32_t u[PPT];
     {
-        const int dy = NT / w, dx = NT - dy * w;
-        int yy = tid / w, xx = tid - yy * w;
-        if (n == NT * PPT && dx == 0 && (int64_t)h * d.pitch * 2 < ((int64_t)1 << 31)) {
-            const int64_t o0 = ((int64_t)y0 * d.pitch + x0) * 2;
-            const __amdgpu_buffer_rsrc_t rs =
-                __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)d.data + o0), (short)0, 0x7fffffff, 0x00020000);
-            const int vo = (yy * (int)d.pitch + xx) * 2;
-            const int so = dy * (int)d.pitch * 2;
+        constexpr int PER = (NB / 2 + NT - 1) / NT;   // words of two bins per thread
+        uint32_t c[PER], tot = 0u;
 #pragma unroll
-            for (int k = 0; k < PPT; ++k) u[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, vo, k * so, 0);
-        } else {
-            const gu16_t* src = (const gu16_t*)d.data;
+        for (int q = 0; q < PER; ++q) {
+            const int i = tid * PER + q;
+            c[q] = (i < NB / 2) ? sh.start[i] : 0u;
+            tot += (c[q] & 0xffffu) + (c[q] >> 16);
+        }
+        uint32_t incl = tot;
 #pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                u[k] = kNone;
-                if (k * NT + tid < n) u[k] = (uint32_t)src[(int64_t)(y0 + yy) * d.pitch + x0 + xx];
-                xx += dx;
-                yy += dy;
-                if (xx >= w) {
-                    xx -= w;
-                    ++yy;
-                }
-            }
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o);
+            if (lane >= o) incl += y;
         }
-    }
-    // 2. count, min, max and the exact sums of (v - c0), (v - c0)^2 about the
-    //    mesh's first pixel c0 (then re-centred on the minimum), one barrier
-    const uint32_t c0 = (uint32_t)((const gu16_t*)d.data)[(int64_t)y0 * d.pitch + x0];
-    uint32_t na = 0u, unused = 0u, mn = 0xffffffffu, mx = 0u;
-    uint64_t t1 = 0ull, t2 = 0ull;   // (v - c0) as two's complement, (v - c0)^2
+        if (lane == 63) sh.wc[wv] = incl;
+        __syncthreads();
+        uint32_t run = incl - tot;
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const uint32_t v = u[k];
-        if (v != kNone) {
-            const int64_t e = (int64_t)v - (int64_t)c0;
-            ++na;
-            t1 += (uint64_t)e;
-            t2 += (uint64_t)(e * e);
-            mn = min(mn, v);
-            mx = max(mx, v);
-        }
-    }
-    int par = 0;
-    block_u16<NT>(na, unused, t1, t2, mn, mx, par, sh);
-    if (mn == mx) {
-        if (tid == 0) {
-            d.back_raw[out_idx] = (double)mn;
-            d.rms_raw[out_idx] = 0.0;
-            d.iters[out_idx] = 0;
-        }
-        return;
-    }
-    {
-        // about the minimum: S1' = S1 + n (c0 - mn), S2' = S2 + 2 (c0 - mn) S1 + n (c0 - mn)^2
-        const int64_t sh0 = (int64_t)c0 - (int64_t)mn;
-        const int64_t s1 = (int64_t)t1;
-        t2 = (uint64_t)((int64_t)t2 + 2 * sh0 * s1 + (int64_t)na * sh0 * sh0);
-        t1 = (uint64_t)(s1 + (int64_t)na * sh0);
-    }
-    // exact statistics of the pixels in [lo, hi] from the registers (all
-    // wavefronts, one barrier): count, count below lo, sums of (v - mn)^p
-    auto reg_stats = [&](uint32_t lo, uint32_t hi, uint32_t& c, uint32_t& below, uint64_t& s1, uint64_t& s2) {
-        c = below = 0u;
-        s1 = s2 = 0ull;
-        uint32_t z0 = 0xffffffffu, z1 = 0u;
+        for (int i = 0; i < NW - 1; ++i) run += (i < wv) ? sh.wc[i] : 0u;
 #pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const uint32_t v = u[k];
-            const bool in = v != kNone && v >= lo && v <= hi;
-            const uint64_t dd = (uint64_t)(v - mn);
-            c += in ? 1u : 0u;
-            below += (v < lo) ? 1u : 0u;
-            s1 += in ? dd : 0ull;
-            s2 += in ? dd * dd : 0ull;
+        for (int q = 0; q < PER; ++q) {
+            const int i = tid * PER + q;
+            const uint32_t s1 = run + (c[q] & 0xffffu);
+            if (i < NB / 2) sh.start[i] = run | (s1 << 16);
+            run = s1 + (c[q] >> 16);
         }
-        block_u16<NT>(c, below, s1, s2, z0, z1, par, sh);
-    };
-    // 3. histogram window: 1-ADU bins over [wlo, wlo + NB) holding the
-    //    median, with prefix sums; cbw = pixels below it
-    int sft = 0;
-    while (((mx - mn) >> sft) >= (uint32_t)kU16Bins) ++sft;
-    for (int b = tid; b < kU16Bins; b += NT) sh.p0[b] = 0u;
+        if (tid == 0) sh.start[NB / 2] = (uint32_t)n;
+    }
     __syncthreads();
+    const uint16_t* start = reinterpret_cast<const uint16_t*>(sh.start);
 #pragma unroll
     for (int k = 0; k < PPT; ++k)
-        if (u[k] != kNone) atomicAdd(&sh.p0[(u[k] - mn) >> sft], 1u);
+        if (v[k] == v[k]) sh.val[start[pk[k] >> 16] + (pk[k] & 0xffffu)] = (T)v[k];
     __syncthreads();
-    u16_prefix<NT>(sh);
-    uint32_t wlo = mn, cbw = 0u;
-    if (sft > 0) {
-        // the coarse bin of the lower median; the window starts half a window
-        // below it, on a coarse-bin boundary
-        const int bm = u16_find(sh, (na - 1) / 2);
-        const int b0 = max(0, bm - ((kU16Bins / 2) >> sft));
-        cbw = sh.p0[b0];
-        wlo = mn + ((uint32_t)b0 << sft);
-        __syncthreads();
-        for (int b = tid; b < kU16Bins; b += NT) sh.p0[b] = 0u;
-        __syncthreads();
+    if (wv != 0) return;
+    __builtin_amdgcn_s_setprio(3);   // one wavefront's chain of latencies from here on
+    t1 = sh.w1[0];
+    th = sh.wh[0];
+    tl = sh.wl[0];
 #pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const uint32_t r = u[k] - wlo;   // (kNone and values below wlo wrap above NB)
-            if (u[k] != kNone && r < (uint32_t)kU16Bins) atomicAdd(&sh.p0[r], 1u);
-        }
-        __syncthreads();
-        u16_prefix<NT>(sh);
+    for (int i = 1; i < NW; ++i) {
+        t1 += sh.w1[i];
+        th += sh.wh[i];
+        tl += sh.wl[i];
     }
-    const uint32_t wtot = sh.p0[kU16Bins];
-    const uint32_t whi = wlo + (uint32_t)kU16Bins - 1u;   // last value inside the window
-    // From here every wavefront runs the clipping loop by itself on the same
-    // data (uniform results, no barrier), except for the rare intervals or
-    // ranks outside the window, which take block-wide register passes.
-    auto stats = [&](uint32_t lo, uint32_t hi, uint32_t& c, uint32_t& below, uint64_t& s1, uint64_t& s2) {
-        if (lo >= wlo && hi <= whi) {
-            const uint32_t a0 = lo - wlo, a1 = hi - wlo + 1;
-            c = sh.p0[a1] - sh.p0[a0];
-            const uint64_t q1 = (uint64_t)(sh.p1[a1] - sh.p1[a0]);
-            const uint64_t q2 = sh.p2[a1] - sh.p2[a0];
-            // sums of (v - mn) = (bin + off)
-            const uint64_t off = (uint64_t)(wlo - mn);
-            s1 = q1 + off * c;
-            s2 = q2 + 2ull * off * q1 + off * off * c;
-            below = cbw + sh.p0[a0];
-        } else {
-            reg_stats(lo, hi, c, below, s1, s2);
-        }
-    };
-    // value of global rank g (0-based over all the mesh's pixels) within [lo, hi]
-    auto value_at = [&](uint32_t g, uint32_t lo, uint32_t hi) -> uint32_t {
-        if (g >= cbw && g < cbw + wtot) return wlo + (uint32_t)u16_find(sh, g - cbw);
-        // outside the window: bisection on the smallest x with #(v <= x) > g
-        uint32_t zl = lo, zh = hi;
-        while (zl < zh) {
-            const uint32_t mid = zl + ((zh - zl) >> 1);
-            uint32_t c, bl;
-            uint64_t s1, s2;
-            reg_stats(0u, mid, c, bl, s1, s2);
-            if (c > g) zh = mid;
-            else zl = mid + 1;
-        }
-        return zl;
-    };
-    auto sigma_of = [&](uint32_t c, uint64_t s1, uint64_t s2) {
-        // n^2 var = n S2 - S1^2, exact in 64-bit integers (< 2^61)
-        const uint64_t num = (uint64_t)c * s2 - s1 * s1;
-        const double nd = (double)c;
-        return sqrt((double)num / (nd * nd));
-    };
-    const double sig0 = sigma_of(na, t1, t2);
-    double sig = sig0;
-    double mean = (double)mn + (double)t1 / (double)na;
-    uint32_t L = mn, H = mx, below = 0u;
-    auto median = [&]() {
-        const uint32_t r2 = na / 2, r1 = (na & 1) ? r2 : r2 - 1;
-        const uint32_t v1 = value_at(below + r1, L, H);
-        const uint32_t v2 = (r2 == r1) ? v1 : value_at(below + r2, L, H);
-        return 0.5 * ((double)v1 + (double)v2);
-    };
-    double med = median();
-    const double clip = (double)a.clip;
+    // 4. the clipping loop (one wavefront; every branch below is uniform)
+    const int half = lane >> 5, hl = lane & 31;
+    int ncur = n, rank0 = 0;              // surviving values, and how many lie below them
+    float L = -INFINITY, H = INFINITY;    // survivors: L <= v < H
+    int pL = 0, pH = n;                   // positions of the bins that hold them
+    constexpr int G = NB / 64;
+    const int top = start[lane * G];      // every G-th bin start
+    float med_h = 0.0f, med_l = 0.0f;     // median (an unevaluated pair: exact)
+    double mean = 0.0, sig = 0.0, sig0 = 0.0;
     int iters = 0;
-    for (int it = 0; it < a.max_iter; ++it) {
-        const double lim = clip * sig;
-        // the new interval: every integer v of [L, H] with |v - med| <= lim
-        // (the differences are exact; the bounds from FP64 are nudged to the
-        // exact decision)
-        double cl = ceil(med - lim), ch = floor(med + lim);
-        while (cl - 1.0 >= (double)L && med - (cl - 1.0) <= lim) cl -= 1.0;
-        while (cl <= (double)H && med - cl > lim) cl += 1.0;
-        while (ch + 1.0 <= (double)H && (ch + 1.0) - med <= lim) ch += 1.0;
-        while (ch >= (double)L && ch - med > lim) ch -= 1.0;
-        const uint32_t Ln = (uint32_t)fmax(cl, (double)L), Hn = (uint32_t)fmin(ch, (double)H);
-        uint32_t c = 0u, bl = 0u;
-        uint64_t s1 = 0ull, s2 = 0ull;
-        if (Ln <= Hn) stats(Ln, Hn, c, bl, s1, s2);
-        ++iters;
-        if (c == na || c == 0u) break;
+    for (;; ++iters) {
+        // mean and standard deviation
+        const double nd = (double)ncur;
+        if (kInt) {
+            // n^2 var = n S2 - S1^2 in 64-bit integers (< 2^61); the mean
+            // from the sum about the minimum
+            const int64_t i1 = (int64_t)t1;
+            const int64_t num = (int64_t)ncur * (int64_t)th - i1 * i1;
+            sig = sqrt((double)num / (nd * nd));
+            mean = (double)mn + (t1 + nd * (cs - (double)mn)) / nd;
+        } else {
+            const double q1 = t1 / nd;
+            const double vv = (th + tl) / nd - q1 * q1;
+            mean = cs + q1;
+            sig = sqrt(vv > 0.0 ? vv : 0.0);
+            if (!(vv > 1e-12 * (q1 * q1))) {
+                // a rounding residue or a real spread?
+                float lmn = INFINITY, lmx = -INFINITY;
+                for (int i = pL + lane; i < pH; i += 64) {
+                    const float x = (float)sh.val[i];
+                    if (x >= L && x < H) {
+                        lmn = fminf(lmn, x);
+                        lmx = fmaxf(lmx, x);
+                    }
+                }
+                if (wave_min(lmn) == wave_max(lmx)) sig = 0.0;
+            }
+        }
+        if (iters == 0) sig0 = sig;
+        // the median: the bin of its rank (bins start at rising positions),
+        // then the order statistic inside the bin
+        {
+            const int r2 = rank0 + ncur / 2, r1 = (ncur & 1) ? r2 : r2 - 1;
+            float o[2] = {0.0f, 0.0f};
+            int have = 0;
+#pragma unroll 1
+            while (have < 2) {
+                const int r = have ? r2 : r1;
+                const int g = __popcll(__ballot(top <= r)) - 1;
+                const int in = start[g * G + 1 + (G == 64 ? lane : min(lane, G - 1))];   // ends of its bins
+                const int k = __popcll(__ballot(lane < G && in <= r));
+                const int b = g * G + k;
+                const int e = __builtin_amdgcn_readlane(in, k);
+                const int s = __builtin_amdgcn_readlane(k > 0 ? in : top, k > 0 ? k - 1 : g);
+                const int m = e - s, j = r - s;
+                const bool both = r2 < e;   // the upper middle value lies here too
+                if (kInt && bscale == 1.0f && b > 0 && b < NB - NB / 4) {
+                    o[have] = blo + (float)b;   // a bin of one value
+                    if (both) o[1] = o[have];
+                } else if (m <= 64) {
+                    // the value with j smaller ones (or, among equals, fewer)
+                    const float x = (lane < m) ? (float)sh.val[s + lane] : INFINITY;
+                    int q = 0;
+                    for (int i = 0; i < m; i += 4) {   // (lanes past m hold +inf)
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) q += lane_f(x, i + u) < x ? 1 : 0;
+                    }
+                    auto at = [&](int jj) {
+                        uint64_t hit;
+                        while ((hit = __ballot(lane < m && q == jj)) == 0ull) --jj;
+                        return lane_f(x, __builtin_ctzll(hit));
+                    };
+                    o[have] = at(j);
+                    if (both) o[1] = (r2 == r) ? o[have] : at(j + 1);
+                } else {
+                    // a large bin: bisection on the order-preserving bits
+                    float lmn = INFINITY, lmx = -INFINITY;
+                    for (int i = s + lane; i < e; i += 64) {
+                        lmn = fminf(lmn, (float)sh.val[i]);
+                        lmx = fmaxf(lmx, (float)sh.val[i]);
+                    }
+                    const uint32_t z0 = f2ord(wave_min(lmn)), z1 = f2ord(wave_max(lmx));
+                    for (int t = 0; t < 2; ++t) {
+                        uint32_t a0 = z0, a1 = z1;
+                        while (a0 < a1) {
+                            const uint32_t mid = a0 + ((a1 - a0) >> 1);
+                            const float xm = ord2f(mid);
+                            int c = 0;
+                            for (int i = s + lane; i < e; i += 64) c += ((float)sh.val[i] <= xm) ? 1 : 0;
+                            if (wave_sum_i(c) > j + t) a1 = mid;
+                            else a0 = mid + 1;
+                        }
+                        if (t == 0) {
+                            o[have] = ord2f(a0);
+                            if (!both) break;
+                            o[1] = ord2f(a0);
+                            if (r2 == r) break;
+                        } else {
+                            o[1] = ord2f(a0);
+                        }
+                    }
+                }
+                have = both ? 2 : have + 1;
+            }
+            if (r1 == r2) {
+                med_h = o[0];
+                med_l = 0.0f;
+            } else {
+                float s, e;
+                two_sum(o[0], o[1], s, e);
+                med_h = 0.5f * s;
+                med_l = 0.5f * e;
+            }
+        }
+        if (iters >= a.max_iter) break;
+        // the new ends of the interval
+        float Ln, Hn;
+        if (kInt) {
+            // the integers with |v - med| <= lim (the differences are exact;
+            // the bounds from FP64 are nudged to the exact decision)
+            const double med = (double)med_h + (double)med_l, lim = (double)a.clip * sig;
+            double cl = fmax(ceil(med - lim), (double)mn), ch = fmin(floor(med + lim), (double)mx);
+            while (cl - 1.0 >= (double)mn && med - (cl - 1.0) <= lim) cl -= 1.0;
+            while (cl <= (double)mx && med - cl > lim) cl += 1.0;
+            while (ch + 1.0 <= (double)mx && (ch + 1.0) - med <= lim) ch += 1.0;
+            while (ch >= (double)mn && ch - med > lim) ch -= 1.0;
+            Ln = (float)cl;
+            Hn = (float)(ch + 1.0);
+        } else {
+            // a value is kept when |(v - med_h) - med_l| <= thr in FP32; the
+            // difference rises with v, so the first value kept and the first
+            // dropped above are found among 32 neighbours of med -+ thr (one
+            // end per half of the wavefront), else by bisection
+            const float thr = (float)((double)a.clip * sig);
+            auto on = [&](float x) {
+                const float dx = (x - med_h) - med_l;
+                return half ? dx > thr : dx >= -thr;
+            };
+            const double md = (double)med_h + (double)med_l;
+            const float g = (float)(half ? md + (double)thr : md - (double)thr);
+            const uint32_t k0 = f2ord(g) - 16u;
+            const uint64_t bm = __ballot(fabsf(g) < 1e38f && on(ord2f(k0 + (uint32_t)hl)));
+            const int pc0 = __popcll(bm & 0xffffffffull), pc1 = __popcll(bm >> 32);
+            float t;
+            if (pc0 > 0 && pc0 < 32 && pc1 > 0 && pc1 < 32) {
+                t = ord2f(k0 + 32u - (uint32_t)(half ? pc1 : pc0));
+            } else {
+                uint32_t z0 = f2ord(-3.402823466e38f), z1 = f2ord(INFINITY);
+                for (int s = 0; s < 32; ++s) {
+                    const uint32_t mid = z0 + ((z1 - z0) >> 1);
+                    const bool yes = z0 < z1 && on(ord2f(mid));
+                    if (yes) z1 = mid;
+                    else if (z0 < z1) z0 = mid + 1;
+                }
+                t = ord2f(z0);
+            }
+            Ln = lane_f(t, 0);
+            Hn = lane_f(t, 32);
+        }
+        Ln = fmaxf(L, Ln);
+        Hn = fminf(H, Hn);
+        if (!(Ln < Hn)) {   // nothing left
+            ++iters;
+            break;
+        }
+        // what leaves, [L, Ln) and [Hn, H): the positions of the bins from
+        // one end of each range to the other, taken as one run
+        const int bL = mesh_bin<NB>(Ln, blo, bscale), bH = mesh_bin<NB>(Hn, blo, bscale);
+        const int sL = start[bL], sH = start[bH], eH = start[bH + 1];
+        const int nl = (int)start[bL + 1] - pL, run = nl + pH - sH;
+        double s1 = 0.0, sq = 0.0, sl = 0.0;
+        int low = 0, gone = 0;
+        constexpr int U = 4;   // values per lane in flight
+        for (int i0 = 0; i0 < run; i0 += 64 * U) {
+            float x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (u > 0 && i0 + 64 * u >= run) break;
+                const int i = min(i0 + 64 * u + lane, run - 1);
+                x[u] = (float)sh.val[i < nl ? pL + i : sH + (i - nl)];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (u > 0 && i0 + 64 * u >= run) break;
+                const int i = i0 + 64 * u + lane;
+                const bool lo = i < nl && x[u] >= L && x[u] < Ln;
+                const bool hi = i >= nl && i < run && x[u] >= Hn && x[u] < H;
+                const uint64_t bl = __ballot(lo), bh = __ballot(hi);
+                if ((bl | bh) == 0ull) continue;
+                low += __popcll(bl);
+                gone += __popcll(bl | bh);
+                if (lo || hi) accum(x[u], s1, sq, sl);
+            }
+        }
+        if (gone == 0 || gone == ncur) {
+            ++iters;
+            break;
+        }
+        t1 -= wave_total(s1);
+        th -= wave_total(sq);
+        if (!kInt) tl -= wave_total(sl);
+        ncur -= gone;
+        rank0 += low;
         L = Ln;
         H = Hn;
-        na = c;
-        below = bl;
-        sig = (L == H) ? 0.0 : sigma_of(c, s1, s2);
-        mean = (double)mn + (double)s1 / (double)c;
-        med = median();
+        pL = sL;
+        pH = eH;
     }
-    if (tid == 0) {
+    if (lane == 0) {
+        const double med = (double)med_h + (double)med_l;
         const double dsig = fabs(sig - sig0);
         const double back = (dsig < (double)a.crowd * sig0) ? mean
                                                              : ((double)a.mode_a * med - (double)a.mode_b * mean);
@@ -1712,47 +1188,43 @@ __global__ __launch_bounds__(kSplThreads) void k_spline_x(const FrameDesc* __res
 
 // ---------------------------------------------------------------------------
 // launchers
-// cfg: 0 = automatic, 1 = 256 x 16, 2 = 512 x 16, 3 = 512 x 32, 4 = 1024 x 16
-// (threads x pixels per thread; the product must cover the largest mesh)
-template <int NT, int PPT>
+// cfg: 0 = automatic, 1 = 256 x 16, 2 = 512 x 16, 3 = 512 x 32, 4 = 1024 x 16,
+// 5 = 64 x 16 (threads x pixels per thread; the product must cover the
+// largest mesh).  The automatic choice is the smallest that covers it: 32 x 32
+// meshes in 256-thread workgroups leave three wavefronts of four idle (4.3 MP
+// of them: 216 us in the 256 x 16 shape of the register passes, 34 us in 64 x
+// 16).
+template <typename T, int NT, int PPT>
 static void launch_mesh_nt(FrameDesc* desc, const FrameDesc* one, int nframes, int total_meshes, BkgArgs a,
                            hipStream_t s) {
-    if (one) k_mesh_stats<NT, PPT, true><<<total_meshes, NT, 0, s>>>(desc, *one, nframes, a);
-    else k_mesh_stats<NT, PPT, false><<<total_meshes, NT, 0, s>>>(desc, FrameDesc{}, nframes, a);
+    if (one) k_mesh_stats<T, NT, PPT, true><<<total_meshes, NT, 0, s>>>(desc, *one, nframes, a);
+    else k_mesh_stats<T, NT, PPT, false><<<total_meshes, NT, 0, s>>>(desc, FrameDesc{}, nframes, a);
 }
 
-template <int NT, int PPT>
-static void launch_mesh_u16_nt(FrameDesc* desc, const FrameDesc* one, int nframes, int total_meshes, BkgArgs a,
-                               hipStream_t s) {
-    if (one) k_mesh_stats_u16<NT, PPT, true><<<total_meshes, NT, 0, s>>>(desc, *one, nframes, a);
-    else k_mesh_stats_u16<NT, PPT, false><<<total_meshes, NT, 0, s>>>(desc, FrameDesc{}, nframes, a);
+template <typename T>
+static void launch_mesh_t(FrameDesc* desc, const FrameDesc* one, int nframes, int total_meshes, int max_area,
+                          BkgArgs a, int cfg, hipStream_t s) {
+    const bool fits = cfg == 1 ? max_area <= 4096 : cfg == 2 ? max_area <= 8192 : cfg == 5 ? max_area <= 1024 : true;
+    if (cfg == 0 || !fits) cfg = max_area <= 1024 ? 5 : max_area <= 4096 ? 1 : max_area <= 8192 ? 2 : 3;
+    switch (cfg) {
+        case 1: launch_mesh_nt<T, 256, 16>(desc, one, nframes, total_meshes, a, s); break;
+        case 2: launch_mesh_nt<T, 512, 16>(desc, one, nframes, total_meshes, a, s); break;
+        case 4: launch_mesh_nt<T, 1024, 16>(desc, one, nframes, total_meshes, a, s); break;
+        case 5: launch_mesh_nt<T, 64, 16>(desc, one, nframes, total_meshes, a, s); break;
+        default: launch_mesh_nt<T, 512, 32>(desc, one, nframes, total_meshes, a, s); break;
+    }
 }
 
-// uint16 meshes; cfg as for the float kernel (threads x pixels per thread)
+// uint16 meshes
 void launch_mesh_stats_u16(FrameDesc* desc, const FrameDesc* one, int nframes, int total_meshes, int max_area,
                            BkgArgs a, int cfg, hipStream_t s) {
-    if (cfg == 0) cfg = (max_area <= 4096) ? 1 : (max_area <= 8192) ? 2 : 3;
-    if (cfg == 1 && max_area > 4096) cfg = 3;
-    if (cfg == 2 && max_area > 8192) cfg = 3;
-    switch (cfg) {
-        case 1: launch_mesh_u16_nt<256, 16>(desc, one, nframes, total_meshes, a, s); break;
-        case 2: launch_mesh_u16_nt<512, 16>(desc, one, nframes, total_meshes, a, s); break;
-        case 4: launch_mesh_u16_nt<1024, 16>(desc, one, nframes, total_meshes, a, s); break;
-        default: launch_mesh_u16_nt<512, 32>(desc, one, nframes, total_meshes, a, s); break;
-    }
+    launch_mesh_t<uint16_t>(desc, one, nframes, total_meshes, max_area, a, cfg, s);
 }
 
+// float32 meshes
 void launch_mesh_stats(FrameDesc* desc, const FrameDesc* one, int nframes, int total_meshes, int max_area, BkgArgs a,
                        int cfg, hipStream_t s) {
-    if (cfg == 0) cfg = (max_area <= 4096) ? 1 : (max_area <= 8192) ? 2 : 3;
-    if (cfg == 1 && max_area > 4096) cfg = 3;
-    if (cfg == 2 && max_area > 8192) cfg = 3;
-    switch (cfg) {
-        case 1: launch_mesh_nt<256, 16>(desc, one, nframes, total_meshes, a, s); break;
-        case 2: launch_mesh_nt<512, 16>(desc, one, nframes, total_meshes, a, s); break;
-        case 4: launch_mesh_nt<1024, 16>(desc, one, nframes, total_meshes, a, s); break;
-        default: launch_mesh_nt<512, 32>(desc, one, nframes, total_meshes, a, s); break;
-    }
+    launch_mesh_t<float>(desc, one, nframes, total_meshes, max_area, a, cfg, s);
 }
 
 void launch_grid_filter(const FrameDesc* desc, int nframes, int total_meshes, int fsize, hipStream_t s) {

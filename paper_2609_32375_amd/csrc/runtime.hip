@@ -644,11 +644,11 @@ extern "C" gp_status gp_background(gp_ctx* ctx, const gp_frame* frames, int32_t 
     if (!(bp->flags & GP_BKG_GRID_GIVEN)) {
         bool any_u16 = false, any_f32 = false;
         for (int f = 0; f < nframes; ++f) (frames[f].dtype == GP_U16 ? any_u16 : any_f32) = true;
-        BkgArgs a{bp->clip_sigma, bp->crowd_tol, bp->mode_a, bp->mode_b, bp->max_iter, bp->filter_size,
-                  any_u16 ? 1 : 0};
+        BkgArgs a{bp->clip_sigma, bp->crowd_tol, bp->mode_a, bp->mode_b, bp->max_iter, bp->filter_size};
         {
             ProfScope ps(ctx, s, "mesh_stats");
             std::vector<int> cands;
+            if (P.max_area <= 1024) cands.push_back(5);
             if (P.max_area <= 4096) cands.push_back(1);
             if (P.max_area <= 8192) cands.push_back(2);
             cands.push_back(3);

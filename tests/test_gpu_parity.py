@@ -109,6 +109,53 @@ def test_mesh_statistics_structured(P, m):
     ph.close()
 
 
+def _bin_meshes(mw, mh, dt, seed):
+    """Eight meshes of mw x mh pixels whose values stress the grouping of a
+    mesh by bins: a sky of few integer levels (bins of many equal values),
+    values about zero, a tail of far negative values, half the mesh in a
+    bright source, one different pixel, values over ten decades, and two sky
+    levels so far apart that each falls into one bin, the last with ties."""
+    rng = np.random.default_rng(seed)
+    n = mw * mh
+    lev = 200.0 + np.rint(0.6 * rng.standard_normal(n))
+    zero = 10.0 * rng.standard_normal(n)
+    low = 900.0 + 20.0 * rng.standard_normal(n)
+    low[: n // 20] -= 800.0 * rng.random(n // 20)
+    half = 500.0 + 8.0 * rng.standard_normal(n)
+    half[n // 2:] += 30000.0 * rng.random(n - n // 2)
+    one = np.full(n, 777.0)
+    one[n // 3] = 40000.0
+    dec = 10.0 ** rng.uniform(-2.0, 4.7, n)
+    far = np.where(rng.random(n) < 0.6, 100.0, 60000.0) + 2.0 * rng.standard_normal(n)
+    ties = np.where(rng.random(n) < 0.5, 50.0, 51.0)
+    ties[:2] = 9000.0
+    blocks = [rng.permutation(b).reshape(mh, mw) for b in (lev, zero, low, half, one, dec, far, ties)]
+    img = np.block([blocks[:4], blocks[4:]])
+    if dt == "u16":
+        return np.clip(np.rint(img), 0, 65535).astype(np.uint16)
+    return img.astype(np.float32)
+
+
+@pytest.mark.parametrize("dt", ["f32", "u16"])
+@pytest.mark.parametrize("mw,mh", [(16, 16), (31, 33), (32, 32), (41, 25), (64, 64), (91, 90), (127, 129)])
+def test_mesh_statistics_at_the_edges_of_the_launch_shapes(P, mw, mh, dt):
+    """Both sides of each launch shape's largest mesh (1024, 4096, 8192 and
+    16384 pixels), with the meshes' last row and column cut short."""
+    _say("mesh bins", mw, mh, dt)
+    img = _bin_meshes(mw, mh, dt, mw * mh)
+    img = np.ascontiguousarray(img[: 2 * mh - 3, : 4 * mw - 5])
+    p = _params("c1", mesh_w=mw, mesh_h=mh, mesh_filter=1)
+    ph = P.Photometry([_dev(img)], p, p.kernel(), capacity=64)
+    ph.background()
+    g = ph.grids(0)
+    check_meshes(img, g, p)
+    ph.background()   # the places inside a bin vary from run to run, the results do not
+    h = ph.grids(0)
+    for k in ("back_raw", "rms_raw", "iters"):
+        np.testing.assert_array_equal(g[k], h[k])
+    ph.close()
+
+
 def _structured_meshes_u16(m, seed):
     """uint16 meshes (4 x 3 of m x m) for the integer statistics kernel: the
     float structured set rounded and clipped (ties, a bright source over a
