@@ -76,19 +76,6 @@ __device__ __forceinline__ int mesh_bin(float x, float lo, float scale) {
 }
 
 // sum over the wavefront's lanes (of values whose sums are exact: any order)
-__device__ __forceinline__ double lane_d(double v, int l) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
-    return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double v) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
-}
 __device__ __forceinline__ double wave_total(double v) {
     v += dpp_d<0xB1>(v);    // lane ^ 1
     v += dpp_d<0x4E>(v);    // lane ^ 2
@@ -96,10 +83,6 @@ __device__ __forceinline__ double wave_total(double v) {
     v += dpp_d<0x140>(v);   // 15 - lane of each 16
     return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
 }
-__device__ __forceinline__ float lane_f(float v, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-
 // One workgroup per mesh.  Whatever was clipped before, the surviving values
 // are always those of one interval [L, H).  The workgroup groups the values by
 // bin in LDS once (a histogram whose returned counts are the places inside a
@@ -122,8 +105,8 @@ __device__ __forceinline__ float lane_f(float v, int l) {
 // What hides it is meshes per CU: 7 of 64^2, two of 128^2 (74 KB of LDS).
 // A pass over all pixels in registers per iteration, with a sorted window for
 // the median (float) or prefix sums of a histogram (uint16), took: 12300^2
-// crowded float in 128^2 meshes 2222 us, now 1175; 6144^2 260, now 135;
-// 2048^2 in 64^2 meshes 40, now 22; 371 MP of uint16 1122, now 695.
+// crowded float in 128^2 meshes 2222 us, now 985; 6144^2 260, now 135;
+// 2048^2 in 64^2 meshes 40, now 22; 371 MP of uint16 1122, now 680.
 //
 // ONE: a one-frame call, whose descriptor comes with the launch (d1);
 // workgroup 0 stores it in the table for the launches that follow
@@ -406,31 +389,52 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
                     o[have] = at(j);
                     if (both) o[1] = (r2 == r) ? o[have] : at(j + 1);
                 } else {
-                    // a large bin: bisection on the order-preserving bits
-                    float lmn = INFINITY, lmx = -INFINITY;
-                    for (int i = s + lane; i < e; i += 64) {
-                        lmn = fminf(lmn, (float)sh.val[i]);
-                        lmx = fmaxf(lmx, (float)sh.val[i]);
+                    // a large bin: the smallest value with more than j at or
+                    // below it, by bisection (of the integers, or of the
+                    // order-preserving bits), and the next one up
+                    float y[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) y[u] = (lane + 64 * u < m) ? (float)sh.val[s + lane + 64 * u] : INFINITY;
+                    auto upto = [&](float x) {
+                        int c = 0;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) c += __popcll(__ballot(y[u] <= x));
+                        for (int i = s + 256; i < e; i += 64)
+                            c += __popcll(__ballot(i + lane < e && (float)sh.val[min(i + lane, e - 1)] <= x));
+                        return c;
+                    };
+                    auto value = [&](uint32_t z) { return kInt ? (float)z : ord2f(z); };
+                    float y0 = mn, y1 = mx;
+                    if (m > 256) {
+                        // (often one value many times: saturated pixels)
+                        y0 = INFINITY;
+                        y1 = -INFINITY;
+                        for (int i = s + lane; i < e; i += 64) {
+                            y0 = fminf(y0, (float)sh.val[i]);
+                            y1 = fmaxf(y1, (float)sh.val[i]);
+                        }
+                        y0 = wave_min(y0);
+                        y1 = wave_max(y1);
                     }
-                    const uint32_t z0 = f2ord(wave_min(lmn)), z1 = f2ord(wave_max(lmx));
-                    for (int t = 0; t < 2; ++t) {
-                        uint32_t a0 = z0, a1 = z1;
-                        while (a0 < a1) {
-                            const uint32_t mid = a0 + ((a1 - a0) >> 1);
-                            const float xm = ord2f(mid);
-                            int c = 0;
-                            for (int i = s + lane; i < e; i += 64) c += ((float)sh.val[i] <= xm) ? 1 : 0;
-                            if (wave_sum_i(c) > j + t) a1 = mid;
-                            else a0 = mid + 1;
+                    uint32_t a0 = kInt ? (uint32_t)y0 : f2ord(y0), a1 = kInt ? (uint32_t)y1 : f2ord(y1);
+                    while (a0 < a1) {
+                        const uint32_t mid = a0 + ((a1 - a0) >> 1);
+                        if (upto(value(mid)) > j) a1 = mid;
+                        else a0 = mid + 1;
+                    }
+                    const float x1 = value(a0);
+                    o[have] = x1;
+                    if (both) {
+                        float x2 = x1;
+                        if (r2 != r && upto(x1) == j + 1) {
+                            x2 = INFINITY;
+                            for (int i = s + lane; i < e; i += 64) {
+                                const float x = (float)sh.val[i];
+                                x2 = x > x1 ? fminf(x2, x) : x2;
+                            }
+                            x2 = wave_min(x2);
                         }
-                        if (t == 0) {
-                            o[have] = ord2f(a0);
-                            if (!both) break;
-                            o[1] = ord2f(a0);
-                            if (r2 == r) break;
-                        } else {
-                            o[1] = ord2f(a0);
-                        }
+                        o[1] = x2;
                     }
                 }
                 have = both ? 2 : have + 1;
