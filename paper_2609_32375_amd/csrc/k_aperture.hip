@@ -1,14 +1,15 @@
 // k_aperture.hip -- circular aperture photometry with exact pixel/disk overlap.
 //
 // One wavefront per catalogued object.  The rows of the object's box are taken
-// in bands of 16: the band's background and noise-map cubics are built in LDS
-// (FP64 -> working precision), the pixels the outer circle can touch are
-// numbered run by run and spread over the lanes, and each lane forms M = I - B
-// for its pixels and classifies them against every circle (the aperture radii,
-// r_in and r_out).  Pixels wholly inside or outside a circle take weight 1 or
-// 0; the rest get the exact area of the circle inside the pixel from a
-// cancellation-free formula: clipped rectangle + trapezoid under the chord +
-// circular segment (theta - sin theta by series for small angles).
+// in bands whose background and noise-map cubics fit a fixed share of LDS (FP64
+// -> working precision; one band for the usual radii), the pixels the outer
+// circle can touch are numbered run by run and spread over the lanes, and each
+// lane forms M = I - B for its pixels and classifies them against every circle
+// (the aperture radii, r_in and r_out).  Pixels wholly inside or outside a
+// circle take weight 1 or 0; the rest get the exact area of the circle inside
+// the pixel from a cancellation-free formula: clipped rectangle + trapezoid
+// under the chord + circular segment (theta - sin theta by series for small
+// angles).
 //
 // The paper measures fluxes in circular apertures of several radii with the
 // variance propagated through the same weights and float64 accumulation; the
@@ -19,28 +20,39 @@
 
 namespace gpk {
 
-constexpr int kApBand = 17;    // rows per band (two bands cover the 34-row box of r_max <= 15)
 constexpr int kApBox = 2 * 66; // widest box (r <= 64)
 constexpr int kApWaves = 4;
+constexpr int kApCubics = 80;  // row cubics (rows x spline pieces) of a band
+constexpr int kApList = 256;   // queued (pixel, circle) cuts per wavefront
+// wavefronts per SIMD the registers are held to (FP32): more circles keep more
+// sums, and would spill at four
+constexpr int ap_occ(int nc) { return nc <= 5 ? 4 : nc <= 7 ? 3 : 2; }
+static_assert(kApCubics <= 2 * 64, "two row cubics per lane");
 
-constexpr int kApList = 128;   // queued (pixel, circle) cuts per wavefront
-constexpr int kApUnroll = 2;   // pixels per lane in flight
-constexpr int kApMaxFrames = kMaxFramesPerCall;   // object-count prefix over the frames, in LDS
-constexpr int kApPrefixBytes = (int)((sizeof(int32_t) * (kApMaxFrames + 1) + 15) / 16 * 16);
-
+// a queued cut: M, the pixel variance, and box column | box row << 8 | circle << 16
 template <typename Real>
 struct ApEntry {
-    Real dx, dy, m, var;
-    int32_t j;
+    Real m, var;
+    uint32_t code;
 };
 
-// Per-wavefront LDS layout (dynamic shared memory; the host sizes it from the
-// number of spline pieces a box can touch).  Bin sums are per lane, bin-major,
-// so a lane's read-modify-write of its bin never conflicts with another lane.
+// Per-wavefront LDS layout (dynamic shared memory; the host sizes it).
+//   col   local spline coordinate and piece of each box column
+//   row   of each row of the band: element offset and column of its first
+//         pixel, less the pixel's number in the band
+//   mark  one bit per pixel number: a row starts at the next number
+template <typename Real>
+struct ApCol {
+    Real sx;
+    int32_t piece;
+};
+struct ApRow {
+    int32_t off, x0;
+};
 template <typename Real, int NC>
 struct ApLayout {
-    int o_s, o_a, o_v, o_colp, o_cols, o_rxl, o_roff, o_tab, o_list, o_rad, bytes;
-    __host__ __device__ ApLayout(int band, int nixmax) {
+    int o_col, o_row, o_mark, o_tab, o_list, o_rad, marks, bytes;
+    __host__ __device__ ApLayout(int side) {
         int o = 0;
         auto take = [&](int n, int al) {
             o = (o + al - 1) / al * al;
@@ -48,71 +60,114 @@ struct ApLayout {
             o += n;
             return r;
         };
-        o_s = take(NC * 64 * 8, 16);
-        o_a = take(NC * 64 * 8, 16);
-        o_v = take(NC * 64 * 8, 16);
-        o_colp = take(kApBox * 4, 16);
-        o_cols = take(kApBox * (int)sizeof(Real), 16);
-        o_rxl = take(band * 4, 16);
-        o_roff = take((band + 1) * 4, 16);
-        o_tab = take(band * nixmax * (int)sizeof(RowT<Real>), 16);
+        marks = 2 * (min(64, side) * side / 64 + 2);   // 32-bit words
+        o_col = take(side * (int)sizeof(ApCol<Real>), 16);
+        o_row = take(min(64, side) * (int)sizeof(ApRow), 16);
+        o_mark = take(marks * 4, 16);
+        o_tab = take(kApCubics * (int)sizeof(RowT<Real>), 16);
         o_list = take(kApList * (int)sizeof(ApEntry<Real>), 16);
         o_rad = take(NC * (int)sizeof(Real), 16);
         bytes = (o + 15) / 16 * 16;
+    }
+};
+// object-count prefix over the frames (whole workgroup), before the wavefronts' parts
+__host__ __device__ __forceinline__ int ap_prefix_bytes(int nframes) { return (4 * (nframes + 1) + 15) / 16 * 16; }
+
+// Sums of N (16 or 32) values over the wavefront's lanes, in a fixed order.
+// The halves of the wavefront exchange halves of the list, then the 16-lane
+// rows quarters of it, so that only N / 4 values are left for the four steps
+// inside a row.  total(i) is value i's sum.
+template <int N>
+struct WaveTotals {
+    double v[N / 4];
+    __device__ __forceinline__ static double swap_add32(double a, double b) {
+        const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+        const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+        return __longlong_as_double((long long)((uint64_t)l[0] | ((uint64_t)h[0] << 32))) +
+               __longlong_as_double((long long)((uint64_t)l[1] | ((uint64_t)h[1] << 32)));
+    }
+    __device__ __forceinline__ static double swap_add16(double a, double b) {
+        const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+        const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+        return __longlong_as_double((long long)((uint64_t)l[0] | ((uint64_t)h[0] << 32))) +
+               __longlong_as_double((long long)((uint64_t)l[1] | ((uint64_t)h[1] << 32)));
+    }
+    __device__ __forceinline__ explicit WaveTotals(const double (&x)[N]) {
+        double h[N / 2];
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) h[i] = swap_add32(x[i], x[i + N / 2]);   // lanes 32..: value i + N / 2
+#pragma unroll
+        for (int i = 0; i < N / 4; ++i) {
+            double t = swap_add16(h[i], h[i + N / 4]);   // odd rows: value i + N / 4 of the half
+            t += dpp_d<0xB1>(t);
+            t += dpp_d<0x4E>(t);
+            t += dpp_d<0x141>(t);
+            t += dpp_d<0x140>(t);
+            v[i] = t;
+        }
+    }
+    __device__ __forceinline__ double total(int i) const {
+        return lane_d(v[i % (N / 4)], 16 * (((i / (N / 4)) & 1) | (i / (N / 2)) << 1));
     }
 };
 
 // Circles: the aperture radii, r_in and r_out, sorted by radius on the host
 // (a.crad / a.crole).  Circles are nested, so a pixel lies wholly inside every
 // circle from some index kin on, wholly outside those before kout, and only
-// the circles in [kout, kin) cut it (usually none or one).  A wholly-inside
-// pixel adds (M, 1, var) to bin kin; the circle sums are prefix sums over the
-// bins.  A cut pixel is queued and, in a compacted lane-parallel pass, adds
-// its exact weight w as (w M, w, w^2 var) to bin j and subtracts it from bin
-// j + 1, so that only circle j sees it.
+// the circles in [kout, kin) cut it (usually none or one).  A pixel adds
+// (M, 1, var) to the sums of every circle that holds it.  A cut pixel is
+// queued and, in a compacted lane-parallel pass, adds its exact weight w as
+// (w M, w, w^2 var) to its circle.
 //
 // Only the pixels the outer circle can touch are visited: each row of the box
 // contributes the run of columns within half a pixel plus the chord of the
-// outer circle, and the runs of a band of rows are numbered consecutively and
-// spread over the lanes.  Sums are kept per lane (FP64: flux, area, variance) and
-// reduced in a fixed order, so an object's result does not depend on what else
-// runs.
+// outer circle; the runs of a band are numbered consecutively and spread over
+// the lanes, and a pixel's row is the number of row starts marked below it.
+// Sums are kept per lane in registers (FP64: flux, area, variance) and
+// reduced in a fixed order, so an object's result does not depend on what
+// else runs.
+//
+// Bound by VALU issue and the latency between an object's LDS tables, its
+// pixels and its queue, at four wavefronts per SIMD (9 KB of LDS each).
+// Keeping the sums of every lane in LDS bins, finding a pixel's row by 17
+// compares, two bands per box, pieces of straddling pixels one after another
+// and the object's descriptor in vector registers took: 106,344 objects of
+// 371 MP uint16 (r_out 15, two apertures) 1605 us, now 912; 60,243 of a
+// crowded 12300^2 frame (r_out 18, three) 1255, now 684; 13,233 of 6144^2 289,
+// now 153; FP64, 1092 objects, 73, now 33.
 // ONE: a one-frame call, whose descriptor comes with the launch (d1) instead
 // of from the workspace table
 template <typename Real, int NC, bool ONE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(Real) == 4 ? 3 : 1))) void k_aperture(const FrameDesc* __restrict__ desc, FrameDesc d1, ApArgs a, ApCat cat,
-                                                  int band, int nixmax) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(Real) == 4 ? ap_occ(NC) : 1))) void
+k_aperture(const FrameDesc* __restrict__ desc, FrameDesc d1, ApArgs a, ApCat cat, int nixmax) {
     extern __shared__ __align__(16) unsigned char ap_dyn[];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const ApLayout<Real, NC> L(band, nixmax);
-    int32_t* fpre = reinterpret_cast<int32_t*>(ap_dyn);     // kApPrefixBytes
-    unsigned char* base = ap_dyn + kApPrefixBytes + (size_t)wv * L.bytes;
-    double* binS = (double*)(base + L.o_s);
-    double* binA = (double*)(base + L.o_a);
-    double* binV = (double*)(base + L.o_v);
-    int32_t* colp = (int32_t*)(base + L.o_colp);
-    Real* cols = (Real*)(base + L.o_cols);
-    int32_t* rxl = (int32_t*)(base + L.o_rxl);
-    int32_t* roff = (int32_t*)(base + L.o_roff);
+    // (the wavefront's number, and with it everything about its object, in scalar registers)
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int R = (int)ceilf(a.rmax) + 1;
+    const int side = 2 * R + 2;
+    const ApLayout<Real, NC> L(side);
+    int32_t* fpre = reinterpret_cast<int32_t*>(ap_dyn);
+    unsigned char* base = ap_dyn + ap_prefix_bytes(a.nframes) + (size_t)wv * L.bytes;
+    ApCol<Real>* cols = (ApCol<Real>*)(base + L.o_col);
+    ApRow* rows = (ApRow*)(base + L.o_row);
+    uint32_t* mark = (uint32_t*)(base + L.o_mark);
     RowT<Real>* tab = (RowT<Real>*)(base + L.o_tab);
     ApEntry<Real>* list = (ApEntry<Real>*)(base + L.o_list);
     Real* rad = (Real*)(base + L.o_rad);
     const uint64_t below = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
 
-    Real cr[NC], cr2[NC];
+    Real cr2[NC];
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
-        cr[j] = (Real)a.crad[j];
-        cr2[j] = cr[j] * cr[j];
-    }
-    const Real rmax = cr[NC - 1], rmax2 = cr2[NC - 1];
-    const int R = (int)ceilf(a.rmax) + 1;
-    const int side = 2 * R + 2;
+    for (int j = 0; j < NC; ++j) cr2[j] = (Real)a.crad[j] * (Real)a.crad[j];
+    const Real rmax = (Real)a.crad[NC - 1], rmax2 = cr2[NC - 1];
     const Real inv_gain = (a.gain > 0.f) ? (Real)1 / (Real)a.gain : (Real)0;
     // radius by circle index for the cut-pixel pass (a lane-varying index)
 #pragma unroll
     for (int j = 0; j < NC; ++j)
-        if (lane == j) rad[j] = cr[j];
+        if (lane == j) rad[j] = (Real)a.crad[j];
 
     // The catalogued objects of all frames, numbered consecutively (frame by
     // frame, rows < n_obj only), are split into 8 contiguous ranges, one per
@@ -120,28 +175,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(Real
     const int nf = a.nframes;
     if (wv == 0) {
         // prefix of min(n_obj, capacity) over the frames (one wavefront)
-        constexpr int PER = kApMaxFrames / 64;
-        int t = 0;
-        for (int q = 0; q < PER; ++q) {
-            const int fr = lane * PER + q;
-            if (fr < nf) t += min(cat.n_obj[fr], a.capacity);
-        }
-        int incl = t;
+        int run = 0;
+        for (int f0 = 0; f0 < nf; f0 += 64) {
+            const int fr = f0 + lane;
+            const int c = fr < nf ? min(cat.n_obj[fr], a.capacity) : 0;
+            int incl = c;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(incl, o);
-            if (lane >= o) incl += y;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(incl, o);
+                if (lane >= o) incl += y;
+            }
+            if (fr < nf) fpre[fr] = run + incl - c;
+            run += __shfl(incl, 63);
         }
-        int run = incl - t;
-        for (int q = 0; q < PER; ++q) {
-            const int fr = lane * PER + q;
-            fpre[fr] = run;
-            if (fr < nf) run += min(cat.n_obj[fr], a.capacity);
-        }
-        if (lane == 63) fpre[kApMaxFrames] = incl;
+        if (lane == 0) fpre[nf] = run;
     }
     __syncthreads();
-    const int total = fpre[kApMaxFrames];
+    const int total = __builtin_amdgcn_readfirstlane(fpre[nf]);
     const int chunk = (total + kXcds - 1) / kXcds;
     const int xcd = blockIdx.x % kXcds, per_xcd = gridDim.x / kXcds;
     const int o_end = min(total, (xcd + 1) * chunk);
@@ -150,73 +200,90 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(Real
         int lo = 0, hi = nf - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (fpre[mid] <= o) lo = mid;
+            if (__builtin_amdgcn_readfirstlane(fpre[mid]) <= o) lo = mid;
             else hi = mid - 1;
         }
-        const int f = lo, k = o - fpre[f];
+        const int f = lo, k = o - __builtin_amdgcn_readfirstlane(fpre[f]);
         const int row = f * a.capacity + k;
         const FrameDesc& d = ONE ? d1 : desc[f];
-        const double xc = cat.x[row], yc = cat.y[row];
+        const double xc = lane_d(cat.x[row], 0), yc = lane_d(cat.y[row], 0);
         const int cxi = (int)floor(xc), cyi = (int)floor(yc);
         const Real fx = (Real)(xc - (double)cxi), fy = (Real)(yc - (double)cyi);
         const int bx0 = cxi - R, by0 = cyi - R;
         const int cx_lo = max(bx0, 0), cx_hi = min(bx0 + side - 1, d.W - 1);
         const int ixlo = (cx_lo <= cx_hi) ? piece_of(cx_lo, d.W, d.mw) : 0;
-        const int nix = (cx_lo <= cx_hi) ? min(piece_of(cx_hi, d.W, d.mw) - ixlo + 1, nixmax) : 0;
+        const int nix = (cx_lo <= cx_hi) ? min(piece_of(cx_hi, d.W, d.mw) - ixlo + 1, nixmax) : 1;
         wave_sync();
         for (int c = lane; c < side; c += 64) {
             const int px = bx0 + c;
             if (px >= 0 && px < d.W) {
                 const int ix = piece_of(px, d.W, d.mw);
-                colp[c] = min(ix - ixlo, nixmax - 1);
-                cols[c] = (Real)((double)px - piece_ref(ix, d.W, d.mw));
+                cols[c] = ApCol<Real>{(Real)((double)px - piece_ref(ix, d.W, d.mw)), min(ix - ixlo, nixmax - 1)};
             }
         }
+        double S[NC], V[NC], A[NC];   // sums of the pixels a circle holds or cuts
+        int notin[NC], used = 0;      // visited pixels a circle does not hold, visited pixels
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
-            binS[j * 64 + lane] = 0.0;
-            binA[j * 64 + lane] = 0.0;
-            binV[j * 64 + lane] = 0.0;
+            S[j] = V[j] = A[j] = 0.0;
+            notin[j] = 0;
         }
         // queued cuts: pixels within one quadrant from the bottom of the list
         // (listn entries), pixels that straddle an axis through the centre
-        // from the top (nstr entries), so that a lane-parallel round of the
-        // former evaluates a single quadrant piece
+        // from the top (nstr entries), whose pieces on the two sides are
+        // evaluated by two lanes
         int listn = 0, nstr = 0;
-        auto add_w = [&](const ApEntry<Real>& E, Real w) __attribute__((always_inline)) {
+        auto add_w = [&](const ApEntry<Real>& E, bool on, Real w) __attribute__((always_inline)) {
             const double ws = (double)w * (double)E.m;
-            const Real wa = w, wvv = w * w * E.var;
-            const int i0 = E.j * 64 + lane;
-            binS[i0] += ws;
-            binA[i0] += (double)wa;
-            binV[i0] += (double)wvv;
-            if (E.j + 1 < NC) {
-                binS[i0 + 64] -= ws;
-                binA[i0 + 64] -= (double)wa;
-                binV[i0 + 64] -= (double)wvv;
+            const Real wvv = w * w * E.var;
+            const int jj = on ? (int)(E.code >> 16) : -1;
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                S[j] += jj == j ? ws : 0.0;
+                A[j] += (double)(jj == j ? w : (Real)0);
+                V[j] += (double)(jj == j ? wvv : (Real)0);
             }
         };
         // exact weights of the queued cut pixels
         auto flush = [&]() __attribute__((always_inline)) {
             wave_sync();
-            for (int e = lane; e < listn; e += 64) {
-                const ApEntry<Real> E = list[e];
-                const Real rj = rad[E.j];
-                const Real ax = fabs(E.dx), ay = fabs(E.dy);
-                const Real w = quad_area<Real>(ax - (Real)0.5, ax + (Real)0.5, ay - (Real)0.5, ay + (Real)0.5, rj,
-                                               rj * rj);
-                add_w(E, w);
+            for (int e0 = 0; e0 < listn; e0 += 64) {
+                const ApEntry<Real> E = list[min(e0 + lane, listn - 1)];
+                const Real rj = rad[E.code >> 16];
+                const Real ax = fabs((Real)((int)(E.code & 255u) - R) - fx);
+                const Real ay = fabs((Real)((int)((E.code >> 8) & 255u) - R) - fy);
+                const Real w = quad_area<Real, false>(ax - (Real)0.5, ax + (Real)0.5, ay - (Real)0.5, ay + (Real)0.5,
+                                                      rj, rj * rj);
+                add_w(E, e0 + lane < listn, w);
             }
-            for (int e = lane; e < nstr; e += 64) {
-                const ApEntry<Real> E = list[kApList - 1 - e];
-                const Real rj = rad[E.j];
-                add_w(E, pixel_area<Real>(E.dx, E.dy, rj, rj * rj));
+            for (int e0 = 0; e0 < nstr; e0 += 32) {
+                // lane pair: the two sides of the axis x = xc (or of y = yc);
+                // a pixel on both axes has two pieces per lane
+                const int e = e0 + (lane >> 1);
+                const ApEntry<Real> E = list[kApList - 1 - min(e, nstr - 1)];
+                const Real rj = rad[E.code >> 16];
+                const Real ax = fabs((Real)((int)(E.code & 255u) - R) - fx);
+                const Real ay = fabs((Real)((int)((E.code >> 8) & 255u) - R) - fy);
+                const Real xl = ax - (Real)0.5, xh = ax + (Real)0.5, yl = ay - (Real)0.5, yh = ay + (Real)0.5;
+                const bool sx = xl < (Real)0, sy = yl < (Real)0, second = (lane & 1) != 0;
+                const Real px0 = sx ? (Real)0 : xl, px1 = sx && !second ? -xl : xh;
+                Real py0 = yl, py1 = yh;
+                if (sy) {
+                    py0 = (Real)0;
+                    py1 = sx || !second ? -yl : yh;
+                }
+                const Real a1 = quad_area<Real, true>(px0, px1, py0, py1, rj, rj * rj);
+                Real a2 = (Real)0;
+                if (__ballot(sx && sy) != 0ull && sx && sy) a2 = quad_area<Real, true>(px0, px1, (Real)0, yh, rj, rj * rj);
+                const Real o1 = __shfl_xor(a1, 1), o2 = __shfl_xor(a2, 1);
+                add_w(E, e < nstr && !second, ((a1 + a2) + o1) + o2);
             }
             listn = 0;
             nstr = 0;
             wave_sync();
         };
         const int ry0 = max(by0, 0), ry1 = min(by0 + side - 1, d.H - 1);
+        const int band = min(64, kApCubics / nix);
         for (int band0 = ry0; band0 <= ry1; band0 += band) {
             const int nb = min(band, ry1 - band0 + 1);
             wave_sync();
@@ -240,152 +307,122 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(Real
                 const int y = __shfl_up(incl, o);
                 if (lane >= o) incl += y;
             }
-            const int total = __shfl(incl, nb - 1);
+            const int total = __builtin_amdgcn_readlane(incl, nb - 1);
+            // (the rows with pixels are consecutive: a chord grows towards the centre)
+            int r0 = total > 0 ? __builtin_ctzll(__ballot(cnt > 0)) : 0;   // row of the numbers reached so far
+            for (int i = lane; i < (total + 63) / 64 * 2; i += 64) mark[i] = 0u;
+            wave_sync();
             if (lane < nb) {
-                rxl[lane] = xl;
-                roff[lane] = incl - cnt;
+                const int start = incl - cnt;
+                rows[lane] = ApRow{(band0 + lane) * (int)d.pitch + xl - start, xl - start};
+                if (start > 0) atomicOr(&mark[(start - 1) >> 5], 1u << ((start - 1) & 31));
             }
-            if (lane == 0) roff[nb] = total;
-            for (int e = lane; e < nb * nix; e += 64) {
-                const int rr = e / nix, pi = e - rr * nix;
+            for (int i = lane; i < 2 * nb * nix; i += 64) {
+                const int e = i >> 1, rr = e / nix, pi = e - rr * nix;
                 const int py = band0 + rr;
                 const int jy = piece_of(py, d.H, d.mh);
                 const double u = (double)py - piece_ref(jy, d.H, d.mh);
-                tab[rr * nixmax + pi] = make_row<Real>(d.coef, d.nx, d.ny, ixlo + pi, jy, u);
+                make_half_row(d.coef, d.nx, d.ny, i & 1, ixlo + pi, jy, u, tab[e]);
             }
             wave_sync();
-            // the band's row offsets in registers: a pixel's row is the number
-            // of rows that end at or before it (compares, no dependent loads)
-            int ro[kApBand + 1];
-#pragma unroll
-            for (int q = 0; q <= kApBand; ++q) ro[q] = (q <= nb) ? roff[q] : 0x7fffffff;
-            for (int b0 = 0; b0 < total; b0 += 64 * kApUnroll) {
-                int pxs[kApUnroll], rrs[kApUnroll];
-                float iv[kApUnroll];
-#pragma unroll
-                for (int u = 0; u < kApUnroll; ++u) {
-                    const int idx = b0 + u * 64 + lane;
-                    rrs[u] = -1;
-                    pxs[u] = 0;
-                    iv[u] = 0.0f;
-                    if (idx < total) {
-                        int r = 0, start = 0;
-#pragma unroll
-                        for (int q = 1; q <= kApBand; ++q) {
-                            const bool past = ro[q] <= idx;
-                            r += past ? 1 : 0;
-                            start = past ? ro[q] : start;
-                        }
-                        rrs[u] = r;
-                        pxs[u] = rxl[r] + (idx - start);
-                        iv[u] = load_px(d, pxs[u], band0 + r);
+            // row, column and value of pixel number b + lane (row -1: past the band)
+            auto fetch = [&](int b, int& r, int& px, float& v) __attribute__((always_inline)) {
+                r = -1;
+                px = bx0;
+                v = 0.0f;
+                if (b >= total) return;
+                const uint32_t m0 = mark[b >> 5], m1 = mark[(b >> 5) + 1];
+                const int rr = r0 + (int)__builtin_amdgcn_mbcnt_hi(m1, __builtin_amdgcn_mbcnt_lo(m0, 0u));
+                r0 += __popc(m0) + __popc(m1);
+                if (b + lane < total) {
+                    const ApRow W = rows[rr];
+                    const int off = W.off + b + lane;
+                    r = rr;
+                    px = W.x0 + b + lane;
+                    v = d.dtype == kDtypeU16 ? (float)((gu16_t*)d.data)[off] : ((gfloat_t*)d.data)[off];
+                }
+            };
+            int r_, px;
+            float iv;
+            fetch(0, r_, px, iv);
+            int b0 = 0;
+            do {
+                int rn, pxn;
+                float ivn;
+                fetch(b0 + 64, rn, pxn, ivn);   // (the next round's loads under this one's work)
+                const int c = px - bx0, cy = band0 + max(r_, 0) - by0;
+                const Real dx = (Real)(c - R) - fx;
+                const Real dy = (Real)(cy - R) - fy;
+                const Real ax = fabs(dx), ay = fabs(dy);
+                const Real nxd = fmax(ax - (Real)0.5, (Real)0), nyd = fmax(ay - (Real)0.5, (Real)0);
+                const Real fxd = ax + (Real)0.5, fyd = ay + (Real)0.5;
+                const Real dmin2 = nxd * nxd + nyd * nyd, dmax2 = fxd * fxd + fyd * fyd;
+                const bool use = r_ >= 0 && dmin2 < rmax2;
+                int kin = 0, kout = 0;
+                Real m = 0, var = 0;
+                if (use) {
+                    const ApCol<Real> C = cols[c];
+                    const RowT<Real> T = tab[r_ * nix + C.piece];
+                    m = eval_M(T, C.sx, (Real)iv);
+                    if (a.want_err) {
+                        const Real rv = eval_R(T, C.sx);
+                        var = rv * rv + ((m > (Real)0) ? m * inv_gain : (Real)0);
                     }
+                    ++used;
                 }
 #pragma unroll
-                for (int u = 0; u < kApUnroll; ++u) {
-                    const int r_ = rrs[u];
-                    const int px = pxs[u], py = band0 + (r_ < 0 ? 0 : r_);
-                    const Real dx = (Real)(px - cxi) - fx;
-                    const Real dy = (Real)(py - cyi) - fy;
-                    const Real ax = fabs(dx), ay = fabs(dy);
-                    const Real nxd = fmax(ax - (Real)0.5, (Real)0), nyd = fmax(ay - (Real)0.5, (Real)0);
-                    const Real fxd = ax + (Real)0.5, fyd = ay + (Real)0.5;
-                    const Real dmin2 = nxd * nxd + nyd * nyd, dmax2 = fxd * fxd + fyd * fyd;
-                    const bool use = r_ >= 0 && dmin2 < rmax2;
-                    int kin = NC, kout = NC;
-                    Real m = 0, var = 0;
-                    if (use) {
-                        const int c = px - bx0;
-                        const RowT<Real> T = tab[r_ * nixmax + colp[c]];
-                        const Real sx = cols[c];
-                        m = eval_M(T, sx, (Real)iv[u]);
-                        if (a.want_err) {
-                            const Real rv = eval_R(T, sx);
-                            var = rv * rv + ((m > (Real)0) ? m * inv_gain : (Real)0);
-                        }
-                        kin = 0;
-                        kout = 0;
-#pragma unroll
-                        for (int j = 0; j < NC; ++j) {
-                            kin += (cr2[j] < dmax2) ? 1 : 0;
-                            kout += (cr2[j] <= dmin2) ? 1 : 0;
-                        }
-                        if (kin < NC) {
-                            const int i0 = kin * 64 + lane;
-                            binS[i0] += (double)m;
-                            binA[i0] += 1.0;
-                            binV[i0] += (double)var;
-                        }
-                    }
-                    // circles that cut the pixel: queue (pixel, circle) pairs
-                    const int ncut = kin - kout;
-                    const bool str = ax < (Real)0.5 || ay < (Real)0.5;
-                    for (int q = 0;; ++q) {
-                        const bool has = q < ncut;
-                        const uint64_t bm = __ballot(has && !str), bs = __ballot(has && str);
-                        if ((bm | bs) == 0ull) break;
-                        if (has) {
-                            const int pos = str ? kApList - 1 - (nstr + __popcll(bs & below))
-                                                : listn + __popcll(bm & below);
-                            list[pos] = ApEntry<Real>{dx, dy, m, var, kout + q};
-                        }
-                        listn += __popcll(bm);
-                        nstr += __popcll(bs);
-                        if (listn + nstr > kApList - 64) flush();
+                for (int j = 0; j < NC; ++j) {
+                    const bool cut = use && cr2[j] < dmax2, in = use && !cut;
+                    kin += cut ? 1 : 0;
+                    kout += use && cr2[j] <= dmin2 ? 1 : 0;
+                    notin[j] += cut ? 1 : 0;
+                    if (__ballot(in) != 0ull) {   // (the inner circles: the rows near the centre)
+                        S[j] += (double)(in ? m : (Real)0);
+                        V[j] += (double)(in ? var : (Real)0);
                     }
                 }
-            }
-        }
-        flush();
-        // circle sums: prefix over the bins in each lane (in place), then each
-        // of the 3 NC totals summed over the lanes in a fixed order
-        {
-            double ps = 0.0, pa = 0.0, pv = 0.0;
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-                const int i0 = j * 64 + lane;
-                ps += binS[i0];
-                pa += binA[i0];
-                pv += binV[i0];
-                binS[i0] = ps;
-                binA[i0] = pa;
-                binV[i0] = pv;
-            }
-        }
-        wave_sync();
-        constexpr int Q = 3 * NC;
-        constexpr int Q2 = (Q <= 16) ? 16 : 32;
-        constexpr int G = 64 / Q2;          // lanes per total
-        constexpr int SPAN = 64 / G;        // lane slots each of them sums
-        double part = 0.0;
-        {
-            const int q = lane / G, g = lane - q * G;
-            if (q < Q) {
-                const int j = (q < NC) ? q : (q < 2 * NC ? q - NC : q - 2 * NC);
-                const int s0 = j * 64 + g * SPAN;
-                if (q < NC) {
-                    for (int t = 0; t < SPAN; ++t) part += binS[s0 + t];
-                } else {
-                    const double* src = (q < 2 * NC) ? binA : binV;
-                    for (int t = 0; t < SPAN; ++t) part += (double)src[s0 + t];
+                // circles that cut the pixel: queue (pixel, circle) pairs; the
+                // queue is worked off when full and at the object's last round
+                const int ncut = kin - kout;
+                const bool str = ax < (Real)0.5 || ay < (Real)0.5;
+                const uint32_t code = (uint32_t)c | ((uint32_t)cy << 8);
+                const bool last = band0 + band > ry1 && b0 + 64 >= total;
+                for (int q = 0;; ++q) {
+                    const bool has = q < ncut;
+                    const uint64_t bm = __ballot(has && !str), bs = __ballot(has && str);
+                    const bool none = (bm | bs) == 0ull;
+                    if (has) {
+                        const int pos = str ? kApList - 1 - (nstr + __popcll(bs & below))
+                                            : listn + __popcll(bm & below);
+                        list[pos] = ApEntry<Real>{m, var, code | ((uint32_t)(kout + q) << 16)};
+                    }
+                    listn += __popcll(bm);
+                    nstr += __popcll(bs);
+                    if (listn + nstr > kApList - 64 || (none && last)) flush();
+                    if (none) break;
                 }
-            }
-#pragma unroll
-            for (int o = G / 2; o >= 1; o >>= 1) {
-                const double w = __shfl_xor(part, o);
-                part = ((lane & o) == 0) ? part + w : w + part;
-            }
+                r_ = rn;
+                px = pxn;
+                iv = ivn;
+            } while ((b0 += 64) < total);
         }
-        double S[NC], A[NC], V[NC];
+        constexpr int N = (3 * NC <= 16) ? 16 : 32;
+        double x[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = 0.0;
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
-            S[j] = __shfl(part, j * G);
-            A[j] = __shfl(part, (NC + j) * G);
-            V[j] = a.want_err ? __shfl(part, (2 * NC + j) * G) : 0.0;
+            x[j] = S[j];
+            x[NC + j] = A[j] + (double)(used - notin[j]);
+            x[2 * NC + j] = V[j];
         }
+        const WaveTotals<N> T(x);
         double Sin = 0, Ain = 0, Sout = 0, Aout = 0;
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
+            S[j] = T.total(j);
+            A[j] = T.total(NC + j);
+            V[j] = T.total(2 * NC + j);
             const int role = a.crole[j];
             if (role == kMaxRadii) {
                 Sin = S[j];
@@ -418,31 +455,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(Real
 
 template <typename Real, int NC>
 static void launch_ap_nc(const FrameDesc* desc, const FrameDesc* one, const ApArgs& a, const ApCat& cat, int blocks,
-                         int band, int nixmax, hipStream_t s) {
-    const ApLayout<Real, NC> L(band, nixmax);
+                         int side, int nixmax, hipStream_t s) {
+    const ApLayout<Real, NC> L(side);
     // waves per workgroup: as many (up to kApWaves) as keep the workgroup's
     // LDS within 64 KB; the grid keeps the same number of wavefronts
+    const size_t pre = (size_t)ap_prefix_bytes(a.nframes);
     int nw = kApWaves;
-    while (nw > 1 && (size_t)kApPrefixBytes + (size_t)L.bytes * nw > 64 * 1024) nw >>= 1;
-    const size_t lds = (size_t)kApPrefixBytes + (size_t)L.bytes * nw;
+    while (nw > 1 && pre + (size_t)L.bytes * nw > 64 * 1024) nw >>= 1;
+    const size_t lds = pre + (size_t)L.bytes * nw;
     const int wg = blocks * (kApWaves / nw);
     const int g = kXcds * std::max(1, (wg + kXcds - 1) / kXcds);
-    if (one) k_aperture<Real, NC, true><<<g, 64 * nw, lds, s>>>(desc, *one, a, cat, band, nixmax);
-    else k_aperture<Real, NC, false><<<g, 64 * nw, lds, s>>>(desc, FrameDesc{}, a, cat, band, nixmax);
+    if (one) k_aperture<Real, NC, true><<<g, 64 * nw, lds, s>>>(desc, *one, a, cat, nixmax);
+    else k_aperture<Real, NC, false><<<g, 64 * nw, lds, s>>>(desc, FrameDesc{}, a, cat, nixmax);
 }
 
 template <typename Real>
 static void launch_ap_t(const FrameDesc* desc, const FrameDesc* one, const ApArgs& a, const ApCat& cat, int blocks,
-                        int band, int nixmax, hipStream_t s) {
+                        int side, int nixmax, hipStream_t s) {
     switch (a.nr + 2) {
-        case 3: launch_ap_nc<Real, 3>(desc, one, a, cat, blocks, band, nixmax, s); break;
-        case 4: launch_ap_nc<Real, 4>(desc, one, a, cat, blocks, band, nixmax, s); break;
-        case 5: launch_ap_nc<Real, 5>(desc, one, a, cat, blocks, band, nixmax, s); break;
-        case 6: launch_ap_nc<Real, 6>(desc, one, a, cat, blocks, band, nixmax, s); break;
-        case 7: launch_ap_nc<Real, 7>(desc, one, a, cat, blocks, band, nixmax, s); break;
-        case 8: launch_ap_nc<Real, 8>(desc, one, a, cat, blocks, band, nixmax, s); break;
-        case 9: launch_ap_nc<Real, 9>(desc, one, a, cat, blocks, band, nixmax, s); break;
-        default: launch_ap_nc<Real, 10>(desc, one, a, cat, blocks, band, nixmax, s); break;
+        case 3: launch_ap_nc<Real, 3>(desc, one, a, cat, blocks, side, nixmax, s); break;
+        case 4: launch_ap_nc<Real, 4>(desc, one, a, cat, blocks, side, nixmax, s); break;
+        case 5: launch_ap_nc<Real, 5>(desc, one, a, cat, blocks, side, nixmax, s); break;
+        case 6: launch_ap_nc<Real, 6>(desc, one, a, cat, blocks, side, nixmax, s); break;
+        case 7: launch_ap_nc<Real, 7>(desc, one, a, cat, blocks, side, nixmax, s); break;
+        case 8: launch_ap_nc<Real, 8>(desc, one, a, cat, blocks, side, nixmax, s); break;
+        case 9: launch_ap_nc<Real, 9>(desc, one, a, cat, blocks, side, nixmax, s); break;
+        default: launch_ap_nc<Real, 10>(desc, one, a, cat, blocks, side, nixmax, s); break;
     }
 }
 
@@ -459,9 +497,8 @@ void launch_aperture(const FrameDesc* desc, const FrameDesc* one, const ApArgs& 
     const int R = (int)ceilf(a.rmax) + 1;
     const int side = 2 * R + 2;
     const int nixmax = ap_nixmax(side, mesh_w, max_nx);
-    const int band = kApBand;
-    if (f64) launch_ap_t<double>(desc, one, a, cat, blocks, band, nixmax, s);
-    else launch_ap_t<float>(desc, one, a, cat, blocks, band, nixmax, s);
+    if (f64) launch_ap_t<double>(desc, one, a, cat, blocks, side, nixmax, s);
+    else launch_ap_t<float>(desc, one, a, cat, blocks, side, nixmax, s);
 }
 
 }  // namespace gpk

@@ -62,31 +62,44 @@ __device__ __forceinline__ Real theta_minus_sin(Real t) {
     return t - sin(t);
 }
 
-// area of the disk (centre 0, radius r) inside [a0,a1] x [b0,b1], all >= 0
+// theta - sin(theta) for theta = 2 asin(s), s >= 1/4.  Only circles of radius
+// below 2 sqrt(2) have chords that wide, so it is called, not inlined: asin and
+// sin would take 30 registers of every wavefront's loop.
 template <typename Real>
+__device__ __attribute__((noinline)) Real seg_wide(Real s) {
+    return theta_minus_sin<Real>((Real)2 * asin(s));
+}
+
+// area of the disk (centre 0, radius r) inside [a0,a1] x [b0,b1], all >= 0.
+// Every rounding is written out (the compiler fuses nothing by itself), so a
+// weight has the same bits wherever this is inlined.  AXIS: a piece of a pixel
+// that straddles an axis through the centre (its roundings differ).
+template <typename Real, bool AXIS>
 __device__ __forceinline__ Real quad_area(Real a0, Real a1, Real b0, Real b1, Real r, Real r2) {
-    if (a0 * a0 + b0 * b0 >= r2) return (Real)0;
-    if (a1 * a1 + b1 * b1 <= r2) return (a1 - a0) * (b1 - b0);
-    const Real uhi = ap_sqrt(fmax(r2 - b0 * b0, (Real)0));   // arc height == b0
+#pragma clang fp contract(off)
+    const Real b0s = b0 * b0, b1s = b1 * b1;
+    if ((AXIS ? a0 * a0 + b0s : fma(a0, a0, b0s)) >= r2) return (Real)0;
+    if ((AXIS ? a1 * a1 + b1s : fma(a1, a1, b1s)) <= r2) return (a1 - a0) * (b1 - b0);
+    const Real uhi = ap_sqrt(fmax(AXIS ? fma(-b0, b0, r2) : r2 - b0s, (Real)0));   // arc height == b0
     // abscissa where the arc height is b1; when b1 >= r the arc stays below b1
-    const Real ulo = (b1 * b1 < r2) ? ap_sqrt(r2 - b1 * b1) : (Real)-1;
+    const Real ulo = (b1s < r2) ? ap_sqrt(AXIS ? fma(-b1, b1, r2) : r2 - b1s) : (Real)-1;
     const Real p = fmin(fmax(ulo, a0), a1);
     const Real q = fmin(uhi, a1);
     Real area = (p - a0) * (b1 - b0);
     if (q > p) {
         // arc heights above b0 at p and q: (r^2 - u^2 - b0^2) / (s(u) + b0)
-        const Real sp = (p == ulo) ? b1 : ap_sqrt(fmax(r2 - p * p, (Real)0));
-        const Real sq = (q == uhi) ? b0 : ap_sqrt(fmax(r2 - q * q, (Real)0));
+        const Real sp = (p == ulo) ? b1 : ap_sqrt(fmax(fma(-p, p, r2), (Real)0));
+        const Real sq = (q == uhi) ? b0 : ap_sqrt(fmax(fma(-q, q, r2), (Real)0));
         const Real hp = (p == ulo) ? (b1 - b0) : ap_div(fma(-p, p, fma(-b0, b0, r2)), sp + b0);
         const Real hq = (q == uhi) ? (Real)0 : ap_div(fma(-q, q, fma(-b0, b0, r2)), sq + b0);
-        area += (Real)0.5 * (q - p) * (hp + hq);
+        area = fma((Real)0.5 * (q - p), hp + hq, area);
         // circular segment between the chord and the arc: half chord over r
         // is the sine of half the angle it subtends
         const Real dxc = q - p, dyc = sp - sq;
-        const Real chord = ap_sqrt(dxc * dxc + dyc * dyc);
+        const Real chord = ap_sqrt(fma(dxc, dxc, dyc * dyc));
         const Real sh = fmin(ap_div(chord, (Real)2 * r), (Real)1);
-        const Real tms = (sh < (Real)0.25) ? seg_series<Real>(sh) : theta_minus_sin<Real>((Real)2 * asin(sh));
-        area += (Real)0.5 * r2 * tms;
+        const Real tms = (sh < (Real)0.25) ? seg_series<Real>(sh) : seg_wide<Real>(sh);
+        area = fma((Real)0.5 * r2, tms, area);
     }
     return area;
 }
@@ -119,7 +132,7 @@ __device__ __forceinline__ Real pixel_area(Real dx, Real dy, Real r, Real r2) {
     Real a = 0;
     for (int i = 0; i < nxp; ++i)
         for (int j = 0; j < nyp; ++j)
-            if (xb[i] > xa[i] && yb[j] > ya[j]) a += quad_area<Real>(xa[i], xb[i], ya[j], yb[j], r, r2);
+            if (xb[i] > xa[i] && yb[j] > ya[j]) a += quad_area<Real, true>(xa[i], xb[i], ya[j], yb[j], r, r2);
     return a;
 }
 

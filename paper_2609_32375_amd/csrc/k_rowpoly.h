@@ -71,6 +71,35 @@ __device__ __forceinline__ RowT<double> make_row<double>(const double* coef, int
     return t;
 }
 
+// the background (q = 0) or noise (q = 1) half of make_row's cubics: half the
+// coefficients in registers, and two lanes to a row
+__device__ __forceinline__ void make_half_row(const double* coef, int nx, int ny, int q, int ix, int jy, double u,
+                                              RowT<float>& t) {
+    double a[4];
+    piece_row(coef, nx, ny, q, ix, jy, u, a);
+    const float c0 = (float)a[0], lo = (float)(a[0] - (double)c0);
+    float* o = q ? &t.r0 : &t.a1;
+    if (!q) {
+        t.a0h = c0;
+        t.a0l = lo;
+    } else {
+        *o++ = c0;
+    }
+    o[0] = (float)a[1];
+    o[1] = (float)a[2];
+    o[2] = (float)a[3];
+}
+__device__ __forceinline__ void make_half_row(const double* coef, int nx, int ny, int q, int ix, int jy, double u,
+                                              RowT<double>& t) {
+    double a[4];
+    piece_row(coef, nx, ny, q, ix, jy, u, a);
+    double* o = q ? &t.r0 : &t.a0;
+    o[0] = a[0];
+    o[1] = a[1];
+    o[2] = a[2];
+    o[3] = a[3];
+}
+
 // M = I - B at local coordinate s of the row's piece
 __device__ __forceinline__ float eval_M(const RowT<float>& t, float s, float v) {
     float delta = fmaf(fmaf(t.a3, s, t.a2), s, t.a1) * s;

@@ -14,7 +14,7 @@ import pytest
 
 import oracle
 from synth import Params, gaussian_kernel, make_frame
-from tests._util import (AMBIG_T, TOL_B64_ABS, TOL_BKG_REL, TOL_R64_REL, TOL_CEN, TOL_MOM_ABS, check_meshes, cmp_catalog, cmp_phot, f32_params,
+from tests._util import (AMBIG_T, TOL_B64_ABS, TOL_BKG_REL, TOL_R64_REL, TOL_CEN, TOL_MOM_ABS, check_meshes, cmp_catalog, cmp_phot, f32, f32_params,
                          growth_allowance, mesh_ambiguous, peak_ambiguous, phot_condition, thresh_ambiguous, weight_allowance)
 
 pytestmark = pytest.mark.gpu
@@ -469,6 +469,41 @@ def test_aperture_stage_isolated_exact_centres(P, case):
     allow = weight_allowance(M, xs, ys, p, oph)
     err = cmp_phot(r["phot"], oph, cond, cond_ann, allow, tag=str(case))
     _say("photometry errors", err)
+    np.testing.assert_array_equal((r["cat"]["flags"] & 8) != 0, (oph["flags"] & 8) != 0)
+    ph.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("m,radii,r_in,r_out", [
+    (16, (0.4, 0.9), 1.2, 2.0),                                     # circles inside one pixel and its neighbours
+    (64, (1.0, 2.6, 5.0, 7.0, 9.0, 11.0, 13.0, 15.0), 16.0, 20.0),  # ten circles, the cut queue filled several times
+    (64, (40.0,), 50.0, 64.0),                                      # boxes of several bands of rows
+    (16, (30.0,), 33.0, 64.0),                                      # eleven spline pieces across a box
+    (128, (3.0,), 0.0, 4.0),                                        # no inner circle
+], ids=lambda v: str(v))
+def test_aperture_box_and_queue_edges(P, m, radii, r_in, r_out, prec):
+    _say("aperture edges", m, radii, r_in, r_out, prec)
+    fr, p = _field(FIELD_CASES[0])
+    p.mesh_w = p.mesh_h = m
+    p.radii, p.r_in, p.r_out, p.gain, p.want_err = tuple(f32(r) for r in radii), f32(r_in), f32(r_out), f32(1.5), True
+    img = fr.image
+    I = img.astype(np.float64)
+    H, W = img.shape
+    ob = oracle.background(I, p, maps=True)
+    M = I - ob.B
+    rng = np.random.default_rng(6)
+    xs = np.concatenate([rng.uniform(-3, W + 3, 30), [0.0, W - 1.0, 20.0, 20.5, 31.5, -70.0, W / 2]])
+    ys = np.concatenate([rng.uniform(-3, H + 3, 30), [0.0, H - 1.0, 20.0, 20.0, 31.5, 5.0, H + 70.0]])
+    ph = P.Photometry([_dev(img)], p, p.kernel(), capacity=len(xs), precision=prec)
+    ph.set_grids(0, ob.back, ob.rms)
+    ph.background(grid_given=True)
+    ph.set_catalog(0, xs, ys)
+    ph.aperture()
+    r = ph.results(0)
+    oph = oracle.aperture(M, ob.R, xs, ys, list(p.radii), p.r_in, p.r_out, p.gain, p.want_err)
+    cond, cond_ann = phot_condition(M, xs, ys, p)
+    allow = weight_allowance(M, xs, ys, p, oph, precision=prec)
+    _say("photometry errors", cmp_phot(r["phot"], oph, cond, cond_ann, allow))
     np.testing.assert_array_equal((r["cat"]["flags"] & 8) != 0, (oph["flags"] & 8) != 0)
     ph.close()
 
