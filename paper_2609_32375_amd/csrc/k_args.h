@@ -27,12 +27,13 @@ struct DetArgs {
     double kdd[kMaxK * kMaxK];
 };
 
-// what the host hands to the argument-writing kernel (the dense kernel is
-// normalised on the device)
+// what the host hands to the argument-writing kernel (the dense kernel and the
+// FP64 sum of its taps that it is divided by)
 struct DetArgsIn {
     int32_t kw, kh, separable, conn;
     float thresh, sat;
     int32_t minarea, want_seg;
+    double norm;
     float kraw[kMaxK * kMaxK];
     float kx[kMaxK], ky[kMaxK];
     double kxd[kMaxK], kyd[kMaxK];
@@ -66,28 +67,28 @@ struct CatOut {
 };
 
 // spatially varying matched filter: a reference kernel and up to kMaxModes
-// eigenmodes (taps as given, [column][row][mode] with P0 as mode 0, modes
-// padded to kMaxModes + 1) and, per frame,
-// the coefficient maps (map k of frame f at pf[f].data + k * plane; pixel
-// (x, y) reads [(y / bin) * pitch + x / bin])
+// eigenmodes (taps as given, in the working precision, [column][row][mode] with
+// P0 as mode 0, the modes padded to psf_modes(nmodes)) and, per frame, the
+// coefficient maps (map k of frame f at pf[f].data + k * plane; pixel (x, y)
+// reads [(y / bin) * pitch + x / bin])
 constexpr int kMaxModes = 8;
 constexpr int kPsfTaps = (kMaxModes + 1) * kMaxK * kMaxK;
-struct PsfArgs {
-    int32_t nmodes, bin, kw, kh;
-    float taps[kPsfTaps];
-    double tapsd[kPsfTaps];
-};
 struct PsfFrame {
     const float* data;
     int64_t pitch, plane;
 };
+// correlations of the kernel variant that takes nmodes modes
+__host__ __device__ constexpr int psf_modes(int nmodes) {
+    return nmodes < 2 ? 2 : nmodes < 4 ? 4 : nmodes < 6 ? 6 : kMaxModes + 1;
+}
 
-// peak detection: separation and centroid half-widths (pixels); psf and pf
+// peak detection: separation and centroid half-widths (pixels); taps and pf
 // set for the spatially varying filter, else null
 struct PeakArgs {
     int32_t sep, cwin;
-    const PsfArgs* psf;
+    const void* taps;
     const PsfFrame* pf;
+    int32_t nmodes, bin;
     int32_t mesh_w;   // mesh width of the call (sizes the row cubics of a region row)
 };
 constexpr int kMaxPeakWin = 7;
@@ -145,8 +146,8 @@ void launch_catalog(const DetWork& wk, const CatOut& cat, int minarea, int persi
                     hipStream_t s);
 void launch_seg(const DetWork& wk, int f, int64_t npx, hipStream_t s);
 void launch_peaks(const DetWork& wk, const DetArgs* args, const CatOut& cat, int32_t* comp_status, bool f64, int sep,
-                  int cwin, int kw, int kh, int persist_blocks, const PsfArgs* psf, const PsfFrame* pf,
-                  int nmodes, int mesh_w, int xcd_cus, hipStream_t s);
+                  int cwin, int kw, int kh, int persist_blocks, const void* taps, const PsfFrame* pf,
+                  int nmodes, int bin, int mesh_w, int xcd_cus, hipStream_t s);
 // copy `bytes` (a multiple of 4) from host memory to device memory through
 // kernel arguments (no copy engine, so the call can be captured)
 void launch_write_bytes(void* dst, const void* src, size_t bytes, hipStream_t s);

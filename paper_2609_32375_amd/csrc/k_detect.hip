@@ -1356,8 +1356,8 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
         // the 70 x 70 outputs of sep 3 make 490 items, two rounds of the 256
         // threads, and each tap feeds ten FMAs
         typedef __attribute__((address_space(4))) const Real ctap_t;
-        const ctap_t* tp = (const ctap_t*)(kDbl ? (const void*)pk.psf->tapsd : (const void*)pk.psf->taps);
-        const int nmodes = pk.psf->nmodes;
+        const ctap_t* tp = (const ctap_t*)pk.taps;
+        const int nmodes = pk.nmodes;
         constexpr int kVaryRows = 10;
         const int nrb = (fh + kVaryRows - 1) / kVaryRows;
         for (int it = tid; it < fw * nrb; it += 256) {
@@ -1368,7 +1368,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
             // (the item's coefficients are loaded after the correlations:
             // held during them they would cost (NA - 1) x kVaryRows registers)
             const PsfFrame pfr = pk.pf[f];
-            const int bin = pk.psf->bin;
+            const int bin = pk.bin;
             const int gx = x0 - sep + i;
             Real acc[NA][kVaryRows];
 #pragma unroll
@@ -1385,7 +1385,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
 #pragma unroll
                 for (int t = 0; t < NC; ++t)
                     col[t] = (t < kh + kVaryRows - 1) ? ms[min(mr0 + t, L.rmh - 1) * L.rmw + mc + b] : (Real)0;
-                const ctap_t* tb = tp + b * kh * (kMaxModes + 1);
+                const ctap_t* tb = tp + b * kh * NA;
                 constexpr int kTapRows = 2;
 #pragma unroll
                 for (int a0 = 0; a0 < kMaxK; a0 += kTapRows) {
@@ -1394,7 +1394,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
 #pragma unroll
                         for (int c = 0; c < kTapRows; ++c)
 #pragma unroll
-                            for (int m = 0; m < NA; ++m) t[c][m] = tb[min(a0 + c, kh - 1) * (kMaxModes + 1) + m];
+                            for (int m = 0; m < NA; ++m) t[c][m] = tb[min(a0 + c, kh - 1) * NA + m];
 #pragma unroll
                         for (int c = 0; c < kTapRows; ++c)
                             if (a0 + c < kh && a0 + c < kMaxK)
@@ -1686,17 +1686,19 @@ static void launch_peak_tiles(const DetWork& wk, const DetArgs* args, const Peak
 template <typename Real>
 static void launch_peak_tiles_t(const DetWork& wk, const DetArgs* args, const PeakArgs& pk, int kw, int kh,
                                 int nmodes, int mesh_w, int xcd_cus, hipStream_t s) {
-    if (!pk.psf) launch_peak_tiles<Real, 0>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s);
-    else if (nmodes < 2) launch_peak_tiles<Real, 2>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s);
-    else if (nmodes < 4) launch_peak_tiles<Real, 4>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s);
-    else if (nmodes < 6) launch_peak_tiles<Real, 6>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s);
-    else launch_peak_tiles<Real, kMaxModes + 1>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s);
+    switch (pk.taps ? psf_modes(nmodes) : 0) {
+        case 0: launch_peak_tiles<Real, 0>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s); break;
+        case 2: launch_peak_tiles<Real, 2>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s); break;
+        case 4: launch_peak_tiles<Real, 4>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s); break;
+        case 6: launch_peak_tiles<Real, 6>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s); break;
+        default: launch_peak_tiles<Real, kMaxModes + 1>(wk, args, pk, kw, kh, mesh_w, xcd_cus, s); break;
+    }
 }
 
 void launch_peaks(const DetWork& wk, const DetArgs* args, const CatOut& cat, int32_t* comp_status, bool f64, int sep,
-                  int cwin, int kw, int kh, int persist_blocks, const PsfArgs* psf, const PsfFrame* pf,
-                  int nmodes, int mesh_w, int xcd_cus, hipStream_t s) {
-    const PeakArgs pk{sep, cwin, psf, pf, mesh_w};
+                  int cwin, int kw, int kh, int persist_blocks, const void* taps, const PsfFrame* pf,
+                  int nmodes, int bin, int mesh_w, int xcd_cus, hipStream_t s) {
+    const PeakArgs pk{sep, cwin, taps, pf, nmodes, bin, mesh_w};
     if (f64) launch_peak_tiles_t<double>(wk, args, pk, kw, kh, nmodes, mesh_w, xcd_cus, s);
     else launch_peak_tiles_t<float>(wk, args, pk, kw, kh, nmodes, mesh_w, xcd_cus, s);
     k_peak_bits<<<persist_blocks, 256, 0, s>>>(wk);
@@ -1795,8 +1797,9 @@ __global__ void k_write_desc(DescChunk c, FrameDesc* table) {
 }
 
 // Per-call set-up of the detection, one workgroup: the last descriptors, the
-// filter arguments (the dense kernel normalised with an FP64 sum in a fixed
-// order) and zeroed counters.  (The detection tiles clear the rank bitmap.)
+// filter arguments and zeroed counters.  (The detection tiles clear the rank
+// bitmap.)  The sum of the taps comes with the arguments: 169 additions in a
+// row took 8 us here.
 __global__ __launch_bounds__(256) void k_det_setup(DescChunk c, FrameDesc* table, DetArgsIn in, DetArgs* out,
                                                    uint32_t* counters) {
     const int t = threadIdx.x;
@@ -1812,13 +1815,9 @@ __global__ __launch_bounds__(256) void k_det_setup(DescChunk c, FrameDesc* table
         out->minarea = in.minarea;
         out->want_seg = in.want_seg;
     }
-    // every lane forms the same sum in the same order
-    double sum = 0.0;
     const int n = in.kw * in.kh;
-    for (int i = 0; i < n; ++i) sum += (double)in.kraw[i];
-    const double norm = (sum != 0.0) ? sum : 1.0;
     for (int i = t; i < kMaxK * kMaxK; i += 256) {
-        const double v = (i < n) ? (double)in.kraw[i] / norm : 0.0;
+        const double v = (i < n) ? (double)in.kraw[i] / in.norm : 0.0;
         out->kdd[i] = v;
         out->kd[i] = (float)v;
     }
@@ -1830,13 +1829,17 @@ __global__ __launch_bounds__(256) void k_det_setup(DescChunk c, FrameDesc* table
     }
 }
 
+// (4 KB of kernel arguments: the taps of a reference and five 13 x 13 modes and
+// one frame's map descriptor go in one launch)
+constexpr int kWordChunk = 1020;
 struct WordChunk {
     uint32_t n;
-    uint32_t w[960];
+    uint32_t w[kWordChunk];
 };
-__global__ void k_write_words(uint32_t* dst, WordChunk c) {
-    for (uint32_t i = threadIdx.x; i < c.n; i += blockDim.x) dst[i] = c.w[i];
+__global__ __launch_bounds__(1024) void k_write_words(uint32_t* dst, WordChunk c) {
+    if (threadIdx.x < c.n) dst[threadIdx.x] = c.w[threadIdx.x];
 }
+static_assert(sizeof(WordChunk) + 8 <= 4096 && kWordChunk <= 1024, "one launch's arguments, one word per thread");
 
 void launch_write_bytes(void* dst, const void* src, size_t bytes, hipStream_t s) {
     const uint32_t* w = (const uint32_t*)src;
@@ -1844,9 +1847,9 @@ void launch_write_bytes(void* dst, const void* src, size_t bytes, hipStream_t s)
     uint32_t* d = (uint32_t*)dst;
     while (nw > 0) {
         WordChunk c;
-        c.n = (uint32_t)std::min<size_t>(nw, 960);
+        c.n = (uint32_t)std::min<size_t>(nw, kWordChunk);
         for (uint32_t i = 0; i < c.n; ++i) c.w[i] = w[i];
-        k_write_words<<<1, 256, 0, s>>>(d, c);
+        k_write_words<<<1, 1024, 0, s>>>(d, c);
         w += c.n;
         d += c.n;
         nw -= c.n;

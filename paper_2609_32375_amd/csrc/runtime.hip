@@ -287,7 +287,7 @@ void plan_fixed(int32_t nframes, Plan& P) {
     P.o_bitmap = sec(128 * (size_t)P.total_blocks);
     P.o_blockcnt = sec(sizeof(uint32_t) * (P.total_blocks + 1));
     P.o_chunks = sec(sizeof(uint32_t) * (ceil_div(P.total_blocks, kScanChunk) + 1));
-    P.o_psf = sec(sizeof(PsfArgs) + sizeof(PsfFrame) * nframes);
+    P.o_psf = sec(sizeof(double) * kPsfTaps + sizeof(PsfFrame) * nframes);
     P.o_spline = o;
     for (int f = 0; f < nframes; ++f) {
         FramePlan& F = P.fr[f];
@@ -415,8 +415,8 @@ bool separable_factors(const gp_det_params* dp, double* kx, double* ky) {
     return true;
 }
 
-// filter arguments of a detection call (the dense kernel is normalised on the
-// device; a rank-one kernel also gets its normalised factors)
+// filter arguments of a detection call (a rank-one kernel also gets its
+// normalised factors)
 DetArgsIn det_in(const gp_det_params* dp) {
     DetArgsIn in{};
     in.kw = dp->kw;
@@ -426,7 +426,12 @@ DetArgsIn det_in(const gp_det_params* dp) {
     in.sat = dp->sat_level;
     in.minarea = dp->minarea;
     in.want_seg = 0;
-    for (int i = 0; i < dp->kw * dp->kh; ++i) in.kraw[i] = dp->kernel[i];
+    double sum = 0.0;
+    for (int i = 0; i < dp->kw * dp->kh; ++i) {
+        in.kraw[i] = dp->kernel[i];
+        sum += (double)dp->kernel[i];
+    }
+    in.norm = (sum != 0.0) ? sum : 1.0;
     double kx[kMaxK] = {0}, ky[kMaxK] = {0};
     in.separable = separable_factors(dp, kx, ky) ? 1 : 0;
     for (int i = 0; i < kMaxK; ++i) {
@@ -922,6 +927,7 @@ static gp_status peaks_run(gp_ctx* ctx, const gp_frame* frames, int32_t nframes,
         in.sat = dp->sat_level;
         in.minarea = 1;
         in.kraw[(kh / 2) * kw + kw / 2] = 1.0f;
+        in.norm = 1.0;
     } else {
         in = det_in(dp);
     }
@@ -944,36 +950,34 @@ static gp_status peaks_run(gp_ctx* ctx, const gp_frame* frames, int32_t nframes,
     wk.total_blocks = (int32_t)P.total_blocks;
     // tiles an XCD holds in flight (two peak workgroups per CU)
     wk.ahead = std::max(0, ctx->cus / kXcds) * 2;
-    PsfArgs* pargs = nullptr;
+    void* taps = nullptr;
     PsfFrame* pframes = nullptr;
     {
         ProfScope ps(ctx, s, "setup");
         launch_det_setup(tail, (FrameDesc*)(W + P.o_desc), in, dargs, wk.counters, s);
         if (psf) {
-            // the model's header and taps (FP32 as given and their exact FP64
-            // values), then the frames' map descriptors
-            pargs = (PsfArgs*)(W + P.o_psf);
-            pframes = (PsfFrame*)(W + P.o_psf + sizeof(PsfArgs));
-            // taps as [column][row][mode], modes padded to kMaxModes + 1
-            const int nt = kw * kh * (kMaxModes + 1);
-            std::vector<float> tf(nt, 0.0f);
-            std::vector<double> td(nt, 0.0);
+            // the frames' map descriptors and after them the taps in the
+            // working precision, [column][row][mode] with the modes padded
+            // to the kernel variant's, as one block
+            const int ns = psf_modes(psf->nmodes), nt = kw * kh * ns;
+            const size_t real = f64 ? 8 : 4;
+            std::vector<char> blob(sizeof(PsfFrame) * nframes + real * nt, 0);
+            PsfFrame* pf = (PsfFrame*)blob.data();
+            for (int f = 0; f < nframes; ++f)
+                pf[f] = psf->nmodes > 0 ? PsfFrame{psf->maps[f].data, psf->maps[f].pitch, psf->maps[f].plane}
+                                        : PsfFrame{nullptr, 0, 0};
+            char* t = blob.data() + sizeof(PsfFrame) * nframes;
             for (int m = 0; m <= psf->nmodes; ++m)
                 for (int a = 0; a < kh; ++a)
                     for (int b = 0; b < kw; ++b) {
                         const float v = psf->kernels[(m * kh + a) * kw + b];
-                        tf[(b * kh + a) * (kMaxModes + 1) + m] = v;
-                        td[(b * kh + a) * (kMaxModes + 1) + m] = (double)v;
+                        const int i = (b * kh + a) * ns + m;
+                        if (f64) ((double*)t)[i] = (double)v;
+                        else ((float*)t)[i] = v;
                     }
-            const int32_t hdr[4] = {psf->nmodes, psf->bin, kw, kh};
-            launch_write_bytes(pargs, hdr, sizeof(hdr), s);
-            launch_write_bytes(pargs->taps, tf.data(), tf.size() * 4, s);
-            launch_write_bytes(pargs->tapsd, td.data(), td.size() * 8, s);
-            std::vector<PsfFrame> pf(nframes);
-            for (int f = 0; f < nframes; ++f)
-                pf[f] = psf->nmodes > 0 ? PsfFrame{psf->maps[f].data, psf->maps[f].pitch, psf->maps[f].plane}
-                                        : PsfFrame{nullptr, 0, 0};
-            launch_write_bytes(pframes, pf.data(), pf.size() * sizeof(PsfFrame), s);
+            pframes = (PsfFrame*)(W + P.o_psf);
+            taps = W + P.o_psf + sizeof(PsfFrame) * nframes;
+            launch_write_bytes(pframes, blob.data(), blob.size(), s);
         }
     }
     HIP_TRY(hipGetLastError());
@@ -981,8 +985,8 @@ static gp_status peaks_run(gp_ctx* ctx, const gp_frame* frames, int32_t nframes,
               cat->pmin, cat->flux, cat->x, cat->y, cat->x2, cat->y2, cat->xy, cat->peak, cat->flags};
     {
         ProfScope ps(ctx, s, psf ? "peaks_psf" : "peaks");
-        launch_peaks(wk, dargs, co, comp_status, f64, pp->sep, pp->cwin, kw, kh, ctx->cus * 4, pargs, pframes,
-                     psf ? psf->nmodes : 0, bp->mesh_w, std::max(0, ctx->cus / kXcds), s);
+        launch_peaks(wk, dargs, co, comp_status, f64, pp->sep, pp->cwin, kw, kh, ctx->cus * 4, taps, pframes,
+                     psf ? psf->nmodes : 0, psf ? psf->bin : 1, bp->mesh_w, std::max(0, ctx->cus / kXcds), s);
     }
     HIP_TRY(hipGetLastError());
     return GP_OK;
