@@ -6,12 +6,12 @@
 //                 wavefront.  Every sum is exact, so a mesh gives bit-identical
 //                 results wherever it is scheduled.
 //  k_spline_y_pcr, k_spline_x_pcr (and the *_blk variants)
-//                 grids of at most 127 knots per axis: the f x f median over
+//                 grids of at most 511 knots per axis: the f x f median over
 //                 the mesh grid (truncated at the edges) and the natural cubic
 //                 splines through the mesh centres, one wavefront per spline up
-//                 to 63 knots on the solved axis, one 128-thread workgroup up to
-//                 127, solved in FP64 by parallel cyclic reduction and turned
-//                 into bicubic pieces per mesh cell.
+//                 to 63 knots on the solved axis, one workgroup with more
+//                 threads than knots beyond, solved in FP64 by parallel cyclic
+//                 reduction and turned into bicubic pieces per mesh cell.
 //  k_grid_filter, k_spline_*
 //                 the same for larger grids: one thread per mesh for the
 //                 filter, one per spline for the FP64 Thomas solve.
@@ -948,23 +948,26 @@ __device__ __forceinline__ void pcr_piece(int n, int lane, double f, double m, d
 }
 
 // Grids of 64 to kPcrBlkMax knots on the solved axis: the same reduction over
-// a workgroup of 128 threads (thread = knot), seven rounds, the rows exchanged
-// through LDS (s*: 128 doubles each)
-constexpr int kPcrBlkMax = 127;
+// a workgroup of NT = 128, 256 or 512 threads (thread = knot), seven to nine
+// rounds, the rows exchanged through LDS (s*: NT doubles each).  More knots go
+// to the serial solve: its columns fill few lanes and each is one chain of
+// divisions (16 frames of up to 150 x 100 knots: 219 us with the filter, 52 us here).
+constexpr int kPcrBlkMax = 511;
 
+template <int NT>
 __device__ double pcr_second_derivs_blk(int n, int k, double t0, double t1, double t2, double fm, double f,
                                         double fp, double* sa, double* sc, double* sd, double* sr) {
     const bool row = k >= 1 && k <= n - 2;
     const double h0 = t1 - t0, h1 = t2 - t1;
     double a = row ? h0 : 0.0, b = row ? 2.0 * (h0 + h1) : 1.0, c = row ? h1 : 0.0;
     double d = row ? 6.0 * ((fp - f) / h1 - (f - fm) / h0) : 0.0;
-    for (int st = 1; st < 128; st <<= 1) {
+    for (int st = 1; st < NT; st <<= 1) {
         sa[k] = a;
         sc[k] = c;
         sd[k] = d;
         sr[k] = 1.0 / b;
         __syncthreads();
-        const bool okl = k >= st, okh = k + st < 128;
+        const bool okl = k >= st, okh = k + st < NT;
         const double al = okl ? sa[k - st] : 0.0, cl = okl ? sc[k - st] : 0.0, dl = okl ? sd[k - st] : 0.0;
         const double rl = okl ? sr[k - st] : 1.0;
         const double ah = okh ? sa[k + st] : 0.0, ch = okh ? sc[k + st] : 0.0, dh = okh ? sd[k + st] : 0.0;
@@ -981,9 +984,9 @@ __device__ double pcr_second_derivs_blk(int n, int k, double t0, double t1, doub
 
 // y splines (and the mesh filter when F > 0), one workgroup per (quantity,
 // mesh column); blockIdx.y = frame
-template <int F>
-__global__ __launch_bounds__(128) void k_spline_y_pcr_blk(const FrameDesc* __restrict__ desc) {
-    __shared__ double sa[128], sc[128], sd[128], sr[128];
+template <int F, int NT>
+__global__ __launch_bounds__(NT) void k_spline_y_pcr_blk(const FrameDesc* __restrict__ desc) {
+    __shared__ double sa[NT], sc[NT], sd[NT], sr[NT];
     const FrameDesc& d = desc[blockIdx.y];
     const int nx = d.nx, ny = d.ny, t = threadIdx.x;
     const int g = blockIdx.x;
@@ -1012,9 +1015,9 @@ __global__ __launch_bounds__(128) void k_spline_y_pcr_blk(const FrameDesc* __res
     const double t2 = knot_at(min(k + 1, ny - 1), d.H, d.mh);
     sd[t] = f;
     __syncthreads();
-    const double fm = sd[max(t - 1, 0)], fp = sd[min(t + 1, 127)];
+    const double fm = sd[max(t - 1, 0)], fp = sd[min(t + 1, NT - 1)];
     __syncthreads();
-    const double m = pcr_second_derivs_blk(ny, t, t0, t1, t2, fm, f, fp, sa, sc, sd, sr);
+    const double m = pcr_second_derivs_blk<NT>(ny, t, t0, t1, t2, fm, f, fp, sa, sc, sd, sr);
     sa[t] = f;
     sc[t] = m;
     sd[t] = t2 - t1;
@@ -1032,8 +1035,9 @@ __global__ __launch_bounds__(128) void k_spline_y_pcr_blk(const FrameDesc* __res
 }
 
 // x splines, one workgroup per (quantity, y piece, power of u); blockIdx.y = frame
-__global__ __launch_bounds__(128) void k_spline_x_pcr_blk(const FrameDesc* __restrict__ desc) {
-    __shared__ double sa[128], sc[128], sd[128], sr[128];
+template <int NT>
+__global__ __launch_bounds__(NT) void k_spline_x_pcr_blk(const FrameDesc* __restrict__ desc) {
+    __shared__ double sa[NT], sc[NT], sd[NT], sr[NT];
     const FrameDesc& d = desc[blockIdx.y];
     const int nx = d.nx, ny = d.ny, t = threadIdx.x;
     const int g = blockIdx.x;
@@ -1045,9 +1049,9 @@ __global__ __launch_bounds__(128) void k_spline_x_pcr_blk(const FrameDesc* __res
     const double t2 = knot_at(min(k + 1, nx - 1), d.W, d.mw);
     sd[t] = f;
     __syncthreads();
-    const double fm = sd[max(t - 1, 0)], fp = sd[min(t + 1, 127)];
+    const double fm = sd[max(t - 1, 0)], fp = sd[min(t + 1, NT - 1)];
     __syncthreads();
-    const double m = pcr_second_derivs_blk(nx, t, t0, t1, t2, fm, f, fp, sa, sc, sd, sr);
+    const double m = pcr_second_derivs_blk<NT>(nx, t, t0, t1, t2, fm, f, fp, sa, sc, sd, sr);
     sa[t] = f;
     sc[t] = m;
     sd[t] = t2 - t1;
@@ -1248,8 +1252,19 @@ bool filter_spline_fits(int max_nx, int max_ny, int fsize) {
     return max_nx <= kPcrBlkMax && max_ny <= kPcrBlkMax && fsize <= 5;
 }
 
+template <int NT>
+static void launch_y_blk(const FrameDesc* desc, int nframes, int max_nx, int fsize, hipStream_t s) {
+    const dim3 gy(2 * max_nx, nframes);
+    switch (fsize) {
+        case 0: k_spline_y_pcr_blk<0, NT><<<gy, NT, 0, s>>>(desc); break;
+        case 1: k_spline_y_pcr_blk<1, NT><<<gy, NT, 0, s>>>(desc); break;
+        case 3: k_spline_y_pcr_blk<3, NT><<<gy, NT, 0, s>>>(desc); break;
+        default: k_spline_y_pcr_blk<5, NT><<<gy, NT, 0, s>>>(desc); break;
+    }
+}
+
 // each axis by its own knot count: up to kPcrMax one wavefront per spline,
-// up to kPcrBlkMax one 128-thread workgroup
+// up to kPcrBlkMax the smallest workgroup with more threads than knots
 void launch_filter_spline(const FrameDesc* desc, int nframes, int max_nx, int max_ny, int fsize, hipStream_t s) {
     if (max_ny <= kPcrMax) {
         const dim3 gy((2 * max_nx + 3) / 4, nframes);
@@ -1259,17 +1274,18 @@ void launch_filter_spline(const FrameDesc* desc, int nframes, int max_nx, int ma
             case 3: k_spline_y_pcr<3><<<gy, 256, 0, s>>>(desc); break;
             default: k_spline_y_pcr<5><<<gy, 256, 0, s>>>(desc); break;
         }
+    } else if (max_ny < 128) {
+        launch_y_blk<128>(desc, nframes, max_nx, fsize, s);
+    } else if (max_ny < 256) {
+        launch_y_blk<256>(desc, nframes, max_nx, fsize, s);
     } else {
-        const dim3 gy(2 * max_nx, nframes);
-        switch (fsize) {
-            case 0: k_spline_y_pcr_blk<0><<<gy, 128, 0, s>>>(desc); break;
-            case 1: k_spline_y_pcr_blk<1><<<gy, 128, 0, s>>>(desc); break;
-            case 3: k_spline_y_pcr_blk<3><<<gy, 128, 0, s>>>(desc); break;
-            default: k_spline_y_pcr_blk<5><<<gy, 128, 0, s>>>(desc); break;
-        }
+        launch_y_blk<512>(desc, nframes, max_nx, fsize, s);
     }
+    const dim3 gx(8 * (max_ny + 1), nframes);
     if (max_nx <= kPcrMax) k_spline_x_pcr<<<dim3(2 * (max_ny + 1), nframes), 256, 0, s>>>(desc);
-    else k_spline_x_pcr_blk<<<dim3(8 * (max_ny + 1), nframes), 128, 0, s>>>(desc);
+    else if (max_nx < 128) k_spline_x_pcr_blk<128><<<gx, 128, 0, s>>>(desc);
+    else if (max_nx < 256) k_spline_x_pcr_blk<256><<<gx, 256, 0, s>>>(desc);
+    else k_spline_x_pcr_blk<512><<<gx, 512, 0, s>>>(desc);
 }
 
 void launch_spline(const FrameDesc* desc, int nframes, int max_nx, int max_ny, hipStream_t s) {

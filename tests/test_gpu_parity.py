@@ -265,6 +265,14 @@ def test_background_maps_match_oracle_spline(P, shape):
     ph.close()
 
 
+@pytest.mark.parametrize("nx,ny", [(128, 3), (3, 128), (255, 2), (2, 255), (256, 130), (130, 257), (511, 5), (5, 511),
+                                   (512, 3), (3, 512)])
+def test_background_maps_of_wide_grids(P, nx, ny):
+    """Both sides of each workgroup size of the cyclic reduction (127, 255 and
+    511 knots; 512 on the serial solve), the last mesh a partial one."""
+    test_background_maps_match_oracle_spline(P, (16 * nx - 3, 16 * ny - 5, 16, 16))
+
+
 def test_constant_sky_gives_constant_background(P):
     img = np.full((150, 220), 812.5, np.float32)
     p = _params("c1", mesh_w=32, mesh_h=32)
