@@ -63,6 +63,7 @@ struct DetShared {
         LocalRec rec[kLocalRecs];
     } u2;
     uint64_t rowmask[kTile];
+    uint32_t satmask[2 * kTile];   // raw pixels at or above the saturation level, a bit each
     int32_t rowoff[kTile + 1];
     int32_t misc[4];
     int32_t colp[REG];      // x piece of each region column (relative to the first)
@@ -229,6 +230,15 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
     const int es = u16 ? 2 : 4;
     const bool inner = kSep && x0 >= rx && y0 >= ry && x0 + tw + rx <= d.W && y0 + th + ry <= d.H &&
                        (int64_t)RH * d.pitch * es < ((int64_t)1 << 31);
+    const float sat = pa->sat;
+    const bool has_sat = sat < INFINITY;
+    if (has_sat && tid < 2 * kTile) sh.satmask[tid] = 0u;   // (set after the next barrier)
+    // v: the raw value at region row r, column c
+    auto note_sat = [&](float v, int r, int c) __attribute__((always_inline)) {
+        const int ly = r - ry, lx = c - rx;
+        if (v >= sat && ly >= 0 && ly < th && lx >= 0 && lx < tw)
+            atomicOr(&sh.satmask[2 * ly + (lx >> 5)], 1u << (lx & 31));
+    };
     auto halo_col = [&](int c) { return c < kR ? c : c + kTile; };
     if (inner) {
         const int64_t o0 = ((int64_t)(y0 - ry) * d.pitch + (x0 - rx)) * es;
@@ -312,6 +322,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
         for (int q = 0; q < CR; ++q) {
             const int r = wv + 4 * q;
             if (r < RH) sh.u2.ms[r * MS + c] = eval_M(sh.u1.tab[r * NIX + pc], sx, (Real)pv[q]);
+            if (has_sat && __ballot(pv[q] >= sat) != 0ull) note_sat(pv[q], r, c);
         }
 #pragma unroll
         for (int i = 0; i < HL; ++i) {
@@ -325,8 +336,10 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
         for (int i = 0; i < NL; ++i) {
             const int e = tid + 256 * i;
             const int r = e / REG, c = e - r * REG;
-            if (r < RH && c < RW)
+            if (r < RH && c < RW) {
                 sh.u2.ms[r * MS + c] = eval_M(sh.u1.tab[r * NIX + sh.colp[c]], sh.colsx[c], (Real)pv[i]);
+                if (has_sat) note_sat(pv[i], r, c);
+            }
         }
     }
     // thresholds t R of the 16 pixels this lane owns: column `lane`, rows 16 wv ..
@@ -334,10 +347,8 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
     Real To[16];
     {
         const Real ts = (Real)pa->thresh;
-        const int gx = colok ? x0 + lane : x0;
-        const int ix = piece_of(gx, d.W, d.mw);
-        const int pc = ix - ixlo;
-        const Real sx = (Real)((double)gx - piece_ref(ix, d.W, d.mw));
+        const int pc = sh.colp[rx + (colok ? lane : 0)];
+        const Real sx = sh.colsx[rx + (colok ? lane : 0)];
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             const int ly = 16 * wv + k;
@@ -387,18 +398,18 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
             Fo[k] = acc;
         }
     } else {
+        // one tap at a time for the lane's 16 rows (values past the region
+        // are read but their sums not used); each sum runs over the taps in
+        // order
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int ly = 16 * wv + k;
-            Real acc = 0;
-            if (colok && ly < th) {
-                for (int a = 0; a < kh; ++a) {
-                    const Real* mr = &sh.u2.ms[(ly + a) * MS + lane];
-                    for (int b = 0; b < kw; ++b)
-                        acc = fma(kDbl ? (Real)pa->kdd[a * kw + b] : (Real)pa->kd[a * kw + b], mr[b], acc);
-                }
+        for (int k = 0; k < 16; ++k) Fo[k] = 0;
+        for (int a = 0; a < kh; ++a) {
+            const Real* mr = &sh.u2.ms[(16 * wv + a) * MS + lane];
+            for (int b = 0; b < kw; ++b) {
+                const Real t = kDbl ? (Real)pa->kdd[a * kw + b] : (Real)pa->kd[a * kw + b];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) Fo[k] = fma(t, mr[k * MS + b], Fo[k]);
             }
-            Fo[k] = acc;
         }
     }
     uint32_t mbits = 0u;
@@ -420,104 +431,106 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
         return;
     }
     // 4. connected components inside the tile.  A tile row is one wavefront
-    //    (lane = column), so each row's mask is one ballot.  Pixels start
-    //    labelled with the first pixel of their horizontal run; runs of
-    //    adjacent rows are then united once per touching pair, in an LDS
-    //    union-find whose roots are the smallest raster index of each
-    //    component.
-    int32_t* lab = sh.u2.lab;      // M is held in VGPRs from here on
-    int16_t* comp = sh.u1.comp;
+    //    (lane = column), so each row's mask is one ballot, and most rows of
+    //    most tiles hold no detection: every step skips them.  Each wavefront
+    //    goes down its 16 rows: a horizontal run takes the smallest label
+    //    of the runs it touches in the row above (its own first pixel if it
+    //    touches none) through an LDS minimum, and where it touches runs of
+    //    different labels these are united in an LDS union-find whose roots
+    //    are the smallest raster index of each component.  The labels so
+    //    found are roots or a step away, where uniting every touching pair
+    //    of runs left chains as long as a component is high (12300^2
+    //    crowded: 69k of 115k cycles per tile; now 14k).
+    int32_t* lab = sh.u2.lab;      // M is held in VGPRs from here on; entries of runs' first pixels
+    int16_t* comp = sh.u1.comp;    // each pixel's label, later its piece id
     const uint64_t below = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));   // lanes < lane
-    // the wavefront's own row masks stay in registers; the row above its
-    // first row is read from LDS
-    uint64_t rm[16];
+    const bool conn8 = pa->conn == 8;
+    // the wavefront's 16 row masks, row k in lane k, and its rows that hold a
+    // detection; the row above its first row is read from LDS
+    auto set_row = [&](uint32_t v, int k, uint32_t old) { return lane == k ? v : old; };
+    uint32_t mlo = 0u, mhi = 0u;
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-        rm[k] = __ballot((mbits >> k) & 1u);
-        if (lane == 0) sh.rowmask[16 * wv + k] = rm[k];
+        const uint64_t m = __ballot((mbits >> k) & 1u);
+        mlo = set_row((uint32_t)m, k, mlo);
+        mhi = set_row((uint32_t)(m >> 32), k, mhi);
     }
-    // (the vertical pass that read the M region lab now occupies was
-    // finished by every wavefront before the barrier above)
+    const uint32_t rows = (uint32_t)__ballot((mlo | mhi) != 0u);
+    auto row_mask = [&](int k) {
+        return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mlo, k) |
+               ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mhi, k) << 32);
+    };
+    if (lane < 16) sh.rowmask[16 * wv + lane] = (uint64_t)mlo | ((uint64_t)mhi << 32);
+    // Where a run of mask m touches the runs of the mask mu above, as bit
+    // masks over the columns (runs start where m rises, end where it falls):
+    //   vertical, at the first column of each overlap:    m & mu & (start | ~(mu << 1))
+    //   8-connectivity, up-left of a run start:           start & (mu << 1)
+    //   8-connectivity, up-right of a run end, none above: end & (mu >> 1) & ~mu
+    auto touching = [&](uint64_t m, uint64_t mu, uint64_t (&cm)[3]) {
+        const uint64_t start = m & ~(m << 1), end = m & ~(m >> 1);
+        cm[0] = m & mu & (start | ~(mu << 1));
+        cm[1] = conn8 ? (start & (mu << 1)) : 0ull;
+        cm[2] = conn8 ? (end & (mu >> 1) & ~mu) : 0ull;
+    };
+    // one wavefront's LDS operations run in order: only the compiler has to
+    // keep theirs
+    auto lds_order = []() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    {
+        int prev = -1;          // label of the pixel above (-1: none)
+        uint64_t mu = 0ull;     // mask of the row above, inside the strip
+        int last = -2;
+        for (uint32_t rr = rows; rr != 0u; rr &= rr - 1u) {
+            const int k = __builtin_ctz(rr), ly = 16 * wv + k;
+            const uint64_t m = row_mask(k);
+            if (k != last + 1) mu = 0ull;
+            const bool on = (m >> lane) & 1ull;
+            const uint64_t zb = ~m & below;
+            const int p0 = ly * kTile + (zb ? 64 - __clzll(zb) : 0);   // the run's first pixel
+            const int p = ly * kTile + lane;
+            if (on && p == p0) lds_st(&lab[p0], p0);
+            int u[3] = {prev, -1, -1};
+            uint64_t cm[3] = {0ull, 0ull, 0ull};
+            if (mu != 0ull) {
+                touching(m, mu, cm);
+                if (cm[1] != 0ull) u[1] = __shfl(prev, max(lane - 1, 0));
+                if (cm[2] != 0ull) u[2] = __shfl(prev, min(lane + 1, 63));
+                lds_order();
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int ly = 16 * wv + k;
-        const int p = ly * kTile + lane;
-        int v = -1;
-        if ((mbits >> k) & 1u) {
-            const uint64_t zb = ~rm[k] & below;
-            const int s0 = zb ? 64 - __clzll(zb) : 0;
-            v = ly * kTile + s0;
+                for (int t = 0; t < 3; ++t)
+                    if ((cm[t] >> lane) & 1ull) atomicMin(&lab[p0], u[t]);
+            }
+            lds_order();
+            const int l = on ? lds_ld(&lab[p0]) : -1;
+            if (on) comp[p] = (int16_t)l;
+            // runs of other labels that this run joins
+            for (int t = 0; t < 3; ++t) {
+                const int ut = t == 0 ? u[0] : t == 1 ? u[1] : u[2];
+                const uint64_t ct = t == 0 ? cm[0] : t == 1 ? cm[1] : cm[2];
+                const bool join = ((ct >> lane) & 1ull) && ut != l;
+                if (__ballot(join) != 0ull && join) lds_union(lab, ut, l);
+            }
+            prev = l;
+            mu = m;
+            last = k;
         }
-        lab[p] = v;
     }
     __syncthreads();
-    const bool conn8 = pa->conn == 8;
-    // Union pairs (pixel, pixel above) for every pair of touching runs, one
-    // at the first column of their overlap.  Each wavefront lists its rows'
-    // pairs in its own share of the (now free) row-cubic region, then the
-    // whole block applies them concurrently; a full list falls back to
-    // uniting at once.  Pixel indices are < 4096: a pair packs into 24 bits.
-    constexpr int PCAP = (int)(sizeof(typename DetShared<Real, REG, NIX>::U1) / sizeof(uint32_t)) / 4;
-    uint32_t* plist = reinterpret_cast<uint32_t*>(&sh.u1) + wv * PCAP;
-    int npair = 0;
-    uint64_t mtop = 0ull;
-    if (wv > 0) {
+    // the first row of a strip against the last row of the strip above
+    if (wv > 0 && (rows & 1u)) {
         const uint64_t t = sh.rowmask[16 * wv - 1];
         // (readfirstlane returns int: widen through uint32_t, not by sign)
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)t);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(t >> 32));
-        mtop = (uint64_t)lo | ((uint64_t)hi << 32);
-    }
-    // The pairs of a row are bit masks over its columns, computed on the
-    // scalar unit from the row's mask m and the mask above mu (runs start
-    // where m rises, end where it falls):
-    //   vertical link at the first column of each overlap: m & mu & (start | ~(mu << 1))
-    //   8-connectivity, up-left of a run start:           start & (mu << 1)
-    //   8-connectivity, up-right of a run end, none above: end & (mu >> 1) & ~mu
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int ly = 16 * wv + k;
-        const uint64_t m = rm[k], mu = (k > 0) ? rm[k - 1] : mtop;
-        const uint64_t start = m & ~(m << 1), end = m & ~(m >> 1);
-        const uint64_t cm[3] = {m & mu & (start | ~(mu << 1)), conn8 ? (start & (mu << 1)) : 0ull,
-                                conn8 ? (end & (mu >> 1) & ~mu) : 0ull};
-        if ((cm[0] | cm[1] | cm[2]) == 0ull) continue;
-        const int p = ly * kTile + lane;
-        const int qq[3] = {p - kTile, p - kTile - 1, p - kTile + 1};
-#pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            const uint64_t bm = cm[t];
-            if (bm == 0ull) continue;
-            const int pos = npair + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bm >> 32),
-                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)bm, 0u));
-            if ((bm >> lane) & 1ull) {
-                if (pos < PCAP) plist[pos] = ((uint32_t)p << 12) | (uint32_t)qq[t];
-                else lds_union(lab, p, qq[t]);
-            }
-            npair += __popcll(bm);
-        }
-    }
-    if (lane == 0) sh.misc[wv] = min(npair, PCAP);
-    __syncthreads();
-    {
-        const int n0 = sh.misc[0], n1 = sh.misc[1], n2 = sh.misc[2], n3 = sh.misc[3];
-        const int tot = n0 + n1 + n2 + n3;
-        for (int i = tid; i < tot; i += 256) {
-            int w = 0, o = i;
-            if (o >= n0) {
-                o -= n0;
-                w = 1;
-                if (o >= n1) {
-                    o -= n1;
-                    w = 2;
-                    if (o >= n2) {
-                        o -= n2;
-                        w = 3;
-                    }
-                }
-            }
-            const uint32_t e = reinterpret_cast<const uint32_t*>(&sh.u1)[w * PCAP + o];
-            lds_union(lab, (int)(e >> 12), (int)(e & 4095u));
+        uint64_t cm[3];
+        touching(row_mask(0), (uint64_t)lo | ((uint64_t)hi << 32), cm);
+        const int p = 16 * wv * kTile + lane;
+        for (int t3 = 0; t3 < 3; ++t3) {
+            const uint64_t ct = t3 == 0 ? cm[0] : t3 == 1 ? cm[1] : cm[2];
+            if ((ct >> lane) & 1ull) lds_union(lab, comp[p], comp[p - kTile + (t3 == 0 ? 0 : t3 == 1 ? -1 : 1)]);
         }
     }
     __syncthreads();
@@ -526,11 +539,15 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
     // of them) and nothing is written back: each root stays in a register.
     int rt[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) rt[k] = ((mbits >> k) & 1u) ? lab[(16 * wv + k) * kTile + lane] : -1;
+    for (int k = 0; k < 16; ++k) {
+        rt[k] = -1;
+        if (((rows >> k) & 1u) && ((mbits >> k) & 1u)) rt[k] = comp[(16 * wv + k) * kTile + lane];
+    }
     for (;;) {
         bool more = false;
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
+            if (!((rows >> k) & 1u)) continue;
             const int q = rt[k];
             const int g = lab[q & (kTile * kTile - 1)];
             if (q >= 0 && g != q) {
@@ -543,16 +560,23 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
     // roots in raster order: per-row ballots (kept in rowmask, whose union
     // masks are no longer read), then a prefix over the 64 rows
     uint64_t rb[16];
+    {
+        uint32_t lo = 0u, hi = 0u;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int p = (16 * wv + k) * kTile + lane;
-        rb[k] = __ballot(((mbits >> k) & 1u) && rt[k] == p);
-        if (lane == 0) {
-            sh.rowmask[16 * wv + k] = rb[k];
-            sh.rowoff[16 * wv + k + 1] = __popcll(rb[k]);
+        for (int k = 0; k < 16; ++k) {
+            rb[k] = 0ull;
+            if (!((rows >> k) & 1u)) continue;
+            rb[k] = __ballot(rt[k] == (16 * wv + k) * kTile + lane);
+            lo = set_row((uint32_t)rb[k], k, lo);
+            hi = set_row((uint32_t)(rb[k] >> 32), k, hi);
+        }
+        if (lane < 16) {
+            sh.rowmask[16 * wv + lane] = (uint64_t)lo | ((uint64_t)hi << 32);
+            sh.rowoff[16 * wv + lane + 1] = __popc(lo) + __popc(hi);
         }
     }
     __syncthreads();
+    int taken = 0;   // (thread 0: the tile's first record)
     if (wv == 0) {
         // rows' root counts -> exclusive offsets (one wavefront, lane = row)
         const int cnt = sh.rowoff[lane + 1];
@@ -564,29 +588,35 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
         }
         sh.rowoff[lane + 1] = incl;
         if (lane == 0) sh.rowoff[0] = 0;
+        // the tile's records: asked for now, waited for once the pieces are numbered
+        const int n = __builtin_amdgcn_readlane(incl, 63);
+        if (lane == 0) taken = (int)atomicAdd(&wk.counters[0], (uint32_t)n);
     }
     __syncthreads();
     const int ncomp = sh.rowoff[kTile];
-    // piece id of a pixel = rank of its root among the tile's roots
+    // piece id of a pixel = rank of its root among the tile's roots; the ids
+    // of the tile's first and last column, row k in lane k, for the merge
     int co[16];
+    uint32_t cl = ~0u, cr = ~0u;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) co[k] = -1;
-    if (__ballot(mbits != 0u) != 0ull) {   // (no pieces in a wavefront without detections)
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int r = rt[k] & (kTile * kTile - 1);
-            const int ry_ = r >> 6, rx_ = r & 63;
-            const uint64_t lowr = (rx_ == 0) ? 0ull : ((~0ull) >> (64 - rx_));
-            const int c = sh.rowoff[ry_] + __popcll(sh.rowmask[ry_] & lowr);
-            co[k] = ((mbits >> k) & 1u) ? c : -1;
+    for (int k = 0; k < 16; ++k) {
+        co[k] = -1;
+        if (!((rows >> k) & 1u)) continue;
+        const int r = rt[k] & (kTile * kTile - 1);
+        const int ry_ = r >> 6, rx_ = r & 63;
+        const uint64_t lowr = (rx_ == 0) ? 0ull : ((~0ull) >> (64 - rx_));
+        const int c = sh.rowoff[ry_] + __popcll(sh.rowmask[ry_] & lowr);
+        if ((mbits >> k) & 1u) {
+            co[k] = c;
+            comp[(16 * wv + k) * kTile + lane] = (int16_t)c;
         }
+        cl = set_row((uint32_t)__builtin_amdgcn_readlane(co[k], 0), k, cl);
+        cr = set_row((uint32_t)__builtin_amdgcn_readlane(co[k], tw - 1), k, cr);
     }
-#pragma unroll
-    for (int k = 0; k < 16; ++k) comp[(16 * wv + k) * kTile + lane] = (int16_t)co[k];
     // 5. records for the tile's pieces (LDS for the first kLocalRecs, in u2,
     //    now free: M lives in VGPRs)
     if (tid == 0) {
-        int base = (int)atomicAdd(&wk.counters[0], (uint32_t)ncomp);
+        int base = taken;
         if ((int64_t)base + ncomp > (int64_t)wk.rec_cap) {
             atomicOr(&wk.counters[1], 1u);
             base = -2;
@@ -632,16 +662,21 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
         }
     }
     // border labels for the merge, and the per-pixel piece ids
-    int16_t* E = wk.edges + (size_t)gt * 4 * kTile;
-    if (tid < 64) {
-        E[0 * kTile + tid] = (tid < tw) ? comp[0 * kTile + tid] : (int16_t)-1;
-        E[1 * kTile + tid] = (tid < tw) ? comp[(th - 1) * kTile + tid] : (int16_t)-1;
-    } else if (tid < 128) {
-        const int r = tid - 64;
-        E[2 * kTile + r] = (r < th) ? comp[r * kTile + 0] : (int16_t)-1;
-        E[3 * kTile + r] = (r < th) ? comp[r * kTile + tw - 1] : (int16_t)-1;
+    {
+        int16_t* E = wk.edges + (size_t)gt * 4 * kTile;
+        if (wv == 0) E[lane] = (int16_t)co[0];
+        int cb = -1;
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (16 * wv + k == th - 1) cb = co[k];
+        if (wv == (th - 1) >> 4) E[1 * kTile + lane] = (int16_t)cb;
+        if (lane < 16) {
+            E[2 * kTile + 16 * wv + lane] = (int16_t)cl;
+            E[3 * kTile + 16 * wv + lane] = (int16_t)cr;
+        }
     }
     if (seg && colok) {
+#pragma unroll
         for (int k = 0; k < 16; ++k) {
             const int ly = 16 * wv + k;
             if (ly < th) seg[(int64_t)(y0 + ly) * d.W + x0 + lane] = co[k];
@@ -659,32 +694,65 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
             else wk.recs[base + c].pmin = pm;
         }
     }
-    // 6. moments, in two passes over the lane's column runs.  (a) Each run
-    //    adds its exact integer quantities into its piece: pixel-count sums,
-    //    bounding box, peak, max |M|, flags.  (b) Once every run has done so,
-    //    each run adds its M-weighted sums (compensated along the run), every
-    //    term rounded to the piece's quantum for that sum (from its pixel count
-    //    and max |M|): the additions are exact, so the piece's sums do not
-    //    depend on the order in which the runs arrive.
-    //    (A wavefront whose rows hold no detection has no run.)
-    const bool wave_has = __ballot(mbits != 0u) != 0ull;
+    // 6. moments, in two passes over the lane's column runs (vertical
+    //    neighbours of a mask are one piece).  (a) Each run adds its exact
+    //    integer quantities into its piece: pixel-count sums, bounding box,
+    //    peak, max |M|, flags.  (b) Once every run has done so, each run adds
+    //    its M-weighted sums (compensated along the run), every term rounded
+    //    to the piece's quantum for that sum (from its pixel count and max
+    //    |M|): the additions are exact, so the piece's sums do not depend on
+    //    the order in which the runs arrive.  A round takes the next run of
+    //    every lane, usually the only one; rows without a detection are
+    //    skipped, and adding a zero for a row outside a lane's run changes
+    //    none of its sums.  (Flushing wherever a run ends put 34 copies of
+    //    the additions into 94 KB of code, more than the instruction cache
+    //    holds, and ran most of them for a few lanes each.)
     const int gx = x0 + lane;
-    if (wave_has) {
-        const float sat = pa->sat;
-        const bool has_sat = sat < INFINITY;
-        int cur = -1, rcnt = 0, rdy = 0, rdy2 = 0, ry0 = 0, ry1 = 0;
+    struct Run {
+        int k0, len;
+        uint32_t rows;
+    };
+    auto next_run = [](uint32_t& todo) {
+        Run r{0, 0, 0u};
+        if (todo != 0u) {
+            r.k0 = __ffs(todo) - 1;
+            r.len = __ffs(~(todo >> r.k0)) - 1;
+            r.rows = ((1u << r.len) - 1u) << r.k0;
+            todo &= ~r.rows;
+        }
+        return r;
+    };
+    for (uint32_t todo = mbits; __ballot(todo != 0u) != 0ull;) {
+        const Run r = next_run(todo);
         float rpk = -INFINITY, ram = 0.0f;
         uint32_t rfl = 0u;
-        auto flush = [&]() {
-            const int addc[6] = {rcnt, lane * rcnt, rdy, lane * lane * rcnt, rdy2, lane * rdy};
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            if (!((rows >> k) & 1u)) continue;
+            const bool in = (r.rows >> k) & 1u;
+            // (float)|M| of an FP64 M may round down by half an ulp; the
+            // quantum keeps a factor two of headroom over the bound
+            rpk = fmaxf(rpk, in ? (float)Mo[k] : -INFINITY);
+            ram = fmaxf(ram, in ? fabsf((float)Mo[k]) : 0.0f);
+        }
+        if (has_sat)
+            for (int i = 0; i < r.len; ++i)
+                if ((sh.satmask[2 * (16 * wv + r.k0 + i) + (lane >> 5)] >> (lane & 31)) & 1u) rfl |= kFlagSat;
+        if (r.len > 0) {
+            const int n = r.len, ya = 16 * wv + r.k0, yb = ya + n - 1;
+            const int cur = comp[ya * kTile + lane];
+            // sums of 1, y and y^2 over the run
+            const int sy = n * ya + n * (n - 1) / 2;
+            const int syy = n * ya * ya + ya * n * (n - 1) + (n - 1) * n * (2 * n - 1) / 6;
+            const int addc[6] = {n, lane * n, sy, lane * lane * n, syy, lane * sy};
             if (cur < kLocalRecs) {
                 LocalRec& R = sh.u2.rec[cur];
 #pragma unroll
                 for (int z = 0; z < 6; ++z) atomicAdd(&R.c[z], addc[z]);
                 atomicMin(&R.xmin, gx);
                 atomicMax(&R.xmax, gx);
-                atomicMin(&R.ymin, y0 + ry0);
-                atomicMax(&R.ymax, y0 + ry1);
+                atomicMin(&R.ymin, y0 + ya);
+                atomicMax(&R.ymax, y0 + yb);
                 atomicMax(&R.peak, f2ord(rpk));
                 atomicMax(&R.amax, __float_as_uint(ram));
                 if (rfl) atomicOr(&R.flags, rfl);
@@ -694,48 +762,26 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
                 for (int z = 0; z < 6; ++z) unsafeAtomicAdd(&R.s[6 + z], (double)addc[z]);
                 atomicMin(&R.xmin, gx);
                 atomicMax(&R.xmax, gx);
-                atomicMin(&R.ymin, y0 + ry0);
-                atomicMax(&R.ymax, y0 + ry1);
+                atomicMin(&R.ymin, y0 + ya);
+                atomicMax(&R.ymax, y0 + yb);
                 atomicMax(&R.peak, f2ord(rpk));
                 atomicMax(&R.amax, __float_as_uint(ram));
                 if (rfl) atomicOr(&R.flags, rfl);
             }
-            cur = -1;
-            rcnt = rdy = rdy2 = 0;
-            rpk = -INFINITY;
-            ram = 0.0f;
-            rfl = 0u;
-        };
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const bool m = (mbits >> k) & 1u;
-            const int c = co[k];
-            if (cur >= 0 && (!m || c != cur)) flush();
-            if (m) {
-                const int ly = 16 * wv + k;
-                if (cur < 0) {
-                    cur = c;
-                    ry0 = ly;
-                }
-                ry1 = ly;
-                rcnt += 1;
-                rdy += ly;
-                rdy2 += ly * ly;
-                rpk = fmaxf(rpk, (float)Mo[k]);
-                // (float)|M| of an FP64 M may round down by half an ulp; the
-                // quantum keeps a factor two of headroom over the bound
-                ram = fmaxf(ram, fabsf((float)Mo[k]));
-                if (has_sat && load_px(d, gx, y0 + ly) >= sat) rfl |= kFlagSat;
-            }
         }
-        if (cur >= 0) flush();
     }
     __syncthreads();
-    if (wave_has) {
+    for (uint32_t todo = mbits; __ballot(todo != 0u) != 0ull;) {
+        const Run r = next_run(todo);
         RunAcc<Real> run;
         run.reset();
-        int cur = -1;
-        auto flush = [&]() {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            if (!((rows >> k) & 1u)) continue;
+            run.add(((r.rows >> k) & 1u) ? Mo[k] : (Real)0, (Real)(16 * wv + k));
+        }
+        if (r.len > 0) {
+            const int cur = comp[(16 * wv + r.k0) * kTile + lane];
             const bool loc = cur < kLocalRecs;
             double npix, amax;
             if (loc) {
@@ -763,20 +809,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
 #pragma unroll
                 for (int z = 0; z < 6; ++z) unsafeAtomicAdd(&R.s[z], add[z]);
             }
-            run.reset();
-            cur = -1;
-        };
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const bool m = (mbits >> k) & 1u;
-            const int c = co[k];
-            if (cur >= 0 && (!m || c != cur)) flush();
-            if (m) {
-                if (cur < 0) cur = c;
-                run.add(Mo[k], (Real)(16 * wv + k));
-            }
         }
-        if (cur >= 0) flush();
     }
     __syncthreads();
     // 7. publish the LDS records
