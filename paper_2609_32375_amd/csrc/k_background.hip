@@ -120,7 +120,7 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int gm = blockIdx.x;
     if (ONE && gm == 0 && tid == 0) desc[0] = d1;
-    const int f = ONE ? 0 : frame_of(nframes, gm, [&](int i) { return desc[i].mesh_base; });
+    const int f = ONE ? 0 : frame_of_wave(nframes, gm, [&](int i) { return desc[i].mesh_base; });
     const FrameDesc d = ONE ? d1 : desc[f];
     if ((d.dtype == kDtypeU16) != kInt) return;   // the other kernel's mesh of a mixed batch
     const int lm = gm - d.mesh_base;

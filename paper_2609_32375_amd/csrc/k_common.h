@@ -232,6 +232,22 @@ __device__ __forceinline__ int frame_of(int nframes, int idx, Get base) {
     return lo;
 }
 
+// the same by a whole wavefront for one index: 64 bases per load (a chain of
+// dependent loads otherwise), the bases <= idx being a prefix of them
+template <typename Get>
+__device__ __forceinline__ int frame_of_wave(int nframes, int idx, Get base) {
+    if (nframes == 1) return 0;
+    const int lane = threadIdx.x & 63;
+    int f = -1;
+    for (int i0 = 0; i0 < nframes; i0 += 64) {
+        const int i = i0 + lane;
+        const uint64_t m = __ballot(i < nframes && base(min(i, nframes - 1)) <= idx);
+        f += __popcll(m);
+        if (m != ~0ull) break;
+    }
+    return f;
+}
+
 // half-sample symmetric reflection into [0, n)
 __device__ __forceinline__ int reflect_idx(int i, int n) {
     if (i >= 0 && i < n) return i;

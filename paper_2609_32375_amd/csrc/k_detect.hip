@@ -4,12 +4,12 @@
 //                  M = I - B over the tile plus the filter halo in LDS
 //                  (reflected borders), correlates it with the unit-sum kernel
 //                  (two 1-D passes for a rank-one kernel), thresholds F > t R,
-//                  labels the tile's components with a lock-free union-find in
-//                  LDS (roots = smallest raster index), numbers them in raster
-//                  order and accumulates per-piece moments: each lane owns one
-//                  column and sums column runs with compensated FP32, flushing a
-//                  run into the piece's record when it ends.  Border labels are
-//                  kept for the merge.
+//                  labels the tile's components row by row with a union-find
+//                  in LDS (roots = smallest raster index), numbers them in
+//                  raster order and accumulates per-piece moments: each lane
+//                  owns one column and sums column runs with compensated FP32,
+//                  each run added once to the piece's record.  Border labels
+//                  are kept for the merge.
 //  k_merge_edges   unions pieces that touch across tile borders (8- or
 //                  4-neighbourhood) in a global union-find.
 //  k_merge_records adds every non-root piece into its root record and sets
@@ -48,13 +48,56 @@ struct LocalRec {
 // LDS regions are reused phase by phase (REG: region width and height, the
 // tile plus the filter halo; NIX: spline pieces of a region row; 29 KB for
 // FP32, REG = 68 and NIX = 4, five workgroups per compute unit):
-//   u1: row cubics (build M, R) -> union pair lists -> piece ids
+//   u1: row cubics (build M, R) -> the pixels' labels -> piece ids
 //   u2: M over tile + halo (the horizontal pass in place) -> labels -> piece
 //       records (M is held in VGPRs from the labels on)
+//
+// Row cubics as groups of four coefficients: one LDS read for most of M's and
+// one for R's (with the frame of a tile found by one ballot, a mask bit by the
+// mask itself: 16 frames of u16 2047 -> 1986 us, 12300^2 crowded 1411 -> 1361).
+template <typename Real, int N>
+struct CubicTab;
+template <int N>
+struct CubicTab<float, N> {
+    float4 m[N], r[N];   // a0h a0l a1 a2 | r0 .. r3
+    float m3[N];
+    __device__ void put(int i, const RowT<float>& t) {
+        m[i] = make_float4(t.a0h, t.a0l, t.a1, t.a2);
+        r[i] = make_float4(t.r0, t.r1, t.r2, t.r3);
+        m3[i] = t.a3;
+    }
+    __device__ RowT<float> back(int i) const {
+        const float4 v = m[i];
+        RowT<float> t;
+        t.a0h = v.x;
+        t.a0l = v.y;
+        t.a1 = v.z;
+        t.a2 = v.w;
+        t.a3 = m3[i];
+        return t;
+    }
+    __device__ RowT<float> noise(int i) const {
+        const float4 v = r[i];
+        RowT<float> t;
+        t.r0 = v.x;
+        t.r1 = v.y;
+        t.r2 = v.z;
+        t.r3 = v.w;
+        return t;
+    }
+};
+template <int N>
+struct CubicTab<double, N> {
+    RowT<double> t[N];
+    __device__ void put(int i, const RowT<double>& v) { t[i] = v; }
+    __device__ RowT<double> back(int i) const { return t[i]; }
+    __device__ RowT<double> noise(int i) const { return t[i]; }
+};
+
 template <typename Real, int REG, int NIX>
 struct DetShared {
     union U1 {
-        RowT<Real> tab[REG * NIX];
+        CubicTab<Real, REG * NIX> tab;
         int16_t comp[kTile * kTile];
     } u1;
     union U2 {
@@ -183,7 +226,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int gt = xcd_item(blockIdx.x, (wk.total_tiles + kXcds - 1) / kXcds);
     if (gt >= wk.total_tiles) return;
-    const int f = frame_of(wk.nframes, gt, [&](int i) { return wk.desc[i].tile_base; });
+    const int f = frame_of_wave(wk.nframes, gt, [&](int i) { return wk.desc[i].tile_base; });
     const FrameDesc d = wk.desc[f];
     const int lt = gt - d.tile_base;
     const int tx = lt % d.ntx, ty = lt / d.ntx;
@@ -279,7 +322,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
         const int chunk = (wk.total_tiles + kXcds - 1) / kXcds;
         const int g2 = gt + wk.ahead;
         if (wk.ahead > 0 && g2 < min(wk.total_tiles, (blockIdx.x % kXcds + 1) * chunk)) {
-            const int f2 = frame_of(wk.nframes, g2, [&](int i) { return wk.desc[i].tile_base; });
+            const int f2 = frame_of_wave(wk.nframes, g2, [&](int i) { return wk.desc[i].tile_base; });
             const FrameDesc& d2 = wk.desc[f2];
             const int l2 = g2 - d2.tile_base;
             const int x2 = (l2 % d2.ntx) * kTile, y2 = (l2 / d2.ntx) * kTile;
@@ -304,7 +347,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
         const int ys = reflect_idx(y0 - ry + r, d.H);
         const int jy = piece_of(ys, d.H, d.mh);
         const double u = (double)ys - piece_ref(jy, d.H, d.mh);
-        sh.u1.tab[r * NIX + pi] = make_row<Real>(d.coef, d.nx, d.ny, ixlo + pi, jy, u);
+        sh.u1.tab.put(r * NIX + pi, make_row<Real>(d.coef, d.nx, d.ny, ixlo + pi, jy, u));
     }
     for (int c = tid; c < RW; c += 256) {
         const int xs = reflect_idx(x0 - rx + c, d.W);
@@ -321,7 +364,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
 #pragma unroll
         for (int q = 0; q < CR; ++q) {
             const int r = wv + 4 * q;
-            if (r < RH) sh.u2.ms[r * MS + c] = eval_M(sh.u1.tab[r * NIX + pc], sx, (Real)pv[q]);
+            if (r < RH) sh.u2.ms[r * MS + c] = eval_M(sh.u1.tab.back(r * NIX + pc), sx, (Real)pv[q]);
             if (has_sat && __ballot(pv[q] >= sat) != 0ull) note_sat(pv[q], r, c);
         }
 #pragma unroll
@@ -329,7 +372,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
             const int e = tid + 256 * i;
             const int r = e / (HW > 0 ? HW : 1), hc = halo_col(e - r * HW);
             if (r < RH)
-                sh.u2.ms[r * MS + hc] = eval_M(sh.u1.tab[r * NIX + sh.colp[hc]], sh.colsx[hc], (Real)pv[CR + i]);
+                sh.u2.ms[r * MS + hc] = eval_M(sh.u1.tab.back(r * NIX + sh.colp[hc]), sh.colsx[hc], (Real)pv[CR + i]);
         }
     } else {
 #pragma unroll
@@ -337,7 +380,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
             const int e = tid + 256 * i;
             const int r = e / REG, c = e - r * REG;
             if (r < RH && c < RW) {
-                sh.u2.ms[r * MS + c] = eval_M(sh.u1.tab[r * NIX + sh.colp[c]], sh.colsx[c], (Real)pv[i]);
+                sh.u2.ms[r * MS + c] = eval_M(sh.u1.tab.back(r * NIX + sh.colp[c]), sh.colsx[c], (Real)pv[i]);
                 if (has_sat) note_sat(pv[i], r, c);
             }
         }
@@ -352,7 +395,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             const int ly = 16 * wv + k;
-            To[k] = (colok && ly < th) ? ts * eval_R(sh.u1.tab[(ly + ry) * NIX + pc], sx) : (Real)0;
+            To[k] = (colok && ly < th) ? ts * eval_R(sh.u1.tab.noise((ly + ry) * NIX + pc), sx) : (Real)0;
         }
     }
     __syncthreads();
@@ -440,7 +483,8 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
     //    are the smallest raster index of each component.  The labels so
     //    found are roots or a step away, where uniting every touching pair
     //    of runs left chains as long as a component is high (12300^2
-    //    crowded: 69k of 115k cycles per tile; now 14k).
+    //    crowded: 69k of a tile's 115k cycles were labels and roots, now 35k
+    //    of 84k; the kernel 1750 -> 1410 us).
     int32_t* lab = sh.u2.lab;      // M is held in VGPRs from here on; entries of runs' first pixels
     int16_t* comp = sh.u1.comp;    // each pixel's label, later its piece id
     const uint64_t below = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));   // lanes < lane
@@ -487,7 +531,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
             const int k = __builtin_ctz(rr), ly = 16 * wv + k;
             const uint64_t m = row_mask(k);
             if (k != last + 1) mu = 0ull;
-            const bool on = (m >> lane) & 1ull;
+            const bool on = __builtin_amdgcn_inverse_ballot_w64(m);
             const uint64_t zb = ~m & below;
             const int p0 = ly * kTile + (zb ? 64 - __clzll(zb) : 0);   // the run's first pixel
             const int p = ly * kTile + lane;
@@ -501,16 +545,16 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
                 lds_order();
 #pragma unroll
                 for (int t = 0; t < 3; ++t)
-                    if ((cm[t] >> lane) & 1ull) atomicMin(&lab[p0], u[t]);
+                    if (__builtin_amdgcn_inverse_ballot_w64(cm[t])) atomicMin(&lab[p0], u[t]);
             }
             lds_order();
             const int l = on ? lds_ld(&lab[p0]) : -1;
             if (on) comp[p] = (int16_t)l;
             // runs of other labels that this run joins
-            for (int t = 0; t < 3; ++t) {
+            for (int t = 0; mu != 0ull && t < 3; ++t) {
                 const int ut = t == 0 ? u[0] : t == 1 ? u[1] : u[2];
                 const uint64_t ct = t == 0 ? cm[0] : t == 1 ? cm[1] : cm[2];
-                const bool join = ((ct >> lane) & 1ull) && ut != l;
+                const bool join = __builtin_amdgcn_inverse_ballot_w64(ct) && ut != l;
                 if (__ballot(join) != 0ull && join) lds_union(lab, ut, l);
             }
             prev = l;
@@ -530,7 +574,7 @@ k_detect_tiles(DetWork wk, const DetArgs* __restrict__ pa) {
         const int p = 16 * wv * kTile + lane;
         for (int t3 = 0; t3 < 3; ++t3) {
             const uint64_t ct = t3 == 0 ? cm[0] : t3 == 1 ? cm[1] : cm[2];
-            if ((ct >> lane) & 1ull) lds_union(lab, comp[p], comp[p - kTile + (t3 == 0 ? 0 : t3 == 1 ? -1 : 1)]);
+            if (__builtin_amdgcn_inverse_ballot_w64(ct)) lds_union(lab, comp[p], comp[p - kTile + (t3 == 0 ? 0 : t3 == 1 ? -1 : 1)]);
         }
     }
     __syncthreads();
@@ -1257,7 +1301,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
     const int tid = threadIdx.x;
     const int gt = xcd_item(blockIdx.x, (wk.total_tiles + kXcds - 1) / kXcds);
     if (gt >= wk.total_tiles) return;
-    const int f = frame_of(wk.nframes, gt, [&](int i) { return wk.desc[i].tile_base; });
+    const int f = frame_of_wave(wk.nframes, gt, [&](int i) { return wk.desc[i].tile_base; });
     const FrameDesc d = wk.desc[f];
     const int lt = gt - d.tile_base;
     const int tx = lt % d.ntx, ty = lt / d.ntx;
@@ -1329,7 +1373,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
         const int chunk = (wk.total_tiles + kXcds - 1) / kXcds;
         const int g2 = gt + wk.ahead;
         if (wk.ahead > 0 && g2 < min(wk.total_tiles, (blockIdx.x % kXcds + 1) * chunk)) {
-            const int f2 = frame_of(wk.nframes, g2, [&](int i) { return wk.desc[i].tile_base; });
+            const int f2 = frame_of_wave(wk.nframes, g2, [&](int i) { return wk.desc[i].tile_base; });
             const FrameDesc& d2 = wk.desc[f2];
             const int l2 = g2 - d2.tile_base;
             const int x2 = (l2 % d2.ntx) * kTile, y2 = (l2 / d2.ntx) * kTile;

@@ -354,6 +354,57 @@ def test_labels_bit_exact_for_given_mask(P, case, conn, mesh):
     ph.close()
 
 
+def _strip_mask(row, kind):
+    """a 130 x 150 mask whose components meet in one tile row: teeth down to
+    it ("comb"), up from it ("rake"), or zigzags around it ("zigzag": steps of
+    one column, 8-connected only)"""
+    m = np.zeros((130, 150), bool)
+    if kind == "zigzag":
+        yy, xx = np.mgrid[0:130, 0:150]
+        m[(np.abs((xx % 10) - 5) == (yy - row) % 5) & (np.abs(yy - row) < 20)] = True
+        return m
+    lo, hi = (max(0, row - 25), row) if kind == "comb" else (row, row + 25)
+    m[lo:hi + 1, ::3] = True
+    m[row, 2:-2] = True
+    m[row, 60:62] = False
+    return m
+
+
+@pytest.mark.parametrize("kind", ["comb", "rake", "zigzag"])
+@pytest.mark.parametrize("row", [1, 15, 16, 17, 31, 32, 63, 64, 79])
+def test_labels_where_runs_join_at_strip_rows(P, row, kind):
+    """components that join in the first and last rows of a wavefront's 16-row
+    strip and of a tile, and saturated pixels there and in the tile's corners"""
+    _say("strip case", row, kind)
+    mask = _strip_mask(row, kind)
+    H, W = mask.shape
+    c = 500.0
+    img = (c + np.where(mask, 100.0 + 50.0 * np.random.default_rng(row).random(mask.shape), 0.0)).astype(np.float32)
+    for y in (0, 15, 16, 63, 64, row):
+        for x in (0, 30, 31, 32, 63, 64):
+            if mask[y, x] or x % 32 == 0:
+                img[y, x] = 3000.0
+    mask = mask | (img >= 3000.0)
+    for conn in (8, 4):
+        p = _params("c1", mesh_w=64, mesh_h=64, conn=conn, minarea=2, thresh=1.5, sat_level=3000.0)
+        K = np.zeros((3, 3), np.float32)
+        K[1, 1] = 1.0
+        ny, nx = -(-H // 64), -(-W // 64)
+        ph = P.Photometry([_dev(img)], p, K, capacity=H * W, seg=True)
+        ph.set_grids(0, np.full((ny, nx), c), np.zeros((ny, nx)))
+        ph.background(grid_given=True)
+        ph.detect()
+        r = ph.results(0)
+        seg_o, n_o = oracle.label_mask(mask, conn, 2)
+        M = img.astype(np.float64) - c
+        assert r["status"] == 0 and r["n_obj"] == n_o
+        np.testing.assert_array_equal(r["seg"], seg_o)
+        ocat = oracle.measure(img, M, seg_o, n_o, p.sat_level)
+        cmp_catalog(r["cat"], ocat, M, seg_o, tag=f"{kind} {row} {conn}")
+        np.testing.assert_array_equal(r["cat"]["flags"] & 3, ocat["flags"] & 3)
+        ph.close()
+
+
 # ----------------------------------------------------------------------------
 # detection and photometry on star fields, stage-isolated
 # ----------------------------------------------------------------------------
