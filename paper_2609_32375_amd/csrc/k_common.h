@@ -203,6 +203,24 @@ __device__ __forceinline__ double wave_sum_d(double v) {
     }
     return v;
 }
+// the same without LDS: the halves, then the 16-lane rows, then inside a row
+__device__ __forceinline__ double wave_total_d(double v) {
+    const uint64_t x = (uint64_t)__double_as_longlong(v);
+    const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+    v = __longlong_as_double((long long)((uint64_t)l[0] | ((uint64_t)h[0] << 32))) +
+        __longlong_as_double((long long)((uint64_t)l[1] | ((uint64_t)h[1] << 32)));
+    const uint64_t y = (uint64_t)__double_as_longlong(v);
+    const auto l2 = __builtin_amdgcn_permlane16_swap((uint32_t)y, (uint32_t)y, false, false);
+    const auto h2 = __builtin_amdgcn_permlane16_swap((uint32_t)(y >> 32), (uint32_t)(y >> 32), false, false);
+    v = __longlong_as_double((long long)((uint64_t)l2[0] | ((uint64_t)h2[0] << 32))) +
+        __longlong_as_double((long long)((uint64_t)l2[1] | ((uint64_t)h2[1] << 32)));
+    v += dpp_d<0xB1>(v);
+    v += dpp_d<0x4E>(v);
+    v += dpp_d<0x141>(v);
+    v += dpp_d<0x140>(v);
+    return v;
+}
 __device__ __forceinline__ int wave_sum_i(int v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);

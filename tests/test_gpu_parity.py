@@ -997,6 +997,49 @@ def test_background_conv_against_oracle(P, case, prec):
     cb.close()
 
 
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("lx,ly,few", [(15, 17, 47), (17, 31, 48), (33, 47, 49), (63, 65, 1), (127, 3, 48), (3, 127, 49)])
+def test_background_conv_at_step_and_fill_edges(P, lx, ly, few, prec):
+    """tap counts around multiples of the 16 of a step; tiles with as many
+    invalid pixels as are filled one by one, one more and one less; a last row
+    segment and tile of one pixel; an infinite pixel far from most outputs"""
+    W, H = 2049, 129
+    _say("conv edge case", lx, ly, few, prec)
+    rng = np.random.default_rng(lx * ly)
+    I = (500.0 + 20.0 * rng.standard_normal((H, W))).astype(np.float32)
+    kx = (0.2 + rng.random(lx)).astype(np.float32)
+    ky = (0.2 + rng.random(ly)).astype(np.float32)
+    mask = np.zeros((H, W), np.uint8)
+    for x0, y0 in ((0, 0), (64, 64), (1984, 0)):
+        at = rng.choice(64 * 64, few, replace=False)
+        mask[y0 + at // 64, x0 + at % 64] = 1
+    mask[128, 2048] = 1
+    Bo, Ro, no = oracle.background_conv(I, kx.astype(np.float64), ky.astype(np.float64), mask=mask, sat=np.inf,
+                                        gain=1.5, rn=5.0, dark=0.0, texp=0.0)
+    cb = P.ConvBackground([_dev(I)], kx, ky, 1.5, 5.0, precision=prec)
+    cb.run([_dev(mask)])
+    torch.cuda.synchronize()
+    assert int(cb.unfilled[0].item()) == no
+    tol = _conv_tolerances(I, kx, ky, mask, np.inf, Bo, prec, 1.5)
+    B = cb.back[0].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(B - Bo) <= tol), float(np.max(np.abs(B - Bo) - tol))
+    # a pixel of minus infinity is valid: exactly the outputs whose window
+    # holds it (with its mirror images) are lost
+    J = I.copy()
+    J[70, 1000] = -np.inf
+    cb2 = P.ConvBackground([_dev(J)], kx, ky, 1.5, 5.0, precision=prec)
+    cb2.run([_dev(np.zeros_like(mask))])
+    torch.cuda.synchronize()
+    lost = ~np.isfinite(cb2.back[0].cpu().numpy())
+    hit = np.zeros((H, W))
+    hit[70, 1000] = 1.0
+    from scipy import ndimage
+    want = ndimage.correlate(hit, np.ones((ly, lx)), mode="reflect") > 0.5
+    np.testing.assert_array_equal(lost, want)
+    cb.close()
+    cb2.close()
+
+
 def test_background_conv_constant_frame_and_batch(P):
     """A constant frame comes back unchanged; a batch of frames (uint16 and
     float32, several sizes) equals per-frame calls bit for bit."""
