@@ -73,46 +73,6 @@ struct ApLayout {
 // object-count prefix over the frames (whole workgroup), before the wavefronts' parts
 __host__ __device__ __forceinline__ int ap_prefix_bytes(int nframes) { return (4 * (nframes + 1) + 15) / 16 * 16; }
 
-// Sums of N (16 or 32) values over the wavefront's lanes, in a fixed order.
-// The halves of the wavefront exchange halves of the list, then the 16-lane
-// rows quarters of it, so that only N / 4 values are left for the four steps
-// inside a row.  total(i) is value i's sum.
-template <int N>
-struct WaveTotals {
-    double v[N / 4];
-    __device__ __forceinline__ static double swap_add32(double a, double b) {
-        const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
-        const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
-        return __longlong_as_double((long long)((uint64_t)l[0] | ((uint64_t)h[0] << 32))) +
-               __longlong_as_double((long long)((uint64_t)l[1] | ((uint64_t)h[1] << 32)));
-    }
-    __device__ __forceinline__ static double swap_add16(double a, double b) {
-        const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
-        const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
-        const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
-        return __longlong_as_double((long long)((uint64_t)l[0] | ((uint64_t)h[0] << 32))) +
-               __longlong_as_double((long long)((uint64_t)l[1] | ((uint64_t)h[1] << 32)));
-    }
-    __device__ __forceinline__ explicit WaveTotals(const double (&x)[N]) {
-        double h[N / 2];
-#pragma unroll
-        for (int i = 0; i < N / 2; ++i) h[i] = swap_add32(x[i], x[i + N / 2]);   // lanes 32..: value i + N / 2
-#pragma unroll
-        for (int i = 0; i < N / 4; ++i) {
-            double t = swap_add16(h[i], h[i + N / 4]);   // odd rows: value i + N / 4 of the half
-            t += dpp_d<0xB1>(t);
-            t += dpp_d<0x4E>(t);
-            t += dpp_d<0x141>(t);
-            t += dpp_d<0x140>(t);
-            v[i] = t;
-        }
-    }
-    __device__ __forceinline__ double total(int i) const {
-        return lane_d(v[i % (N / 4)], 16 * (((i / (N / 4)) & 1) | (i / (N / 2)) << 1));
-    }
-};
-
 // Circles: the aperture radii, r_in and r_out, sorted by radius on the host
 // (a.crad / a.crole).  Circles are nested, so a pixel lies wholly inside every
 // circle from some index kin on, wholly outside those before kout, and only

@@ -159,6 +159,7 @@ void launch_aperture(const FrameDesc* desc, const FrameDesc* one, const ApArgs& 
 void launch_growth_table(const GrowArgs& a, const GrowTab& t, hipStream_t s);
 hipError_t launch_growth(const FrameDesc* desc, const FrameDesc* one, const GrowArgs& a, const GrowTab& t,
                          const GrowOut& g, int blocks, int waves, bool f64, hipStream_t s);
+constexpr int kGrowMaxWaves = 12;   // wavefronts of k_growth per workgroup and compute unit
 size_t growth_lds_bytes(int nfull, int ncut, int side, int nixmax, int want_var, bool f64, int waves);
 // One frame of a convolution-background call.  Every frame has its own
 // slices of the working planes (hA / hG and G: element offset plane), of the

@@ -203,24 +203,58 @@ __device__ __forceinline__ double wave_sum_d(double v) {
     }
     return v;
 }
-// the same without LDS: the halves, then the 16-lane rows, then inside a row
+// lanes exchanged between the halves of the wavefront (or, 16, of each half),
+// added: the low half gets a's sum over the pair, the high half b's
+__device__ __forceinline__ double swap_add32(double a, double b) {
+    const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+    const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __longlong_as_double((long long)((uint64_t)l[0] | ((uint64_t)h[0] << 32))) +
+           __longlong_as_double((long long)((uint64_t)l[1] | ((uint64_t)h[1] << 32)));
+}
+__device__ __forceinline__ double swap_add16(double a, double b) {
+    const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+    const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __longlong_as_double((long long)((uint64_t)l[0] | ((uint64_t)h[0] << 32))) +
+           __longlong_as_double((long long)((uint64_t)l[1] | ((uint64_t)h[1] << 32)));
+}
+// the sum of one value over the wavefront in every lane, without LDS
 __device__ __forceinline__ double wave_total_d(double v) {
-    const uint64_t x = (uint64_t)__double_as_longlong(v);
-    const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
-    v = __longlong_as_double((long long)((uint64_t)l[0] | ((uint64_t)h[0] << 32))) +
-        __longlong_as_double((long long)((uint64_t)l[1] | ((uint64_t)h[1] << 32)));
-    const uint64_t y = (uint64_t)__double_as_longlong(v);
-    const auto l2 = __builtin_amdgcn_permlane16_swap((uint32_t)y, (uint32_t)y, false, false);
-    const auto h2 = __builtin_amdgcn_permlane16_swap((uint32_t)(y >> 32), (uint32_t)(y >> 32), false, false);
-    v = __longlong_as_double((long long)((uint64_t)l2[0] | ((uint64_t)h2[0] << 32))) +
-        __longlong_as_double((long long)((uint64_t)l2[1] | ((uint64_t)h2[1] << 32)));
+    v = swap_add32(v, v);
+    v = swap_add16(v, v);
     v += dpp_d<0xB1>(v);
     v += dpp_d<0x4E>(v);
     v += dpp_d<0x141>(v);
     v += dpp_d<0x140>(v);
     return v;
 }
+// Sums of N (16 or 32) values over the wavefront's lanes, in a fixed order.
+// The halves of the wavefront exchange halves of the list, then the 16-lane
+// rows quarters of it, so that only N / 4 values are left for the four steps
+// inside a row.  total(i) is value i's sum.
+template <int N>
+struct WaveTotals {
+    double v[N / 4];
+    __device__ __forceinline__ explicit WaveTotals(const double (&x)[N]) {
+        double h[N / 2];
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) h[i] = swap_add32(x[i], x[i + N / 2]);   // lanes 32..: value i + N / 2
+#pragma unroll
+        for (int i = 0; i < N / 4; ++i) {
+            double t = swap_add16(h[i], h[i + N / 4]);   // odd rows: value i + N / 4 of the half
+            t += dpp_d<0xB1>(t);
+            t += dpp_d<0x4E>(t);
+            t += dpp_d<0x141>(t);
+            t += dpp_d<0x140>(t);
+            v[i] = t;
+        }
+    }
+    __device__ __forceinline__ double total(int i) const {
+        return lane_d(v[i % (N / 4)], 16 * (((i / (N / 4)) & 1) | (i / (N / 2)) << 1));
+    }
+};
+
 __device__ __forceinline__ int wave_sum_i(int v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);

@@ -18,8 +18,12 @@
 //
 // One wavefront per source: it evaluates M (and R^2) over the (2R+1)^2 window
 // once into LDS from per-row background cubics, then walks the lists, lane e
-// mod 64 taking entry e, and reduces each radius over the lanes in a fixed
-// butterfly, so a source's result does not depend on what else runs.
+// mod 64 taking entry e, and reduces the radii over the lanes in a fixed
+// order, so a source's result does not depend on what else runs.  Bound by
+// the latency of its LDS reads at the few wavefronts its windows leave room
+// for: with 12 of them per compute unit for 8, the full lists read without a
+// gap at each radius and one reduction per four radii for twelve butterflies,
+// 20000 sources with 13 radii up to 15 took 151 us for 281.
 #include "k_args.h"
 #include "k_overlap.h"
 #include "k_rowpoly.h"
@@ -130,7 +134,7 @@ struct GrLayout {
 constexpr int kGrUnroll = 4;   // window pixels per lane in flight
 
 template <typename Real, bool ONE>
-__global__ __launch_bounds__(512) void k_growth(const FrameDesc* __restrict__ desc, FrameDesc d1, GrowArgs a,
+__global__ __launch_bounds__(64 * kGrowMaxWaves) void k_growth(const FrameDesc* __restrict__ desc, FrameDesc d1, GrowArgs a,
                                                 GrowTab t, GrowOut g) {
     extern __shared__ __align__(16) unsigned char gr_dyn[];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -202,6 +206,7 @@ __global__ __launch_bounds__(512) void k_growth(const FrameDesc* __restrict__ de
         const int wx_lo = max(0, -bx0), wx_hi = min(side - 1, d.W - 1 - bx0);
         const int wy_lo = max(0, -by0), wy_hi = min(side - 1, d.H - 1 - by0);
         const bool any = reach && wx_lo <= wx_hi && wy_lo <= wy_hi;
+        const bool inside = wx_lo == 0 && wy_lo == 0 && wx_hi == side - 1 && wy_hi == side - 1;   // the whole window
         double my_s = 0.0, my_v = 0.0, my_a = 0.0;
         if (any) {
             const int cx_lo = bx0 + wx_lo, cx_hi = bx0 + wx_hi;
@@ -259,33 +264,61 @@ __global__ __launch_bounds__(512) void k_growth(const FrameDesc* __restrict__ de
                 }
             }
             wave_sync();
-            double sm = 0.0, sv = 0.0, sa = 0.0;   // this lane's share of the full lists so far
-            for (int k = 0; k < nr; ++k) {
-                for (int e = a.full_off[k] + lane; e < a.full_off[k + 1]; e += 64) {
-                    const int pk = fl[e];
-                    const int wy = pk >> 16, wx = pk & 0xffff;
-                    const int w = wy * side + wx;
-                    sm += (double)Mw[w];
-                    if (a.want_var) sv += (double)Vw[w];
-                    sa += (wx >= wx_lo && wx <= wx_hi && wy >= wy_lo && wy <= wy_hi) ? 1.0 : 0.0;
+            // Sums: the full lists lie one after the other, so 64 entries at
+            // a time are read whatever list they belong to; radius k takes
+            // the whole rounds before its end and, of the round that holds
+            // its end, the entries below it.  Four radii are reduced at once.
+            auto entry = [&](int pk, double wt, double& m, double& v, double& ar) __attribute__((always_inline)) {
+                const int wy = pk >> 16, wx = pk & 0xffff, w = wy * side + wx;
+                m = wt * (double)Mw[w];
+                v = a.want_var ? wt * (double)Vw[w] : 0.0;
+                ar = inside || (wx >= wx_lo && wx <= wx_hi && wy >= wy_lo && wy <= wy_hi) ? wt : 0.0;
+            };
+            double sm = 0.0, sv = 0.0, sa = 0.0;   // this lane's share of the whole rounds so far
+            double em, ev, ea;                     // and of the round that starts at entry at0
+            int at0 = 0;
+            auto round = [&]() __attribute__((always_inline)) {
+                em = ev = ea = 0.0;
+                if (at0 + lane < a.nfull) entry(fl[at0 + lane], 1.0, em, ev, ea);
+            };
+            round();
+            for (int k0 = 0; k0 < nr; k0 += 4) {
+                double x[16];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    x[q] = x[4 + q] = x[8 + q] = x[12 + q] = 0.0;
+                    const int k = k0 + q;
+                    if (k >= nr) continue;
+                    const int end = a.full_off[k + 1];
+                    while (at0 + 64 <= end) {
+                        sm += em;
+                        sv += ev;
+                        sa += ea;
+                        at0 += 64;
+                        round();
+                    }
+                    const bool below = at0 + lane < end;
+                    double cm = sm + (below ? em : 0.0), cv = sv + (below ? ev : 0.0), ca = sa + (below ? ea : 0.0);
+                    for (int e = a.cut_off[k] + lane; e < a.cut_off[k + 1]; e += 64) {
+                        double m, v, ar;
+                        entry(cl[e], cw[e], m, v, ar);
+                        cm += m;
+                        cv += v;
+                        ca += ar;
+                    }
+                    x[q] = cm;
+                    x[4 + q] = cv;
+                    x[8 + q] = ca;
                 }
-                double cm = 0.0, cv = 0.0, ca = 0.0;
-                for (int e = a.cut_off[k] + lane; e < a.cut_off[k + 1]; e += 64) {
-                    const int pk = cl[e];
-                    const double wt = cw[e];
-                    const int wy = pk >> 16, wx = pk & 0xffff;
-                    const int w = wy * side + wx;
-                    cm += wt * (double)Mw[w];
-                    if (a.want_var) cv += wt * (double)Vw[w];
-                    ca += (wx >= wx_lo && wx <= wx_hi && wy >= wy_lo && wy <= wy_hi) ? wt : 0.0;
-                }
-                const double ts = wave_sum_d(sm + cm);
-                const double tv = a.want_var ? wave_sum_d(sv + cv) : 0.0;
-                const double ta = wave_sum_d(sa + ca);
-                if (lane == k) {
-                    my_s = ts;
-                    my_v = tv;
-                    my_a = ta;
+                const WaveTotals<16> T(x);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double ts = T.total(q), tv = T.total(4 + q), ta = T.total(8 + q);
+                    if (lane == k0 + q) {
+                        my_s = ts;
+                        my_v = tv;
+                        my_a = ta;
+                    }
                 }
             }
         }

@@ -1166,12 +1166,20 @@ extern "C" gp_status gp_growth(gp_ctx* ctx, const gp_frame* frames, int32_t nfra
     // spline pieces a window of `side` columns can touch (knots one mesh apart,
     // the last at least half a mesh from its neighbour)
     a.nixmax = std::max(1, std::min(max_nx + 1, (a.side - 1) / std::max(bp->mesh_w, 1) + 3));
-    // wavefronts per workgroup: as many (up to 8) as fit the 160 KB of LDS
-    int waves = 8;
-    while (waves > 1 && growth_lds_bytes(a.nfull, a.ncut, a.side, a.nixmax, a.want_var, f64, waves) > 160 * 1024)
-        --waves;
-    if (growth_lds_bytes(a.nfull, a.ncut, a.side, a.nixmax, a.want_var, f64, waves) > 160 * 1024)
-        return fail(GP_ERR_UNSUPPORTED, "growth window of radius %d does not fit in LDS", a.R);
+    // wavefronts per workgroup: the number (up to 12) that lets most of them
+    // share the 160 KB of LDS of a compute unit, windows of their own and one
+    // copy of the tap table per workgroup (radius 15: one workgroup of 12
+    // where 8 left a third of the LDS unused)
+    int waves = 0, resident = 0;
+    for (int w = kGrowMaxWaves; w >= 1; --w) {
+        const size_t b = growth_lds_bytes(a.nfull, a.ncut, a.side, a.nixmax, a.want_var, f64, w);
+        const int r = (int)std::min<size_t>(160 * 1024 / b, kGrowMaxWaves / w);
+        if (r * w > resident * waves) {
+            waves = w;
+            resident = r;
+        }
+    }
+    if (waves == 0) return fail(GP_ERR_UNSUPPORTED, "growth window of radius %d does not fit in LDS", a.R);
     Plan P;
     plan_bkg(frames, nframes, bp, P);
     plan_fixed(nframes, P);
@@ -1194,7 +1202,7 @@ extern "C" gp_status gp_growth(gp_ctx* ctx, const gp_frame* frames, int32_t nfra
         ProfScope ps(ctx, s, "growth");
         launch_growth_table(a, t, s);
         const int total_rows = nframes * cat->capacity;
-        const int blocks = std::max(1, std::min(ctx->cus * 4, (total_rows + waves - 1) / waves));
+        const int blocks = std::max(1, std::min(ctx->cus * resident, (total_rows + waves - 1) / waves));
         hipError_t e = launch_growth((const FrameDesc*)(W + P.o_desc), one ? &tail.d[0] : nullptr, a, t, g, blocks,
                                      waves, f64, s);
         if (e != hipSuccess) return fail(GP_ERR_HIP, "growth launch: %s", hipGetErrorString(e));

@@ -845,6 +845,34 @@ def test_growth_taps_on_a_zero_background(P, prec):
     ph.close()
 
 
+@pytest.mark.parametrize("radii", [[1], [1, 2], [4, 5, 6, 9], [2, 3, 5, 8, 32], [1, 4, 8, 9, 12, 13, 20, 21, 22]], ids=str)
+def test_growth_radii_sets(P, radii):
+    """numbers of radii around the four that are reduced at once, lists that
+    end inside and at the end of a round of 64 entries, one and several
+    workgroups per compute unit"""
+    W, H = 150, 130
+    rng = np.random.default_rng(len(radii))
+    img = rng.normal(0, 30, (H, W)).astype(np.float32)
+    p = _params("c1")
+    nx, ny = -(-W // p.mesh_w), -(-H // p.mesh_h)
+    ph = P.Photometry([_dev(img)], p, p.kernel(), capacity=200)
+    ph.set_grids(0, np.zeros((ny, nx)), np.full((ny, nx), 3.0))
+    ph.background(grid_given=True)
+    xs, ys = rng.uniform(-5, W + 5, 200), rng.uniform(-5, H + 5, 200)
+    ph.set_catalog(0, xs, ys)
+    ph.growth(radii)
+    r = ph.results(0)["growth"]
+    M = img.astype(np.float64)
+    o = oracle.growth(M, np.full((H, W), 9.0), xs, ys, radii)
+    cond = oracle.growth(np.abs(M), None, xs, ys, radii)["sum"]
+    sa_m, na = growth_allowance(np.abs(M), xs, ys, radii)
+    assert np.all(np.abs(r["sum"] - o["sum"]) <= 8 * 2.0 ** -53 * cond + sa_m)
+    assert np.all(np.abs(r["area"] - o["area"]) <= na + 8 * 2.0 ** -53 * o["area"])
+    assert np.all(np.abs(r["var"] - o["var"]) <= 9.0 * (na + 8 * 2.0 ** -53 * o["area"]))
+    np.testing.assert_array_equal(r["flags"], o["flags"])
+    ph.close()
+
+
 def test_growth_constant_image_closed_form(P):
     c = 7.25
     W, H = 150, 120
