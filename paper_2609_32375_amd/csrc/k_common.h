@@ -300,6 +300,16 @@ __device__ __forceinline__ int frame_of_wave(int nframes, int idx, Get base) {
     return f;
 }
 
+// e / d by a multiplication, for e d < 2^32 and a divisor shared by the
+// workgroup (an integer division is some 25 instructions)
+struct Div {
+    uint32_t d, m;
+    __device__ __forceinline__ explicit Div(int n)
+        : d((uint32_t)n), m((uint32_t)((((uint64_t)1 << 32) + (uint32_t)n - 1) / (uint32_t)n)) {}
+    // (m of 1 does not fit 32 bits)
+    __device__ __forceinline__ int operator()(int e) const { return d == 1u ? e : (int)__umulhi((uint32_t)e, m); }
+};
+
 // half-sample symmetric reflection into [0, n)
 __device__ __forceinline__ int reflect_idx(int i, int n) {
     if (i >= 0 && i < n) return i;

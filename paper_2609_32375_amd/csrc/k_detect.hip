@@ -1285,11 +1285,19 @@ struct PeakLayout {
         }
         o_colp = take(rmw * 4);
         o_cols = take(rmw * real_bytes);
-        o_cand = take(kTile * 2 * 4);
+        o_cand = take((kTile * 2 + 1) * 4);   // candidate bits, the saturation flag
         bytes = (o + 15) / 16 * 16;
     }
 };
 
+// The plain filter's tile is bound by the latency of its phases at three
+// workgroups per compute unit: loads of a region inside the frame without
+// reflection, indices split by a multiplication and not a division, rows
+// without a local maximum left early, raw pixels read again for the
+// saturation flag only if the region holds a saturated one: 4096^2 u16, sep 3,
+// 5 x 5 filter 321 -> 249 us.  The varying filter is bound by its FP32 FMAs
+// (6 x 169 per output, 430 us at the peak rate): 963 -> 889 us.
+//
 // NM > 0: the spatially varying filter (NM dense correlations, the reference
 // and up to NM - 1 modes, weighted by the coefficient maps at the output
 // pixel) in place of the plain one; modes past the model's are zero taps
@@ -1333,6 +1341,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
         }
     }
     if (tid < kTile * 2) cand[tid] = 0u;
+    if (tid == 0) cand[kTile * 2] = 0u;   // a pixel of the region is at or above the saturation level
     // a dense filter's taps, after nu (the rank-one passes do not use them
     // and write over that space)
     const bool sepk = !VARY && pa->separable != 0;
@@ -1349,20 +1358,31 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
     // (12 loads per thread in flight at a time; a region holds at most
     // 92 x 92 pixels, 34 per thread)
     constexpr int kPkBatch = 12;
-    for (int e0 = tid; e0 < mw * mh; e0 += 256 * kPkBatch) {
-        float v[kPkBatch];
+    const Div by_mw(mw);
+    const float sat = pa->sat;
+    bool any_sat = false;
+    auto fill = [&](auto&& px) __attribute__((always_inline)) {
+        for (int e0 = tid; e0 < mw * mh; e0 += 256 * kPkBatch) {
+            float v[kPkBatch];
 #pragma unroll
-        for (int u = 0; u < kPkBatch; ++u) {
-            const int e = e0 + 256 * u;
-            const int r = e / mw, c = e - r * mw;
-            v[u] = (e < mw * mh) ? load_px(d, reflect_idx(gx0 + c, d.W), reflect_idx(gy0 + r, d.H)) : 0.0f;
-        }
+            for (int u = 0; u < kPkBatch; ++u) {
+                const int e = min(e0 + 256 * u, mw * mh - 1), r = by_mw(e);
+                v[u] = px(e - r * mw, r);
+            }
 #pragma unroll
-        for (int u = 0; u < kPkBatch; ++u) {
-            const int e = e0 + 256 * u;
-            const int r = e / mw, c = e - r * mw;
-            if (e < mw * mh) ms[r * L.rmw + c] = (Real)v[u];
+            for (int u = 0; u < kPkBatch; ++u) {
+                const int e = e0 + 256 * u, r = by_mw(e), c = e - r * mw;
+                if (e < mw * mh) ms[r * L.rmw + c] = (Real)v[u];
+                any_sat |= v[u] >= sat;
+            }
         }
+    };
+    if (gx0 >= 0 && gy0 >= 0 && gx0 + mw <= d.W && gy0 + mh <= d.H) {
+        const int64_t o = (int64_t)gy0 * d.pitch + gx0;
+        if (d.dtype == kDtypeU16) fill([&](int c, int r) { return (float)((const gu16_t*)d.data + o)[(int64_t)r * d.pitch + c]; });
+        else fill([&](int c, int r) { return ((const gfloat_t*)d.data + o)[(int64_t)r * d.pitch + c]; });
+    } else {
+        fill([&](int c, int r) { return load_px(d, reflect_idx(gx0 + c, d.W), reflect_idx(gy0 + r, d.H)); });
     }
     // warm the L2 with the region of the tile this XCD takes up one round of
     // resident workgroups later (one load per 128-byte line of its rows,
@@ -1413,9 +1433,10 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
         colsx[c] = (Real)((double)xs - piece_ref(ix, d.W, d.mw));
     }
     __syncthreads();
+    if (any_sat) cand[kTile * 2] = 1u;   // (read after the next barriers)
     // 2. M = I - B over the region, in place
     for (int e = tid; e < mw * mh; e += 256) {
-        const int r = e / mw, c = e - r * mw;
+        const int r = by_mw(e), c = e - r * mw;
         Real* q = &ms[r * L.rmw + c];
         *q = eval_M(tab[r * L.nix + colp[c]], colsx[c], *q);
     }
@@ -1425,6 +1446,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
     //    filter below skips those positions); candidates F > t R inside the tile
     const Real ts = (Real)pa->thresh;
     const int fw = tw + 2 * sep, fh = th + 2 * sep;
+    const Div by_fw(fw);
     if (VARY) {
         // S = sum_m c_m (M corr e_m) (c_0 = 1) over the tile plus sep, into
         // nus.  A work item is kVaryRows output rows of one column and keeps
@@ -1510,7 +1532,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
         const int hr = fh + 2 * ry;
         const int m0 = L.hmy - sep - ry, c0 = L.hmx - sep - rx;
         for (int e = tid; e < hr * fw; e += 256) {
-            const int t = e / fw, i = e - t * fw;
+            const int t = by_fw(e), i = e - t * fw;
             const Real* mrow = &ms[(m0 + t) * L.rmw + c0 + i];
             Real acc = 0;
             for (int b = 0; b < kw; ++b) acc = fma(kDbl ? (Real)pa->kxd[b] : (Real)pa->kx[b], mrow[b], acc);
@@ -1525,7 +1547,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
         const int e = tid + 256 * q;
         nv[q] = 0;
         if (e < fw * fh) {
-            const int j = e / fw, i = e - j * fw;
+            const int j = by_fw(e), i = e - j * fw;
             const int mr = j - sep + L.hmy, mc = i - sep + L.hmx;   // M-region position of (x, y)
             Real acc = 0;
             const int gx = x0 - sep + i, gy = y0 - sep + j;
@@ -1565,7 +1587,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
     for (int q = 0; q < kPkVals; ++q) {
         const int e = tid + 256 * q;
         if (e < fw * fh) {
-            const int j = e / fw, i = e - j * fw;
+            const int j = by_fw(e), i = e - j * fw;
             nus[j * L.rf + i] = nv[q];
         }
     }
@@ -1578,7 +1600,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
     //    peak unless an earlier pixel of the window (raster order) holds the
     //    same value
     const int lane = tid & 63, wv = tid >> 6;
-    const float sat = pa->sat;
+    const bool has_sat = cand[kTile * 2] != 0u;
     // (the wavefront's tile rows that hold a candidate, from one read of
     // their 32 candidate words; rows past th have none)
     uint32_t rows = 0u;
@@ -1592,6 +1614,15 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
         rows &= rows - 1u;
         const int ly = 16 * wv + k, lx = lane;
         const bool isc = ly < th && lx < tw && ((cand[ly * 2 + (lx >> 5)] >> (lx & 31)) & 1u);
+        // most candidates are below a neighbour: only the rows with one that
+        // is not go on (sep >= 1: the neighbours lie in the window)
+        bool top = isc;
+        if (isc && sep >= 1) {
+            const Real* q = &nus[(ly + sep) * L.rf + lx + sep];
+            const Real v = q[0];
+            top = !(v < q[-1]) && !(v < q[1]) && !(v < q[-L.rf]) && !(v < q[L.rf]);
+        }
+        if (__ballot(top) == 0ull) continue;
         Real vm = (Real)-INFINITY, vm2 = (Real)-INFINITY;
         for (int a = 0; a <= 2 * sep; ++a) {
             const Real* row = &nus[(ly + a) * L.rf];
@@ -1603,7 +1634,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
             const Real o1 = __shfl(vm, (lane + dd) & 63), o2 = __shfl(vm2, (lane + dd) & 63);
             wmax = fmax(wmax, lane + dd < kTile ? o1 : o2);
         }
-        if (!isc) continue;
+        if (!top) continue;
         const int gx = x0 + lx, gy = y0 + ly;
         const Real v = nus[(ly + sep) * L.rf + lx + sep];
         if (v < wmax) continue;
@@ -1640,7 +1671,7 @@ __global__ __launch_bounds__(256) void k_peaks_tiles(DetWork wk, const DetArgs* 
                 syy += w * dy * dy;
                 sxy += w * dx * dy;
                 flux += m;
-                if (sat < INFINITY && load_px(d, qx, qy) >= sat) fl |= kFlagSat;
+                if (has_sat && sat < INFINITY && load_px(d, qx, qy) >= sat) fl |= kFlagSat;
             }
         double mx = 0.0, my = 0.0, vx = 0.0, vy = 0.0, cxy = 0.0;
         if (sw > 0.0) {

@@ -745,6 +745,41 @@ def test_peaks_stage_isolated(P, case, prec):
     ph.close()
 
 
+@pytest.mark.parametrize("dt", ["f32", "u16"])
+@pytest.mark.parametrize("sep,cw", [(0, 1), (1, 0), (3, 3), (2, 5)])
+def test_peaks_of_equal_values(P, sep, cw, dt):
+    """few distinct values, so that most maxima are ties, and saturated pixels
+    in the tiles' corners and halos; the delta kernel on a flat background
+    makes every value exact.  Frames of whole tiles and of odd size."""
+    for W, H in ((192, 192), (131, 77), (40, 3)):
+        _say("equal peaks case", sep, cw, dt, W, H)
+        rng = np.random.default_rng(W * 10 + sep)
+        img = 500.0 + 100.0 * rng.integers(0, 4, (H, W))
+        img[rng.random((H, W)) < 0.01] = 3000.0
+        for y in (0, 63, 64, 66, 67, 127):
+            for x in (0, 63, 64, 66, 67, 128):
+                if y < H and x < W:
+                    img[y, x] = 3000.0
+        I = img.astype(np.uint16 if dt == "u16" else np.float32)
+        p = _params("c1", mesh_w=64, mesh_h=64, thresh=1.0, sat_level=3000.0)
+        K = np.ones((1, 1), np.float32)
+        nx, ny = -(-W // 64), -(-H // 64)
+        ph = P.Photometry([_dev(I)], p, K, capacity=W * H)
+        ph.set_grids(0, np.full((ny, nx), 500.0), np.full((ny, nx), 10.0))
+        ph.background(grid_given=True)
+        ph.peaks(sep, cw)
+        c = ph.results(0)["cat"]
+        M = img - 500.0
+        o = oracle.peaks(img, M, M, np.full((H, W), 10.0), 1.0, sep, cw, 3000.0)
+        for k in ("npix", "xmin", "xmax", "ymin", "ymax", "pmin", "flags"):
+            if k in o and k in c:
+                np.testing.assert_array_equal(c[k], o[k], err_msg=k)
+        assert len(c["x"]) == len(o["x"]) > 0
+        np.testing.assert_allclose(c["x"], o["x"], rtol=0, atol=1e-9)
+        np.testing.assert_allclose(c["y"], o["y"], rtol=0, atol=1e-9)
+        ph.close()
+
+
 # ----------------------------------------------------------------------------
 # growth curves on top-hat kernels, stage-isolated
 # ----------------------------------------------------------------------------
