@@ -144,7 +144,7 @@ int detect_tiles_per_cu(bool f64, int rad, int mesh_w);
 void launch_merge(const DetWork& wk, int conn, int minarea, int persist_blocks, hipStream_t s);
 void launch_catalog(const DetWork& wk, const CatOut& cat, int minarea, int persist_blocks, int32_t* comp_status,
                     hipStream_t s);
-void launch_seg(const DetWork& wk, int f, int64_t npx, hipStream_t s);
+void launch_seg(const DetWork& wk, hipStream_t s);
 void launch_peaks(const DetWork& wk, const DetArgs* args, const CatOut& cat, int32_t* comp_status, bool f64, int sep,
                   int cwin, int kw, int kh, int persist_blocks, const void* taps, const PsfFrame* pf,
                   int nmodes, int bin, int mesh_w, int xcd_cus, hipStream_t s);

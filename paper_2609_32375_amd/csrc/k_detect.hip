@@ -1207,29 +1207,30 @@ __global__ __launch_bounds__(256) void k_write_catalog(DetWork wk, CatOut cat, i
     }
 }
 
-// per-pixel labels: piece index -> root -> label (-1 dropped, 0 background)
-__global__ __launch_bounds__(256) void k_seg_finalize(DetWork wk, int f) {
+// per-pixel labels: piece index -> root -> label (-1 dropped, 0 background).
+// One workgroup per tile, a lane per column, over the tiles of all frames that
+// have a label map: a launch per frame, with a division and a tile lookup per
+// pixel, took 29 us for six frames of 0.04 to 1 MP, one launch 10 us.
+__global__ __launch_bounds__(256) void k_seg_finalize(DetWork wk) {
     if (wk.counters[1] != 0u) return;
+    const int gt = xcd_item(blockIdx.x, (wk.total_tiles + kXcds - 1) / kXcds);
+    if (gt >= wk.total_tiles) return;
+    const int f = frame_of_wave(wk.nframes, gt, [&](int i) { return wk.desc[i].tile_base; });
     const FrameDesc& d = wk.desc[f];
-    gi32_t* seg = (gi32_t*)d.seg;
-    const int64_t npx = (int64_t)d.W * d.H;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npx;
-         p += (int64_t)gridDim.x * blockDim.x) {
-        const int v = seg[p];
-        if (v < 0) {
-            seg[p] = 0;
-            continue;
-        }
-        const int y = (int)(p / d.W), x = (int)(p - (int64_t)y * d.W);
-        const int gt = d.tile_base + (y / kTile) * d.ntx + x / kTile;
-        const TileInfo T = wk.tiles[gt];
-        if (T.base < 0) {
-            seg[p] = 0;
-            continue;
-        }
-        const int id = T.base + v;
-        seg[p] = wk.label[wk.root[id]];
-    }
+    if (!d.seg) return;
+    const int lt = gt - d.tile_base, x = lt % d.ntx * kTile + (threadIdx.x & 63);
+    const int y0 = lt / d.ntx * kTile + 16 * (threadIdx.x >> 6), n = min(16, d.H - y0);
+    if (x >= d.W || n <= 0) return;
+    const int base = wk.tiles[gt].base;
+    gi32_t* seg = (gi32_t*)d.seg + (int64_t)y0 * d.W + x;
+    int v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = k < n ? seg[(int64_t)k * d.W] : -1;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = v[k] < 0 || base < 0 ? -1 : wk.root[base + v[k]];
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+        if (k < n) seg[(int64_t)k * d.W] = v[k] < 0 ? 0 : wk.label[v[k]];
 }
 
 // ---------------------------------------------------------------------------
@@ -1893,9 +1894,9 @@ void launch_catalog(const DetWork& wk, const CatOut& cat, int minarea, int persi
     k_write_catalog<<<persist_blocks, 256, 0, s>>>(wk, cat, minarea, comp_status);
 }
 
-void launch_seg(const DetWork& wk, int f, int64_t npx, hipStream_t s) {
-    int blocks = (int)std::min<int64_t>((npx + 255) / 256, 16384);
-    k_seg_finalize<<<blocks, 256, 0, s>>>(wk, f);
+void launch_seg(const DetWork& wk, hipStream_t s) {
+    const int grid = (wk.total_tiles + kXcds - 1) / kXcds * kXcds;
+    k_seg_finalize<<<grid, 256, 0, s>>>(wk);
 }
 
 // descriptor and argument upload (kernel arguments -> workspace)

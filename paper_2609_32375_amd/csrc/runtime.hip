@@ -821,8 +821,9 @@ static gp_status detect_run(gp_ctx* ctx, const gp_frame* frames, int32_t nframes
     HIP_TRY(hipGetLastError());
     if (seg) {
         ProfScope ps(ctx, s, "seg", prof);
-        for (int f = 0; f < nframes; ++f)
-            if (seg[f]) launch_seg(wk, f, (int64_t)frames[f].width * frames[f].height, s);
+        bool any = false;
+        for (int f = 0; f < nframes; ++f) any |= seg[f] != nullptr;
+        if (any) launch_seg(wk, s);
     }
     HIP_TRY(hipGetLastError());
     return GP_OK;
