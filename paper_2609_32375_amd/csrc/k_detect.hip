@@ -209,10 +209,9 @@ struct RunAcc<double> {
 // RAD >= 0: square rank-one kernel of radius RAD applied as two 1-D passes
 // (taps in registers, fully unrolled); RAD < 0: any kernel, applied densely.
 // FP32, radius 1..2, row cubics of at most 4 pieces: under 32 KB of LDS, and
-// the registers fit 96 without spills, so five workgroups per CU (radius 2:
-// 9.56 -> 8.43 ms on the 64-frame batch).  Radius 4 fits too but its code
-// under that limit was slower (1.77 -> 1.94 ms on a 12300^2 frame): it keeps
-// four workgroups per CU.
+// with 96 registers (two spilled) five workgroups per CU (radius 2, when five
+// first fitted: 9.56 -> 8.43 ms on the 64-frame batch, now 7.17).  Radius 4
+// needs 33 KB and keeps four.
 template <typename Real, int RAD, int NIX>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu((NIX <= 4 && sizeof(Real) == 4 && RAD >= 1 && RAD <= 2) ? 5 : 1))) void
@@ -1210,7 +1209,7 @@ __global__ __launch_bounds__(256) void k_write_catalog(DetWork wk, CatOut cat, i
 // per-pixel labels: piece index -> root -> label (-1 dropped, 0 background).
 // One workgroup per tile, a lane per column, over the tiles of all frames that
 // have a label map: a launch per frame, with a division and a tile lookup per
-// pixel, took 29 us for six frames of 0.04 to 1 MP, one launch 10 us.
+// pixel, took 29 us for six frames of up to 1.6 MP, one launch 10 us.
 __global__ __launch_bounds__(256) void k_seg_finalize(DetWork wk) {
     if (wk.counters[1] != 0u) return;
     const int gt = xcd_item(blockIdx.x, (wk.total_tiles + kXcds - 1) / kXcds);
