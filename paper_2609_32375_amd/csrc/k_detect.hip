@@ -15,7 +15,9 @@
 //  k_merge_records adds every non-root piece into its root record and sets
 //                  the first-pixel bit of every component with
 //                  npix >= minarea in a per-frame bitmap.
-//  k_popc_scan     prefix sums of the bitmap's popcounts -> label = rank of
+//  k_merge_sums    the pieces' sums into their roots' (the second pass of the
+//                  merge), and in the same launch the
+//  popc_scan       prefix sums of the bitmap's popcounts -> label = rank of
 //                  the first pixel in raster order.
 //  k_write_catalog moment normalisation (FP64), catalogue rows and the
 //                  per-frame object counts and status.
@@ -1000,40 +1002,6 @@ __global__ __launch_bounds__(256) void k_merge_records(DetWork wk, int minarea) 
     }
 }
 
-// Merge, pass 2: every piece (the root too) moves its sums to the root's tile
-// origin and adds them into the root's accumulators, each term rounded to the
-// component's quantum for that sum.  The bounds are exact integers known
-// after pass 1: max |M| times the pixel count times the extent of the
-// bounding box about the root's origin (X, Y) to the power of the sum's
-// coordinates, and the pixel count times the same for the unit-weight sums.
-__global__ __launch_bounds__(256) void k_merge_sums(DetWork wk) {
-    if (wk.counters[1] != 0u) return;
-    const int total = min((int)wk.counters[0], wk.rec_cap);
-    for (int id = blockIdx.x * blockDim.x + threadIdx.x; id < total; id += gridDim.x * blockDim.x) {
-        const int r = wk.root[id];
-        CompRec& R = wk.recs[r];
-        const CompRec& S = wk.recs[id];
-        const double ox = (double)(S.x0 - R.x0), oy = (double)(S.y0 - R.y0);
-        const double X = (double)(max(abs(R.xmin - R.x0), abs(R.xmax - R.x0)) + 1);
-        const double Y = (double)(max(abs(R.ymin - R.y0), abs(R.ymax - R.y0)) + 1);
-        const double np = (double)R.cnpix;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const double* s = S.s + 6 * h;
-            const double b0 = (h == 0 ? (double)__uint_as_float(R.camax) : 1.0) * np;
-            const double c[6] = {s[0],
-                                 s[1] + ox * s[0],
-                                 s[2] + oy * s[0],
-                                 s[3] + 2.0 * ox * s[1] + ox * ox * s[0],
-                                 s[4] + 2.0 * oy * s[2] + oy * oy * s[0],
-                                 s[5] + ox * s[2] + oy * s[1] + ox * oy * s[0]};
-            const double b[6] = {b0, b0 * X, b0 * Y, b0 * X * X, b0 * Y * Y, b0 * X * Y};
-#pragma unroll
-            for (int z = 0; z < 6; ++z) unsafeAtomicAdd(&R.acc[6 * h + z], quantize(c[z], quantum_exp(b[z])));
-        }
-    }
-}
-
 // Ranks of the bitmap's bits.  k_popc_scan: each workgroup takes kScanChunk
 // consecutive 1024-bit blocks, counts their bits and writes the exclusive
 // prefix of the counts within the chunk to blockcnt; the chunk's total goes to
@@ -1062,8 +1030,8 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* ws, ui
     return off + incl - x;
 }
 
-__global__ __launch_bounds__(256) void k_popc_scan(const uint32_t* __restrict__ bm, uint32_t* blockcnt,
-                                                   uint32_t* chunksum, int nb) {
+__device__ __forceinline__ void popc_scan(const uint32_t* __restrict__ bm, uint32_t* blockcnt, uint32_t* chunksum,
+                                          int nb, int chunk) {
     static_assert(kScanChunk == 512, "four wavefronts of 16 x 64 lanes x 8 words per block");
     __shared__ uint32_t cnt[kScanChunk];
     __shared__ uint32_t ws[4];
@@ -1072,8 +1040,8 @@ __global__ __launch_bounds__(256) void k_popc_scan(const uint32_t* __restrict__ 
     // eight 16-byte words) per load, all 16 loads in flight; eight lanes
     // reduce each block
     {
-        const uint4* src = (const uint4*)bm + (size_t)blockIdx.x * kScanChunk * 8;
-        const int nvec = min(kScanChunk, nb - (int)blockIdx.x * kScanChunk) * 8;
+        const uint4* src = (const uint4*)bm + (size_t)chunk * kScanChunk * 8;
+        const int nvec = min(kScanChunk, nb - chunk * kScanChunk) * 8;
         uint4 q[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -1090,13 +1058,59 @@ __global__ __launch_bounds__(256) void k_popc_scan(const uint32_t* __restrict__ 
         }
     }
     __syncthreads();
-    const int b0 = blockIdx.x * kScanChunk + 2 * tid;
+    const int b0 = chunk * kScanChunk + 2 * tid;
     const uint32_t v0 = (b0 < nb) ? cnt[2 * tid] : 0u, v1 = (b0 + 1 < nb) ? cnt[2 * tid + 1] : 0u;
     uint32_t tot;
     const uint32_t ex = block_excl_scan(v0 + v1, ws, &tot);
     if (b0 < nb) blockcnt[b0] = ex;
     if (b0 + 1 < nb) blockcnt[b0 + 1] = ex + v0;
-    if (tid == 0) chunksum[blockIdx.x] = tot;
+    if (tid == 0) chunksum[chunk] = tot;
+}
+
+__global__ __launch_bounds__(256) void k_popc_scan(const uint32_t* __restrict__ bm, uint32_t* blockcnt,
+                                                   uint32_t* chunksum, int nb) {
+    popc_scan(bm, blockcnt, chunksum, nb, blockIdx.x);
+}
+
+// Merge, pass 2: every piece (the root too) moves its sums to the root's tile
+// origin and adds them into the root's accumulators, each term rounded to the
+// component's quantum for that sum.  The bounds are exact integers known
+// after pass 1: max |M| times the pixel count times the extent of the
+// bounding box about the root's origin (X, Y) to the power of the sum's
+// coordinates, and the pixel count times the same for the unit-weight sums.
+// The ranks' scan needs pass 1 only, so its workgroups, the first nchunks, are
+// part of the same launch (a launch of its own cost a small frame 4 us).
+__global__ __launch_bounds__(256) void k_merge_sums(DetWork wk, int nchunks) {
+    if ((int)blockIdx.x < nchunks) {
+        popc_scan(wk.bitmap, wk.blockcnt, wk.chunksum, wk.total_blocks, blockIdx.x);
+        return;
+    }
+    if (wk.counters[1] != 0u) return;
+    const int total = min((int)wk.counters[0], wk.rec_cap);
+    for (int id = (blockIdx.x - nchunks) * blockDim.x + threadIdx.x; id < total;
+         id += (gridDim.x - nchunks) * blockDim.x) {
+        const int r = wk.root[id];
+        CompRec& R = wk.recs[r];
+        const CompRec& S = wk.recs[id];
+        const double ox = (double)(S.x0 - R.x0), oy = (double)(S.y0 - R.y0);
+        const double X = (double)(max(abs(R.xmin - R.x0), abs(R.xmax - R.x0)) + 1);
+        const double Y = (double)(max(abs(R.ymin - R.y0), abs(R.ymax - R.y0)) + 1);
+        const double np = (double)R.cnpix;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const double* s = S.s + 6 * h;
+            const double b0 = (h == 0 ? (double)__uint_as_float(R.camax) : 1.0) * np;
+            const double c[6] = {s[0],
+                                 s[1] + ox * s[0],
+                                 s[2] + oy * s[0],
+                                 s[3] + 2.0 * ox * s[1] + ox * ox * s[0],
+                                 s[4] + 2.0 * oy * s[2] + oy * oy * s[0],
+                                 s[5] + ox * s[2] + oy * s[1] + ox * oy * s[0]};
+            const double b[6] = {b0, b0 * X, b0 * Y, b0 * X * X, b0 * Y * Y, b0 * X * Y};
+#pragma unroll
+            for (int z = 0; z < 6; ++z) unsafeAtomicAdd(&R.acc[6 * h + z], quantize(c[z], quantum_exp(b[z])));
+        }
+    }
 }
 
 // Every catalogue workgroup scans the chunk totals into LDS itself: a batch
@@ -1882,10 +1896,8 @@ void launch_detect_tiles(const DetWork& wk, const DetArgs* args, bool f64, int r
 void launch_merge(const DetWork& wk, int conn, int minarea, int persist_blocks, hipStream_t s) {
     k_merge_edges<<<(wk.total_tiles + 3) / 4, 256, 0, s>>>(wk, conn);
     k_merge_records<<<persist_blocks, 256, 0, s>>>(wk, minarea);
-    k_merge_sums<<<persist_blocks, 256, 0, s>>>(wk);
-    const int nb = wk.total_blocks;
-    const int nchunks = (nb + kScanChunk - 1) / kScanChunk;
-    k_popc_scan<<<nchunks, 256, 0, s>>>(wk.bitmap, wk.blockcnt, wk.chunksum, nb);
+    const int nchunks = (wk.total_blocks + kScanChunk - 1) / kScanChunk;
+    k_merge_sums<<<nchunks + persist_blocks, 256, 0, s>>>(wk, nchunks);
 }
 
 void launch_catalog(const DetWork& wk, const CatOut& cat, int minarea, int persist_blocks,
