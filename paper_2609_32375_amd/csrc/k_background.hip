@@ -54,7 +54,7 @@ struct MeshShared {
     static constexpr bool kInt = sizeof(T) == 2;
     T val[NT * PPT];
     word16_t start[NB / 2 + 1];
-    double w1[NT / 64], wh[NT / 64], wl[NT / 64];
+    double w1[NT / 64], wu[NT / 64], wh[NT / 64], wl[NT / 64];
     uint32_t wc[NT / 64];
     float wmin[NT / 64], wmax[NT / 64];
     float lo, scale, mid;
@@ -94,10 +94,14 @@ __device__ __forceinline__ double wave_total(double v) {
 //
 // The places inside a bin follow the order of the LDS atomics, so every sum
 // is made exact, hence independent of that order: uint16 values give integer
-// sums below 2^53; a float's (v - c) is rounded to a multiple g of 2^-38 of
-// the mesh's range, its square split at a multiple q of 2^-38 of the squared
-// range into a coarse and a fine part whose sums both stay below 2^53 units
-// (16384 pixels).  A mesh gives bit-identical results wherever it runs.
+// sums below 2^53; a float's (v - c) and its square are each taken as a
+// multiple of 2^-38 and the rest as a multiple of 2^-76 of the range (of its
+// square), whose sums all stay below 2^53 units (16384 pixels).  A value so
+// loses less than in FP64 sums of plain products; where sigma has fallen
+// 2^20 times below that range (a no-data value among the pixels was clipped),
+// or the mean lies 2^10 sigmas from c, the survivors are summed anew about
+// their median, in units of their own range.  A mesh gives bit-identical
+// results wherever it runs.
 //
 // Bound by latency: a mesh of 64^2 (128^2) float pixels takes about 6000
 // (8000) cycles to arrive, 7000 (15000) for the histogram's LDS atomics, 4000
@@ -227,26 +231,33 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
     }
     // 3. group by bin: (bin, place inside it) of every pixel, the sums of all
     //    pixels, bin starts, store.  cs: a value of the mesh near the sky
-    //    level; mg, mq: adding and taking off 1.5 * 2^52 units rounds to a
-    //    whole number of units.
-    const double cs = (double)sh.mid;
-    int ex;
-    (void)frexp(fmax((double)mx - cs, cs - (double)mn), &ex);
-    const double mg = ldexp(1.5, ex - 38 + 52), mq = ldexp(1.5, 2 * ex - 38 + 52);
-    auto accum = [&](float x, double& s1, double& sq, double& sl) __attribute__((always_inline)) {
-        double e = (double)x - cs;
+    //    level; mg, mq and ng, nq, 2^-38 of each: adding and taking off 1.5 *
+    //    2^52 units rounds to a whole number of units (all in scalar registers).
+    double cs = (double)lane_f(sh.mid, 0), mg, mq, ng, nq;
+    auto units = [&](double range) __attribute__((always_inline)) {
+        int ex;
+        (void)frexp(range, &ex);
+        ex = __builtin_amdgcn_readfirstlane(ex);
+        mg = lane_d(ldexp(1.5, ex - 38 + 52), 0);
+        mq = lane_d(ldexp(1.5, 2 * ex - 38 + 52), 0);
+        ng = lane_d(ldexp(1.5, ex - 76 + 52), 0);
+        nq = lane_d(ldexp(1.5, 2 * ex - 76 + 52), 0);
+    };
+    units(fmax((double)mx - cs, cs - (double)mn));
+    auto accum = [&](float x, double& s1, double& su, double& sq, double& sl) __attribute__((always_inline)) {
+        const double e = (double)x - cs;
         if (kInt) {
             s1 += e;
             sq = fma(e, e, sq);
         } else {
-            e = (e + mg) - mg;
-            const double hi = fma(e, e, mq) - mq;
-            s1 += e;
-            sq += hi;
-            sl += fma(e, e, -hi);
+            const double h1 = (e + mg) - mg, hq = fma(e, e, mq) - mq;
+            s1 += h1;
+            su += ((e - h1) + ng) - ng;
+            sq += hq;
+            sl += (fma(e, e, -hq) + nq) - nq;
         }
     };
-    double t1 = 0.0, th = 0.0, tl = 0.0;
+    double t1 = 0.0, tu = 0.0, th = 0.0, tl = 0.0;
     uint32_t pk[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
@@ -256,14 +267,18 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
             const uint32_t sft = (b & 1u) * 16u;
             const uint32_t old = atomicAdd((uint32_t*)&sh.start[b >> 1], 1u << sft);
             pk[k] = (b << 16) | ((old >> sft) & 0xffffu);
-            accum(v[k], t1, th, tl);
+            accum(v[k], t1, tu, th, tl);
         }
     }
     t1 = wave_total(t1);
     th = wave_total(th);
-    if (!kInt) tl = wave_total(tl);
+    if (!kInt) {
+        tu = wave_total(tu);
+        tl = wave_total(tl);
+    }
     if (lane == 0) {
         sh.w1[wv] = t1;
+        sh.wu[wv] = tu;
         sh.wh[wv] = th;
         sh.wl[wv] = tl;
     }
@@ -306,11 +321,13 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
     if (wv != 0) return;
     __builtin_amdgcn_s_setprio(3);   // one wavefront's chain of latencies from here on
     t1 = sh.w1[0];
+    tu = sh.wu[0];
     th = sh.wh[0];
     tl = sh.wl[0];
 #pragma unroll
     for (int i = 1; i < NW; ++i) {
         t1 += sh.w1[i];
+        tu += sh.wu[i];
         th += sh.wh[i];
         tl += sh.wl[i];
     }
@@ -335,12 +352,11 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
             sig = sqrt((double)num / (nd * nd));
             mean = (double)mn + (t1 + nd * (cs - (double)mn)) / nd;
         } else {
-            const double q1 = t1 / nd;
-            const double vv = (th + tl) / nd - q1 * q1;
-            mean = cs + q1;
-            sig = sqrt(vv > 0.0 ? vv : 0.0);
-            if (!(vv > 1e-12 * (q1 * q1))) {
-                // a rounding residue or a real spread?
+            double q1 = (t1 + tu) / nd, vv = (th + tl) / nd - q1 * q1;
+            bool flat = false;
+            // sigma below 2^-20 of the sums' range (mq: 1.5 * 2^14 of its
+            // square) or 2^-10 of the mean's distance from cs, or one value only
+            if (vv <= fmax(mq * (0x1p-54 / 1.5), 0x1p-20 * (q1 * q1))) {
                 float lmn = INFINITY, lmx = -INFINITY;
                 for (int i = pL + lane; i < pH; i += 64) {
                     const float x = (float)sh.val[i];
@@ -349,8 +365,25 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
                         lmx = fmaxf(lmx, x);
                     }
                 }
-                if (wave_min(lmn) == wave_max(lmx)) sig = 0.0;
+                lmn = wave_min(lmn);
+                lmx = wave_max(lmx);
+                flat = lmn == lmx;
+                cs = (double)lane_f(fminf(fmaxf(iters > 0 ? med_h : (float)(cs + q1), lmn), lmx), 0);
+                units(fmax((double)lmx - cs, cs - (double)lmn));
+                t1 = tu = th = tl = 0.0;
+                for (int i = pL + lane; i < pH; i += 64) {
+                    const float x = (float)sh.val[i];
+                    if (x >= L && x < H) accum(x, t1, tu, th, tl);
+                }
+                t1 = wave_total(t1);
+                tu = wave_total(tu);
+                th = wave_total(th);
+                tl = wave_total(tl);
+                q1 = (t1 + tu) / nd;
+                vv = (th + tl) / nd - q1 * q1;
             }
+            mean = cs + q1;
+            sig = vv > 0.0 && !flat ? sqrt(vv) : 0.0;
         }
         if (iters == 0) sig0 = sig;
         // the median: the bin of its rank (bins start at rising positions),
@@ -505,7 +538,7 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
         const int bL = mesh_bin<NB>(Ln, blo, bscale), bH = mesh_bin<NB>(Hn, blo, bscale);
         const int sL = start[bL], sH = start[bH], eH = start[bH + 1];
         const int nl = (int)start[bL + 1] - pL, run = nl + pH - sH;
-        double s1 = 0.0, sq = 0.0, sl = 0.0;
+        double s1 = 0.0, su = 0.0, sq = 0.0, sl = 0.0;
         int low = 0, gone = 0;
         constexpr int U = 4;   // values per lane in flight
         for (int i0 = 0; i0 < run; i0 += 64 * U) {
@@ -526,7 +559,7 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
                 if ((bl | bh) == 0ull) continue;
                 low += __popcll(bl);
                 gone += __popcll(bl | bh);
-                if (lo || hi) accum(x[u], s1, sq, sl);
+                if (lo || hi) accum(x[u], s1, su, sq, sl);
             }
         }
         if (gone == 0 || gone == ncur) {
@@ -535,7 +568,10 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
         }
         t1 -= wave_total(s1);
         th -= wave_total(sq);
-        if (!kInt) tl -= wave_total(sl);
+        if (!kInt) {
+            tu -= wave_total(su);
+            tl -= wave_total(sl);
+        }
         ncur -= gone;
         rank0 += low;
         L = Ln;

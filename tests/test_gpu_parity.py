@@ -156,6 +156,69 @@ def test_mesh_statistics_at_the_edges_of_the_launch_shapes(P, mw, mh, dt):
     ph.close()
 
 
+def _exact_mesh(v, p):
+    """(mean or mode, sigma, passes, largest |survivor|) of one mesh from
+    correctly rounded sums (math.fsum)"""
+    v = v.astype(np.float64).ravel()
+    sig0, it = None, 0
+    while True:
+        n = v.size
+        mean = math.fsum(v) / n
+        sig = math.sqrt(math.fsum((v - mean) ** 2) / n) if v.min() < v.max() else 0.0
+        sig0 = sig if sig0 is None else sig0
+        med = float(np.median(v))
+        if it >= p.max_iter:
+            break
+        keep = np.abs(v - med) <= p.clip_sigma * sig
+        it += 1
+        if keep.all() or not keep.any():
+            break
+        v = v[keep]
+    back = mean if abs(sig - sig0) < p.crowd_tol * sig0 else p.mode_a * med - p.mode_b * mean
+    return back, sig, it, np.abs(v).max()
+
+
+@pytest.mark.parametrize("m", [32, 64, 90, 128])
+def test_float_mesh_sums_lose_nothing_to_outliers(P, m):
+    """Meshes whose pixels span many decades: stars 6e4 times the sky's sigma on
+    a subtracted sky, a 1e7 star on a quiet sky, and no-data values that are
+    clipped away: none of it reaches the mean or the sigma of the survivors."""
+    rng = np.random.default_rng(m)
+    n = m * m
+    sky = lambda c, s: c + s * rng.standard_normal(n)
+    sub, quiet, far, low, two = sky(0.0, 1.0), sky(1000.0, 0.01), sky(500.0, 7.0), sky(250.0, 5.0), sky(90.0, 2.0)
+    k = n // 50
+    sub[:k] += 6e4 * rng.random(k) ** 3
+    quiet[0] = 1e7
+    far[0] = 1e20
+    low[:3] = -3.4028234663852886e38
+    two[:2] = -1e30, 1e12
+    img = np.concatenate([rng.permutation(b).reshape(m, m) for b in (sub, quiet, far, low, two)], axis=1)
+    img = np.ascontiguousarray(img.astype(np.float32))
+    p = _params("c1", mesh_w=m, mesh_h=m, mesh_filter=1)
+    ph = P.Photometry([_dev(img)], p, p.kernel(), capacity=64)
+    ph.background()
+    g = ph.grids(0)
+    ph.background()   # (another order of the values inside the bins)
+    h = ph.grids(0)
+    for j in range(5):
+        back, sig, it, big = _exact_mesh(img[:, j * m:(j + 1) * m], p)
+        # The mean: its sum's terms are whole to 2^-76 of a range at most 2^20
+        # sigmas, and a few roundings of values of the survivors' size follow;
+        # the mode multiplies that by 2.5 + 1.5.  The variance: terms whole to
+        # 2^-76 of that range squared, and a cancellation of at most 2^20
+        # roundings; sigma loses half of it.
+        tb = 4.0 * (2.0 ** -50 * big + 2.0 ** -55 * sig)
+        ts = 2.0 ** -36 + 2.0 ** -31
+        eb, es = abs(g["back_raw"][0, j] - back), abs(g["rms_raw"][0, j] - sig) / sig
+        _say("mesh", m, j, "back", back, eb, "of", tb, "sigma", sig, es, "of", ts, "passes", it)
+        assert g["iters"][0, j] == it
+        assert eb <= tb and es <= ts
+    for k in ("back_raw", "rms_raw", "iters"):
+        np.testing.assert_array_equal(g[k], h[k])
+    ph.close()
+
+
 def _structured_meshes_u16(m, seed):
     """uint16 meshes (4 x 3 of m x m) for the integer statistics kernel: the
     float structured set rounded and clipped (ties, a bright source over a
