@@ -40,6 +40,7 @@ namespace gpk {
 // workgroups and the traffic take the rest: horizontal 260 -> 222 us, vertical
 // 445 -> 326 from blocks of 8 outputs whose window was moved by copies, with
 // uniform row addresses, stores of 64 neighbours and a shorter C.
+
 // the frame of a flattened workgroup index: base[] ascending from 0, so the
 // bases <= item form a prefix (one ballot per 64 frames; all lanes active)
 __device__ __forceinline__ int cv_frame_of(const int32_t* __restrict__ base, int n, int item) {
@@ -360,6 +361,27 @@ __device__ __forceinline__ void cv_hbits(const uint64_t* bits, const double* k, 
     }
 }
 
+// The same sum at one column pc of the tile: a tap is added or an exact zero.
+__device__ __forceinline__ double cv_hpixel(const uint64_t* bits, int pc, const double* k, int taps) {
+    typedef const uint32_t __attribute__((may_alias)) word32_t;
+    word32_t* words = reinterpret_cast<word32_t*>(bits);
+    double acc = 0.0;
+    for (int t0 = 0; t0 < taps; t0 += 32) {
+        // 32 bits from bit pc + t0 on
+        const int o = pc + t0;
+        const uint64_t w = words[o >> 5] | (uint64_t)words[(o >> 5) + 1] << 32;
+        const uint32_t v = (uint32_t)(w >> (o & 31));
+        auto add = [&](int b) __attribute__((always_inline)) { acc += (v >> b) & 1u ? k[t0 + b] : 0.0; };
+        if (taps - t0 >= 32) {
+#pragma unroll
+            for (int b = 0; b < 32; ++b) add(b);
+        } else {
+            for (int b = 0; b < taps - t0; ++b) add(b);
+        }
+    }
+    return acc;
+}
+
 // noise map of a dark-subtracted frame in ADU from B.  FP64 maps: the
 // formula as written, in FP64.  FP32 maps: R^2 = max(B, 0) / g + (rn^2 +
 // dark t) / g^2 from the host's FP64 constants, rounded to FP32, and its
@@ -449,8 +471,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     if (FIRST && fill) {
         // C: validity bits of the tile's neighbourhood (all set in the rows
         // whose reach holds no invalid pixel)
-        uint64_t* bits = reinterpret_cast<uint64_t*>(cv_dyn + conv_v_data_bytes(a.lx, a.ly, sizeof(Real) == 8));
-        const int lane = c;
+        uint64_t* bits = reinterpret_cast<uint64_t*>(cv_dyn + conv_v_data_bytes(a.ly, sizeof(Real) == 8));
+        CvFew* list = reinterpret_cast<CvFew*>(cv_dyn);
         if (d.dtype == kDtypeU16) cv_bits<uint16_t>(d, mask, sat, xc0 - hx, y0 - hy, a.lx, nrows, act, bits);
         else cv_bits<float>(d, mask, sat, xc0 - hx, y0 - hy, a.lx, nrows, act, bits);
         if (threadIdx.x == 0) ninv = 0;
@@ -467,58 +489,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             const int at = n ? atomicAdd(&ninv, n) : 0;
             if (at + n <= kCvFew) {
                 // few so far: their places and A into the list
-                CvFew* list = reinterpret_cast<CvFew*>(cv_dyn + cv_lut_bytes(a.lx));
                 int o = at;
 #pragma unroll
                 for (int q = 0; q < kCvN; ++q)
                     if ((inv >> q) & 1u) list[o++] = CvFew{s0[q], (rb + q) * kCvCols + c, 0};
             }
-            double* lut = reinterpret_cast<double*>(cv_dyn);
-            for (int t = 0; t < cv_pad(a.lx) / 8; ++t) {
-                double v = 0.0;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v += (threadIdx.x >> i) & 1u ? a.kx[8 * t + i] : 0.0;
-                lut[256 * t + threadIdx.x] = v;
-            }
         }
         __syncthreads();
         few = ninv <= kCvFew;
         if (few) {
-            // one pixel per wavefront at a time, its rows over the lanes
-            const double* lut = reinterpret_cast<const double*>(cv_dyn);
-            const CvFew* list = reinterpret_cast<const CvFew*>(cv_dyn + cv_lut_bytes(a.lx));
-            int64_t none = 0;
-            double ky[(kConvTapsPad + 63) / 64];
-#pragma unroll
-            for (int t = 0; t < (kConvTapsPad + 63) / 64; ++t) ky[t] = lane + 64 * t < a.ly ? a.ky[lane + 64 * t] : 0.0;
-            for (int i = g; i < ninv; i += 4) {
-                const int pos = __builtin_amdgcn_readfirstlane(list[i].pos);
+            // C at the listed pixels: a thread per row of a pixel's window,
+            // then a lane per pixel, with the sums in the order (and stored
+            // in the precision) of the sums over the tile, so that a fill
+            // value has the same bits whatever else the tile holds
+            Real* hrow = reinterpret_cast<Real*>(list + kCvFew);
+            for (int e = threadIdx.x; e < ninv * a.ly; e += blockDim.x) {
+                const int i = e / a.ly, r = e - i * a.ly, pos = list[i].pos;
                 const int pr = pos / kCvCols, pc = pos - pr * kCvCols;
-                double cs = 0.0;
-#pragma unroll
-                for (int u = 0; u < (kConvTapsPad + 63) / 64; ++u) {
-                    if (64 * u >= a.ly) break;
-                    // (lanes past the last tap repeat its row, for a zero tap)
-                    const uint64_t* bw = bits + (pr + min(lane + 64 * u, a.ly - 1)) * kCvBitWords;
-                    double h = 0.0;
-                    for (int t0 = 0; t0 < a.lx; t0 += 64) {
-                        const int wi = t0 / 64;
-                        const uint64_t v = pc ? (bw[wi] >> pc) | (bw[wi + 1] << (64 - pc)) : bw[wi];
-#pragma unroll
-                        for (int t = 0; t < 8; ++t)
-                            if (t0 + 8 * t < a.lx) h += lut[256 * (t0 / 8 + t) + (int)((v >> (8 * t)) & 255u)];
-                    }
-                    cs = fma(ky[u], (double)(Real)h, cs);
-                }
-                cs = wave_total_d(cs);
-                if (lane == 0) {
-                    double gv = 0.0;
-                    if (cs != 0.0) gv = list[i].a / cs;
-                    else ++none;
-                    outG[(int64_t)(y0 + pr) * d.W + xc0 + pc] = (Real)gv;
-                }
+                hrow[e] = (Real)cv_hpixel(bits + (pr + r) * kCvBitWords, pc, a.kx, a.lx);
             }
-            if (none) atomicAdd((unsigned long long*)unfilled, (unsigned long long)none);
+            __syncthreads();
+            if (threadIdx.x < ninv) {
+                const CvFew P = list[threadIdx.x];
+                const Real* h = hrow + threadIdx.x * a.ly;
+                double cs = 0.0;
+#pragma unroll 8
+                for (int r = 0; r < a.ly; ++r) cs = fma(a.ky[r], (double)h[r], cs);
+                double gv = 0.0;
+                if (cs != 0.0) gv = P.a / cs;
+                else atomicAdd((unsigned long long*)unfilled, 1ull);
+                const int pr = P.pos / kCvCols, pc = P.pos - pr * kCvCols;
+                outG[(int64_t)(y0 + pr) * d.W + xc0 + pc] = (Real)gv;
+            }
         } else {
             cv_hbits(bits, a.kx, cv_pad(a.lx), nrows, band);
             __syncthreads();
@@ -592,7 +594,7 @@ __global__ void k_conv_setup(CvChunk c, CvWork w) {
 
 template <typename Real>
 static hipError_t conv_t(int nframes, int htotal, int vtotal, const CvArgs& a, const CvWork& w, hipStream_t s) {
-    const size_t lh = conv_h_lds<Real>(), lv = conv_v_lds(a.lx, a.ly, sizeof(Real) == 8);
+    const size_t lh = conv_h_lds<Real>(), lv = conv_v_lds(a.ly, sizeof(Real) == 8);
     hipError_t e;
     const void* hk[2] = {(const void*)k_conv_h<Real>, (const void*)k_conv_h_fill<Real>};
     const void* vk[2] = {(const void*)k_conv_v<Real, true>, (const void*)k_conv_v<Real, false>};

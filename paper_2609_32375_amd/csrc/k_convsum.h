@@ -21,23 +21,19 @@ static_assert(kCvSeg == kCvSegPx && kCvCols == kCvTilePx && kCvRows == kCvTilePx
 constexpr int kCvBitWords = (kCvCols + kConvTapsPad + kCvT + 63) / 64;
 
 __host__ __device__ __forceinline__ int cv_pad(int n) { return (n + kCvT - 1) / kCvT * kCvT; }
-// A vertical workgroup's data: the band, or after A's sums the table of the
-// horizontal sums of 8 validity bits and the list of a few invalid pixels;
-// then the bits.
+// A vertical workgroup's data: the band, or after A's sums the list of a few
+// invalid pixels and the rows of their C; then the bits.
 struct CvFew {
     double a;
     int32_t pos, pad;
 };
-// Invalid pixels of a tile up to which C is formed at those pixels alone (a
-// wavefront each, about 2k cycles) instead of over the tile (about 20k cycles
-// of the workgroup's four): a masked 1031 x 777 frame with 7 such pixels in
-// most tiles and 72 in one column of them took 36.1 us for limits from 128
-// on, 32.6 for 48, 32.4 for 16.
+// Invalid pixels of a tile up to which C is formed at those pixels alone
+// instead of over the tile.
 constexpr int kCvFew = 48;
-__host__ __device__ __forceinline__ size_t cv_lut_bytes(int lx) { return (size_t)(cv_pad(lx) / 8) * 256 * 8; }
-__host__ __device__ __forceinline__ size_t conv_v_data_bytes(int lx, int ly, bool f64) {
-    const size_t band = (size_t)(kCvRows + cv_pad(ly)) * kCvCols * (f64 ? 8 : 4);
-    const size_t few = cv_lut_bytes(lx) + sizeof(CvFew) * kCvFew;
+__host__ __device__ __forceinline__ size_t conv_v_data_bytes(int ly, bool f64) {
+    const size_t real = f64 ? 8 : 4;
+    const size_t band = (size_t)(kCvRows + cv_pad(ly)) * kCvCols * real;
+    const size_t few = (sizeof(CvFew) + ly * real) * kCvFew;
     return band > few ? band : few;
 }
 
@@ -126,8 +122,8 @@ template <typename Real>
 inline size_t conv_h_lds() {
     return sizeof(Real) * (size_t)kHStage * kHRound<Real>;
 }
-inline size_t conv_v_lds(int lx, int ly, bool f64) {
-    return conv_v_data_bytes(lx, ly, f64) + (size_t)(kCvRows + cv_pad(ly)) * kCvBitWords * 8;
+inline size_t conv_v_lds(int ly, bool f64) {
+    return conv_v_data_bytes(ly, f64) + (size_t)(kCvRows + cv_pad(ly)) * kCvBitWords * 8;
 }
 
 }  // namespace gpk

@@ -32,7 +32,7 @@ template <typename Real>
 static void vertical(int ly) {
     const int rows = kCvRows + cv_pad(ly);
     const size_t band_bytes = (size_t)rows * kCvCols * sizeof(Real);
-    if (band_bytes > conv_v_data_bytes(1, ly, sizeof(Real) == 8) || band_bytes > conv_v_lds(1, ly, sizeof(Real) == 8)) abort();
+    if (band_bytes > conv_v_data_bytes(ly, sizeof(Real) == 8) || band_bytes > conv_v_lds(ly, sizeof(Real) == 8)) abort();
     Real* band = (Real*)guarded(band_bytes);
     for (int i = 0; i < rows * kCvCols; ++i) band[i] = (Real)((i * 37) % 1009);
     double k[kConvTapsPad] = {0.0};

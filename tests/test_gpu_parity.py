@@ -1166,6 +1166,55 @@ def test_background_conv_at_step_and_fill_edges(P, lx, ly, few, prec):
     cb2.close()
 
 
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("lx,ly,signed", [(1, 1, False), (3, 5, True), (9, 7, False), (13, 21, True), (31, 3, True), (3, 23, False)])
+def test_background_conv_fills_do_not_depend_on_the_tile(P, lx, ly, signed, prec):
+    """An invalid pixel's fill value, and with it every output only that pixel
+    reaches, has the same bits whether its 64 x 64 tile holds few invalid pixels
+    or many; so has the count of the unfillable ones.  Taps of both signs too,
+    whose sum over the valid pixels may come close to zero or be zero."""
+    W, H = 200, 150
+    _say("conv fill order", lx, ly, signed, prec)
+    rng = np.random.default_rng(100 * lx + ly)
+    I = (500.0 + 20.0 * rng.standard_normal((H, W))).astype(np.float32)
+    kx = (0.2 + rng.random(lx)).astype(np.float32)
+    ky = (0.2 + rng.random(ly)).astype(np.float32)
+    if signed:
+        # alternating pairs that cancel, and a remainder
+        kx = np.round(np.sign(np.cos(np.arange(lx) * np.pi)) * (1 + np.arange(lx) // 2) / 10.0, 1).astype(np.float32)
+    few = np.zeros((H, W), np.uint8)
+    many = np.zeros((H, W), np.uint8)
+    keep = np.zeros((H, W), bool)
+    hx, hy = lx // 2, ly // 2
+    for ty in range(0, H, 64):
+        for tx in range(0, W, 64):
+            x, y = tx + 12, ty + 13   # up to three neighbours in the upper left of a tile
+            for dx, dy in ((0, 0), (1, 0), (0, min(1, hy)))[: 1 + (tx + ty) // 64 % 3]:
+                if x + dx < W and y + dy < H:
+                    few[y + dy, x + dx] = 1
+            keep[max(y - hy, 0):y + hy + 2, max(x - hx, 0):x + hx + 2] = True
+    many |= few
+    y, x = np.mgrid[0:H, 0:W]
+    # the rest: the right of each tile, out of the first ones' sight and they out of its
+    many[(x % 64 >= 46) & (x % 64 < 56) & (y % 64 >= 40) & (y % 64 < 48)] = 1
+    reach = np.zeros((H, W), bool)
+    for yy, xx in zip(*np.nonzero(many & ~few)):
+        reach[max(yy - 2 * hy, 0):yy + 2 * hy + 1, max(xx - 2 * hx, 0):xx + 2 * hx + 1] = True
+    keep &= ~reach
+    out = []
+    for mask in (few, many):
+        cb = P.ConvBackground([_dev(I)], kx, ky, 1.5, 5.0, precision=prec)
+        cb.run([_dev(mask)])
+        torch.cuda.synchronize()
+        out.append((cb.back[0].cpu().numpy(), cb.rms[0].cpu().numpy(), int(cb.unfilled[0].item())))
+        cb.close()
+    assert keep.sum() > 30
+    for a, b in zip(out[0][:2], out[1][:2]):
+        np.testing.assert_array_equal(a[keep], b[keep])
+    if not signed:
+        assert out[0][2] == (few.sum() if lx == ly == 1 else 0)
+
+
 def test_background_conv_constant_frame_and_batch(P):
     """A constant frame comes back unchanged; a batch of frames (uint16 and
     float32, several sizes) equals per-frame calls bit for bit."""
