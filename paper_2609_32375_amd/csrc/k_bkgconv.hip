@@ -496,7 +496,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             }
         }
         __syncthreads();
-        few = ninv <= kCvFew;
+        few = ninv <= kCvFew && ninv * a.ly <= kCvFewRows;
         if (few) {
             // C at the listed pixels: a thread per row of a pixel's window,
             // then a lane per pixel, with the sums in the order (and stored

@@ -27,9 +27,16 @@ struct CvFew {
     double a;
     int32_t pos, pad;
 };
-// Invalid pixels of a tile up to which C is formed at those pixels alone
-// instead of over the tile.
-constexpr int kCvFew = 48;
+// C is formed at a tile's invalid pixels alone, instead of over the tile, up to
+// kCvFew of them whose windows hold up to kCvFewRows rows together: one thread
+// sums a row, so that is four rounds of the workgroup, and both ways' rounds
+// grow with the taps along x.  All 64 x 64 tiles of a masked 2048^2 frame, us a
+// pass alone / over the tile, FP32: 65 x 65 taps 137 / 157 for 4 pixels, 158 /
+// 164 for 16, 178 / 165 for 32; 129 x 129 264 / 307 for 4, 299 / 313 for 8, 359 /
+// 316 for 16; 33 x 21 123 / 126 for 48, 127 / 127 for 64; 9 x 9 108 / 112 for 48;
+// 5 x 129 (nearly no taps along x) 210 / 217 for 24, 225 / 219 for 48.  FP64:
+// 65 x 65 212 / 213 for 16, 129 x 129 477 / 463 for 8, 33 x 21 161 / 164 for 48.
+constexpr int kCvFew = 48, kCvFewRows = 1024;
 __host__ __device__ __forceinline__ size_t conv_v_data_bytes(int ly, bool f64) {
     const size_t real = f64 ? 8 : 4;
     const size_t band = (size_t)(kCvRows + cv_pad(ly)) * kCvCols * real;

@@ -1167,6 +1167,14 @@ def test_background_conv_at_step_and_fill_edges(P, lx, ly, few, prec):
 
 
 @pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("lx,ly,few", [(5, 21, 48), (5, 21, 49), (33, 65, 15), (33, 65, 16), (9, 129, 7), (9, 129, 8)])
+def test_background_conv_at_the_row_limit_of_single_fills(P, lx, ly, few, prec):
+    """both sides of the 48 pixels and of the 1024 window rows up to which
+    invalid pixels are filled one by one"""
+    test_background_conv_at_step_and_fill_edges(P, lx, ly, few, prec)
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "fp64"])
 @pytest.mark.parametrize("lx,ly,signed", [(1, 1, False), (3, 5, True), (9, 7, False), (13, 21, True), (31, 3, True), (3, 23, False)])
 def test_background_conv_fills_do_not_depend_on_the_tile(P, lx, ly, signed, prec):
     """An invalid pixel's fill value, and with it every output only that pixel
