@@ -58,6 +58,7 @@ struct MeshShared {
     uint32_t wc[NT / 64];
     float wmin[NT / 64], wmax[NT / 64];
     float lo, scale, mid;
+    uint32_t part[128];  // a large bin's parts (and an unused word per lane), or the values of one part
 };
 
 // Bins of a mesh: three quarters of them equal steps from lo on, the rest
@@ -83,6 +84,174 @@ __device__ __forceinline__ double wave_total(double v) {
     v += dpp_d<0x140>(v);   // 15 - lane of each 16
     return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
 }
+// order-preserving integers of a pixel's values
+template <typename T>
+__device__ __forceinline__ uint32_t mesh_image(float x) { return sizeof(T) == 2 ? (uint32_t)x : f2ord(x); }
+template <typename T>
+__device__ __forceinline__ float mesh_value(uint32_t z) { return sizeof(T) == 2 ? (float)z : ord2f(z); }
+
+// Of up to 64 values, one per lane (the lanes past m hold +inf): how many are
+// smaller than the lane's, and the one with j smaller ones (or, among equals,
+// fewer).
+__device__ __forceinline__ int wave_rank(float x, int m) {
+    int q = 0;
+    for (int i = 0; i < m; i += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q += lane_f(x, i + u) < x ? 1 : 0;
+    }
+    return q;
+}
+__device__ __forceinline__ float wave_kth(float x, int q, int m, int j) {
+    const int lane = threadIdx.x & 63;
+    uint64_t hit;
+    while ((hit = __ballot(lane < m && q == j)) == 0ull) --j;
+    return lane_f(x, __builtin_ctzll(hit));
+}
+
+// The values of rank j and j + 1 (+inf if there is none) of the m > 256 values
+// of a bin, by one wavefront.  A value that many of them share (masked,
+// clipped or saturated pixels) is tried first: a pass that counts it and the
+// smaller ones.  Else their range is split into 64 equal parts of the
+// order-preserving integers and the part that holds rank j counted out, until
+// it has at most 64 values: a pass for the range, and one or two for the parts,
+// where bisection takes 16 to 32.  The counts of the part that most of a few
+// probes fall into stay in registers (an LDS atomic costs 4 cycles for each
+// lane of the same address).  Called, not inlined: few meshes have such bins,
+// and its registers would cost all of them wavefronts.  With the bins from a
+// third of the sampled pixels, 2048^2 float in 128^2 meshes: 40% of the pixels
+// zero 329 us by bisection, now 27; 40% saturated 319, now 27; half zero and
+// the rest noise above zero (19 passes) 6867, now 224.
+template <typename T>
+using lds_t = __attribute__((address_space(3))) T;
+template <typename T>
+__device__ __attribute__((noinline)) float2 mesh_large_bin(const lds_t<T>* val, lds_t<uint32_t>* part, int m, int j) {
+    const int lane = threadIdx.x & 63;
+    // every value of the bin, four loads in flight
+    auto each = [&](auto&& f) __attribute__((always_inline)) {
+        int i = lane;
+        for (; i - lane + 256 <= m; i += 256) {
+            T x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = val[i + 64 * u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) f(mesh_image<T>((float)x[u]));
+        }
+        for (; i < m; i += 64) f(mesh_image<T>((float)val[i]));
+    };
+    // the most frequent of four probes among 64 of the values, if 9 or more share it
+    const auto frequent = [&](uint32_t z, uint32_t none) __attribute__((always_inline)) {
+        int most = 8;
+        uint32_t best = none;
+        for (int l = 0; l < 64; l += 16) {
+            const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)z, l);
+            const int c = __popcll(__ballot(z == q));
+            if (c > most) {
+                best = q;
+                most = c;
+            }
+        }
+        return best;
+    };
+    const uint32_t first = mesh_image<T>((float)val[lane]);
+    uint32_t a0 = 0u, a1 = ~0u;
+    int mm = m, before = 0;   // values in [a0, a1], of which the one of rank j is sought
+    const uint32_t shared = frequent(first, ~0u);
+    if (shared != ~0u) {
+        uint32_t n = 0u;   // smaller ones, equal ones << 16
+        each([&](uint32_t z) __attribute__((always_inline)) { n += z < shared ? 1u : z == shared ? 0x10000u : 0u; });
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) n += (uint32_t)__shfl_xor((int)n, d);
+        const int lt = __builtin_amdgcn_readfirstlane((int)(n & 0xffffu)), eq = __builtin_amdgcn_readfirstlane((int)(n >> 16));
+        if (j >= lt && j < lt + eq) {
+            a0 = a1 = shared;
+            j -= lt;
+            mm = eq;
+        }
+    }
+    while (a0 != a1) {
+        if (4 * mm > before) {
+            // (at first, and where the last parts hardly split the values: one
+            // value many times, or a range with few values at its ends)
+            uint32_t z0 = ~0u, z1 = 0u;
+            each([&](uint32_t z) __attribute__((always_inline)) {
+                z0 = min(z0, z >= a0 ? z : ~0u);
+                z1 = max(z1, z <= a1 ? z : 0u);
+            });
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) {
+                z0 = min(z0, (uint32_t)__shfl_xor((int)z0, o));
+                z1 = max(z1, (uint32_t)__shfl_xor((int)z1, o));
+            }
+            a0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)z0);
+            a1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)z1);
+        }
+        if (a0 == a1 || mm <= 64) break;
+        before = mm;
+        const int sft = max(0, 26 - __clz((int)(a1 - a0)));
+        const uint32_t probe = (first - a0) >> sft;   // (past the range: above 63)
+        const uint32_t hot = frequent(min(probe, 64u), 64u);
+        part[lane] = 0u;
+        wave_sync();
+        int mine = 0;
+        each([&](uint32_t z) __attribute__((always_inline)) {
+            const uint32_t q = (z - a0) >> sft;
+            const bool in = z >= a0 && z <= a1;
+            atomicAdd((uint32_t*)&part[in && q != hot ? q : 64u + lane], 1u);
+            mine += in && q == hot ? 1 : 0;
+        });
+        wave_sync();
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d);
+        const int c = (int)part[lane] + ((uint32_t)lane == hot ? mine : 0);
+        int incl = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(incl, d);
+            if (lane >= d) incl += y;
+        }
+        const int q = __builtin_ctzll(__ballot(incl > j));
+        mm = __builtin_amdgcn_readlane(c, q);
+        j -= __builtin_amdgcn_readlane(incl, q) - mm;
+        a0 += (uint32_t)q << sft;
+        a1 = min(a1, a0 + ((1u << sft) - 1u));
+        wave_sync();
+    }
+    float x1 = mesh_value<T>(a0), x2 = x1;
+    if (a0 != a1) {
+        part[64] = 0u;   // the number found so far
+        wave_sync();
+        each([&](uint32_t z) __attribute__((always_inline)) {
+            if (z >= a0 && z <= a1) part[atomicAdd((uint32_t*)&part[64], 1u)] = z;
+        });
+        wave_sync();
+        const float x = lane < mm ? mesh_value<T>(part[lane]) : INFINITY;
+        wave_sync();
+        const int q = wave_rank(x, mm);
+        x1 = wave_kth(x, q, mm, j);
+        if (j + 1 < mm) x2 = wave_kth(x, q, mm, j + 1);
+    }
+    if (j + 1 >= mm) {
+        // the next value lies above the part
+        x2 = INFINITY;
+        each([&](uint32_t z) __attribute__((always_inline)) { x2 = z > a1 ? fminf(x2, mesh_value<T>(z)) : x2; });
+        x2 = wave_min(x2);
+    }
+    return make_float2(x1, x2);
+}
+
+// the least of the lanes' values
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_least(float v) {
+    v = fminf(v, dpp_f<0xB1>(v));
+    v = fminf(v, dpp_f<0x4E>(v));
+    v = fminf(v, dpp_f<0x141>(v));
+    v = fminf(v, dpp_f<0x140>(v));
+    return fminf(fminf(lane_f(v, 0), lane_f(v, 16)), fminf(lane_f(v, 32), lane_f(v, 48)));
+}
+
 // One workgroup per mesh.  Whatever was clipped before, the surviving values
 // are always those of one interval [L, H).  The workgroup groups the values by
 // bin in LDS once (a histogram whose returned counts are the places inside a
@@ -113,9 +282,11 @@ __device__ __forceinline__ double wave_total(double v) {
 // 2048^2 in 64^2 meshes 40, now 22; 371 MP of uint16 1122, now 680.
 //
 // ONE: a one-frame call, whose descriptor comes with the launch (d1);
-// workgroup 0 stores it in the table for the launches that follow
+// workgroup 0 stores it in the table for the launches that follow.
+// (Registers for seven wavefronts per SIMD up to 8192 pixels: the float ones
+// spill three in the clipping loop for it.)
 template <typename T, int NT, int PPT, bool ONE>
-__global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc, FrameDesc d1, int nframes,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8192 ? 4 : 7))) void k_mesh_stats(FrameDesc* __restrict__ desc, FrameDesc d1, int nframes,
                                                    BkgArgs a) {
     using SH = MeshShared<T, NT, PPT>;
     constexpr bool kInt = SH::kInt;
@@ -170,9 +341,9 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
         }
     }
     // 2. the mesh's range, and the bins from 64 of its pixels (one per lane of
-    //    the first wavefront, at different heights): their median and the
-    //    16th percentile below it give the sky's level and width even where
-    //    stars cover half the mesh
+    //    the first wavefront, at different heights): the shortest interval with
+    //    a third of them gives the sky's level and width even where stars, or
+    //    masked or saturated pixels of one value, cover half the mesh
     float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
@@ -194,26 +365,37 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
         const uint64_t have = __ballot(s == s);   // (lane 0 always has its first pixel)
         s = wave_sort(s == s ? s : INFINITY, lane);
         const int m = __popcll(have);
-        const float q50 = lane_f(s, (m - 1) / 2), q16 = lane_f(s, (m - 1) / 6);
         constexpr float NC = (float)(NB - NB / 4);
-        float wd = q50 - q16;
+        const int third = (m - 1) / 3;
+        const float up = __shfl(s, min(lane + third, 63)), mid = __shfl(s, min(lane + third / 2, 63));
+        // (not one that reaches from pixels of one value to a few others)
+        const float wide = lane + third < m && up > mid && mid > s ? up - s : INFINITY;
+        const float least = wave_least(wide);
+        float q50 = lane_f(s, (m - 1) / 2);
+        float wd = 0.0f;
+        if (least < INFINITY) {
+            // (the shortest of 64 normal values: 0.4 to 0.9 sigma)
+            wd = 1.5f * least;
+            q50 = lane_f(s, __builtin_ctzll(__ballot(wide == least)) + third / 2);
+        }
         if (lane == 0) sh.mid = q50;
         if (kInt) {
             // steps of one unit where the sky's range leaves room for them:
             // such a bin holds one value
             wd = fmaxf(wd, 1.0f);
             if (lane == 0) {
-                sh.lo = floorf(q50 - 4.0f * wd);
-                sh.scale = fminf(1.0f, NC / (10.0f * wd));
+                sh.lo = floorf(q50 - 6.0f * wd);
+                sh.scale = fminf(1.0f, NC / (14.0f * wd));
             }
         } else if (lane == 0) {
             if (!(wd > 0.0f)) wd = fmaxf(fabsf(q50) * 0x1p-10f, 0x1p-100f);
-            sh.lo = q50 - 4.0f * wd;
-            sh.scale = NC / (10.0f * wd);
+            sh.lo = q50 - 6.0f * wd;
+            sh.scale = NC / (14.0f * wd);
         }
     }
     __syncthreads();
-    const float blo = sh.lo, bscale = sh.scale;
+    // (what all lanes share goes to scalar registers here and below)
+    const float blo = lane_f(sh.lo, 0), bscale = lane_f(sh.scale, 0);
     mn = sh.wmin[0];
     mx = sh.wmax[0];
 #pragma unroll
@@ -221,6 +403,8 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
         mn = fminf(mn, sh.wmin[i]);
         mx = fmaxf(mx, sh.wmax[i]);
     }
+    mn = lane_f(mn, 0);
+    mx = lane_f(mx, 0);
     if (mn == mx) {
         if (tid == 0) {
             d.back_raw[out_idx] = (double)mn;
@@ -233,7 +417,7 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
     //    pixels, bin starts, store.  cs: a value of the mesh near the sky
     //    level; mg, mq and ng, nq, 2^-38 of each: adding and taking off 1.5 *
     //    2^52 units rounds to a whole number of units (all in scalar registers).
-    double cs = (double)lane_f(sh.mid, 0), mg, mq, ng, nq;
+    double cs = lane_d((double)sh.mid, 0), mg, mq, ng, nq;
     auto units = [&](double range) __attribute__((always_inline)) {
         int ex;
         (void)frexp(range, &ex);
@@ -244,8 +428,7 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
         nq = lane_d(ldexp(1.5, 2 * ex - 76 + 52), 0);
     };
     units(fmax((double)mx - cs, cs - (double)mn));
-    auto accum = [&](float x, double& s1, double& su, double& sq, double& sl) __attribute__((always_inline)) {
-        const double e = (double)x - cs;
+    auto accum = [&](double e, double& s1, double& su, double& sq, double& sl) __attribute__((always_inline)) {
         if (kInt) {
             s1 += e;
             sq = fma(e, e, sq);
@@ -267,7 +450,7 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
             const uint32_t sft = (b & 1u) * 16u;
             const uint32_t old = atomicAdd((uint32_t*)&sh.start[b >> 1], 1u << sft);
             pk[k] = (b << 16) | ((old >> sft) & 0xffffu);
-            accum(v[k], t1, tu, th, tl);
+            accum((double)v[k] - cs, t1, tu, th, tl);
         }
     }
     t1 = wave_total(t1);
@@ -331,10 +514,16 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
         th += sh.wh[i];
         tl += sh.wl[i];
     }
+    t1 = lane_d(t1, 0);
+    tu = lane_d(tu, 0);
+    th = lane_d(th, 0);
+    tl = lane_d(tl, 0);
     // 4. the clipping loop (one wavefront; every branch below is uniform)
     const int half = lane >> 5, hl = lane & 31;
     int ncur = n, rank0 = 0;              // surviving values, and how many lie below them
-    float L = -INFINITY, H = INFINITY;    // survivors: L <= v < H
+    // survivors: L <= v < H (at first the whole range, so that an end that
+    // stays beyond it reads no bin)
+    float L = mn, H = kInt ? mx + 1.0f : mx < INFINITY ? ord2f(f2ord(mx) + 1u) : INFINITY;
     int pL = 0, pH = n;                   // positions of the bins that hold them
     constexpr int G = NB / 64;
     const int top = start[lane * G];      // every G-th bin start
@@ -368,23 +557,27 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
                 lmn = wave_min(lmn);
                 lmx = wave_max(lmx);
                 flat = lmn == lmx;
-                cs = (double)lane_f(fminf(fmaxf(iters > 0 ? med_h : (float)(cs + q1), lmn), lmx), 0);
-                units(fmax((double)lmx - cs, cs - (double)lmn));
+                cs = lane_d((double)fminf(fmaxf(iters > 0 ? med_h : (float)(cs + q1), lmn), lmx), 0);
                 t1 = tu = th = tl = 0.0;
-                for (int i = pL + lane; i < pH; i += 64) {
-                    const float x = (float)sh.val[i];
-                    if (x >= L && x < H) accum(x, t1, tu, th, tl);
+                if (!flat) {
+                    units(fmax((double)lmx - cs, cs - (double)lmn));
+                    for (int i = pL + lane; i < pH; i += 64) {
+                        const float x = (float)sh.val[i];
+                        if (x >= L && x < H) accum((double)x - cs, t1, tu, th, tl);
+                    }
+                    t1 = lane_d(wave_total(t1), 0);
+                    tu = lane_d(wave_total(tu), 0);
+                    th = lane_d(wave_total(th), 0);
+                    tl = lane_d(wave_total(tl), 0);
                 }
-                t1 = wave_total(t1);
-                tu = wave_total(tu);
-                th = wave_total(th);
-                tl = wave_total(tl);
                 q1 = (t1 + tu) / nd;
                 vv = (th + tl) / nd - q1 * q1;
             }
             mean = cs + q1;
             sig = vv > 0.0 && !flat ? sqrt(vv) : 0.0;
         }
+        mean = lane_d(mean, 0);
+        sig = lane_d(sig, 0);
         if (iters == 0) sig0 = sig;
         // the median: the bin of its rank (bins start at rising positions),
         // then the order statistic inside the bin
@@ -409,22 +602,12 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
                 } else if (m <= 64) {
                     // the value with j smaller ones (or, among equals, fewer)
                     const float x = (lane < m) ? (float)sh.val[s + lane] : INFINITY;
-                    int q = 0;
-                    for (int i = 0; i < m; i += 4) {   // (lanes past m hold +inf)
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) q += lane_f(x, i + u) < x ? 1 : 0;
-                    }
-                    auto at = [&](int jj) {
-                        uint64_t hit;
-                        while ((hit = __ballot(lane < m && q == jj)) == 0ull) --jj;
-                        return lane_f(x, __builtin_ctzll(hit));
-                    };
-                    o[have] = at(j);
-                    if (both) o[1] = (r2 == r) ? o[have] : at(j + 1);
-                } else {
-                    // a large bin: the smallest value with more than j at or
-                    // below it, by bisection (of the integers, or of the
-                    // order-preserving bits), and the next one up
+                    const int q = wave_rank(x, m);
+                    o[have] = wave_kth(x, q, m, j);
+                    if (both) o[1] = (r2 == r) ? o[have] : wave_kth(x, q, m, j + 1);
+                } else if (m <= 256) {
+                    // the smallest value with more than j at or below it, by
+                    // bisection, and the next one up
                     float y[4];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) y[u] = (lane + 64 * u < m) ? (float)sh.val[s + lane + 64 * u] : INFINITY;
@@ -432,43 +615,30 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
                         int c = 0;
 #pragma unroll
                         for (int u = 0; u < 4; ++u) c += __popcll(__ballot(y[u] <= x));
-                        for (int i = s + 256; i < e; i += 64)
-                            c += __popcll(__ballot(i + lane < e && (float)sh.val[min(i + lane, e - 1)] <= x));
                         return c;
                     };
-                    auto value = [&](uint32_t z) { return kInt ? (float)z : ord2f(z); };
-                    float y0 = mn, y1 = mx;
-                    if (m > 256) {
-                        // (often one value many times: saturated pixels)
-                        y0 = INFINITY;
-                        y1 = -INFINITY;
-                        for (int i = s + lane; i < e; i += 64) {
-                            y0 = fminf(y0, (float)sh.val[i]);
-                            y1 = fmaxf(y1, (float)sh.val[i]);
-                        }
-                        y0 = wave_min(y0);
-                        y1 = wave_max(y1);
-                    }
-                    uint32_t a0 = kInt ? (uint32_t)y0 : f2ord(y0), a1 = kInt ? (uint32_t)y1 : f2ord(y1);
+                    uint32_t a0 = mesh_image<T>(mn), a1 = mesh_image<T>(mx);
                     while (a0 < a1) {
                         const uint32_t mid = a0 + ((a1 - a0) >> 1);
-                        if (upto(value(mid)) > j) a1 = mid;
+                        if (upto(mesh_value<T>(mid)) > j) a1 = mid;
                         else a0 = mid + 1;
                     }
-                    const float x1 = value(a0);
+                    const float x1 = mesh_value<T>(a0);
                     o[have] = x1;
                     if (both) {
                         float x2 = x1;
                         if (r2 != r && upto(x1) == j + 1) {
                             x2 = INFINITY;
-                            for (int i = s + lane; i < e; i += 64) {
-                                const float x = (float)sh.val[i];
-                                x2 = x > x1 ? fminf(x2, x) : x2;
-                            }
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) x2 = y[u] > x1 ? fminf(x2, y[u]) : x2;
                             x2 = wave_min(x2);
                         }
                         o[1] = x2;
                     }
+                } else {
+                    const float2 x = mesh_large_bin<T>((const lds_t<T>*)&sh.val[s], (lds_t<uint32_t>*)sh.part, m, j);
+                    o[have] = x.x;
+                    if (both) o[1] = (r2 == r) ? x.x : x.y;
                 }
                 have = both ? 2 : have + 1;
             }
@@ -527,8 +697,8 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
             Ln = lane_f(t, 0);
             Hn = lane_f(t, 32);
         }
-        Ln = fmaxf(L, Ln);
-        Hn = fminf(H, Hn);
+        Ln = lane_f(fmaxf(L, Ln), 0);
+        Hn = lane_f(fminf(H, Hn), 0);
         if (!(Ln < Hn)) {   // nothing left
             ++iters;
             break;
@@ -537,40 +707,44 @@ __global__ __launch_bounds__(NT) void k_mesh_stats(FrameDesc* __restrict__ desc,
         // one end of each range to the other, taken as one run
         const int bL = mesh_bin<NB>(Ln, blo, bscale), bH = mesh_bin<NB>(Hn, blo, bscale);
         const int sL = start[bL], sH = start[bH], eH = start[bH + 1];
-        const int nl = (int)start[bL + 1] - pL, run = nl + pH - sH;
+        // (an end that has not moved drops nothing: its bin may be a large one)
+        const int nl = Ln > L ? (int)start[bL + 1] - pL : 0, run = nl + (Hn < H ? pH - sH : 0);
         double s1 = 0.0, su = 0.0, sq = 0.0, sl = 0.0;
         int low = 0, gone = 0;
-        constexpr int U = 4;   // values per lane in flight
-        for (int i0 = 0; i0 < run; i0 += 64 * U) {
-            float x[U];
+        // (a value that stays adds an exact zero: no branch for a chain of FP64
+        // additions to wait at)
+        auto drop = [&](float x, int i) __attribute__((always_inline)) {
+            const bool lo = i < nl && x >= L && x < Ln;
+            const bool hi = i >= nl && i < run && x >= Hn && x < H;
+            const uint64_t bl = __ballot(lo), bh = __ballot(hi);
+            low += __popcll(bl);
+            gone += __popcll(bl | bh);
+            accum(lo || hi ? (double)x - cs : 0.0, s1, su, sq, sl);
+        };
+        int i0 = 0;
+        for (; i0 + 256 <= run; i0 += 256) {
+            float x[4];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (u > 0 && i0 + 64 * u >= run) break;
-                const int i = min(i0 + 64 * u + lane, run - 1);
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + 64 * u + lane;
                 x[u] = (float)sh.val[i < nl ? pL + i : sH + (i - nl)];
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (u > 0 && i0 + 64 * u >= run) break;
-                const int i = i0 + 64 * u + lane;
-                const bool lo = i < nl && x[u] >= L && x[u] < Ln;
-                const bool hi = i >= nl && i < run && x[u] >= Hn && x[u] < H;
-                const uint64_t bl = __ballot(lo), bh = __ballot(hi);
-                if ((bl | bh) == 0ull) continue;
-                low += __popcll(bl);
-                gone += __popcll(bl | bh);
-                if (lo || hi) accum(x[u], s1, su, sq, sl);
-            }
+            for (int u = 0; u < 4; ++u) drop(x[u], i0 + 64 * u + lane);
+        }
+        for (; i0 < run; i0 += 64) {
+            const int i = min(i0 + lane, run - 1);
+            drop((float)sh.val[i < nl ? pL + i : sH + (i - nl)], i0 + lane);
         }
         if (gone == 0 || gone == ncur) {
             ++iters;
             break;
         }
-        t1 -= wave_total(s1);
-        th -= wave_total(sq);
+        t1 = lane_d(t1 - wave_total(s1), 0);
+        th = lane_d(th - wave_total(sq), 0);
         if (!kInt) {
-            tu -= wave_total(su);
-            tl -= wave_total(sl);
+            tu = lane_d(tu - wave_total(su), 0);
+            tl = lane_d(tl - wave_total(sl), 0);
         }
         ncur -= gone;
         rank0 += low;
@@ -690,7 +864,6 @@ __device__ void spline_solve(int n, const double* t, const double* c, const doub
     if (n < 3) return;
     double rp = 0.0;
     double f0 = f[0], f1 = f[fs];
-#pragma unroll 4
     for (int k = 1; k <= n - 2; ++k) {
         const double f2 = f[(k + 1) * fs];
         const double h0 = t[k] - t[k - 1], h1 = t[k + 1] - t[k];
@@ -702,7 +875,6 @@ __device__ void spline_solve(int n, const double* t, const double* c, const doub
     }
     double mk = rp;
     m[(n - 2) * ms] = mk;
-#pragma unroll 4
     for (int k = n - 3; k >= 1; --k) {
         mk = r[k * ms] - c[k] * mk;
         m[k * ms] = mk;
@@ -768,7 +940,6 @@ __device__ __forceinline__ void spline_solve_inv(int n, const double* t, const d
     if (n < 3) return;
     double rp = 0.0;
     double f0 = f[0], f1 = f[fs];
-#pragma unroll 4
     for (int k = 1; k <= n - 2; ++k) {
         const double f2 = f[(k + 1) * fs];
         const double rhs = 6.0 * ((f2 - f1) * ih[k] - (f1 - f0) * ih[k - 1]);
@@ -778,7 +949,6 @@ __device__ __forceinline__ void spline_solve_inv(int n, const double* t, const d
         f1 = f2;
     }
     double mk = rp;
-#pragma unroll 4
     for (int k = n - 3; k >= 1; --k) {
         mk = m[k * ms] - c[k] * mk;
         m[k * ms] = mk;
@@ -868,7 +1038,6 @@ __global__ __launch_bounds__(kSplCols) void k_spline_y_small(const FrameDesc* __
     __syncthreads();
     if (!on) return;
     spline_solve_inv(ny, tk, cf, idn, ih, fl + lane, kSplCols, ml + lane, kSplCols);
-#pragma unroll 4
     for (int jy = 0; jy <= ny; ++jy) {
         double c[4];
         piece_poly_inv(ny, tk, ih, fl + lane, kSplCols, ml + lane, kSplCols, jy, c);
@@ -904,7 +1073,6 @@ __global__ __launch_bounds__(kSplCols) void k_spline_x_small(const FrameDesc* __
     __syncthreads();
     if (!on) return;
     spline_solve_inv(nx, tk, cf, idn, ih, fl + lane, kSplCols, ml + lane, kSplCols);
-#pragma unroll 4
     for (int ix = 0; ix <= nx; ++ix) {
         double c[4];
         piece_poly_inv(nx, tk, ih, fl + lane, kSplCols, ml + lane, kSplCols, ix, c);
@@ -1183,7 +1351,6 @@ __global__ __launch_bounds__(kSplThreads) void k_spline_y(const FrameDesc* __res
     double* r = d.scratch + g;
     double* mm = d.scratch + (size_t)2 * nx * ny + g;
     spline_solve(ny, tk, cf, dn, col, nx, r, mm, 2 * nx);
-#pragma unroll 4
     for (int jy = 0; jy <= ny; ++jy) {
         double c[4];
         piece_poly(ny, tk, col, nx, mm, 2 * nx, jy, c);
@@ -1221,7 +1388,6 @@ __global__ __launch_bounds__(kSplThreads) void k_spline_x(const FrameDesc* __res
     double* mm = base + (size_t)G * nx + g;
     const double* vals = d.ycoef + (((size_t)q * (ny + 1) + jy) * nx) * 4 + r;  // stride 4
     spline_solve(nx, tk, cf, dn, vals, 4, w, mm, G);
-#pragma unroll 4
     for (int ix = 0; ix <= nx; ++ix) {
         double c[4];
         piece_poly(nx, tk, vals, 4, mm, G, ix, c);

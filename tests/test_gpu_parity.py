@@ -156,6 +156,55 @@ def test_mesh_statistics_at_the_edges_of_the_launch_shapes(P, mw, mh, dt):
     ph.close()
 
 
+def _large_bin_meshes(m, dt, seed):
+    """Eight meshes whose median lies among hundreds or thousands of values of
+    one bin: a quiet third at a low level fixes the bins (their steps are its
+    width), the rest lies far above it, spread or with shared values around the
+    median's rank; then masked, clipped and saturated skies."""
+    rng = np.random.default_rng(seed)
+    n = m * m
+    q = 37 * n // 100
+
+    def far(*parts):
+        return np.concatenate([10.0 + 1e-3 * rng.standard_normal(q), *parts])[:n]
+
+    u = lambda k, a=30000.0, b=60000.0: a + (b - a) * rng.random(k)
+    spread = far(u(n - q))
+    below = n // 2 - q                     # the lower middle rank is the last value below the shared ones
+    edge = far(u(below, 39990.0, 39999.0), np.full(n // 8, 40000.0), u(n, 40001.0, 40010.0))
+    inside = far(u(below - 3, 39990.0, 39999.0), np.full(n // 8, 40000.0), u(n, 40001.0, 40010.0))
+    last = far(u(below - n // 8 + n % 2, 39990.0, 39999.0), np.full(n // 8, 40000.0), u(n, 40001.0, 40010.0))
+    two = np.where(rng.random(n) < 0.5, 40000.0, 40003.0)
+    two[:q] = 10.0 + 1e-3 * rng.standard_normal(q)
+    masked = 1000.0 + 10.0 * rng.standard_normal(n)
+    masked[: 9 * n // 20] = 0.0
+    clipped = np.maximum(10.0 * rng.standard_normal(n), 0.0)
+    sat = 1000.0 + 10.0 * rng.standard_normal(n)
+    sat[: 13 * n // 25] = 65535.0
+    blocks = [rng.permutation(b).reshape(m, m) for b in (spread, edge, inside, last, two, masked, clipped, sat)]
+    img = np.block([blocks[:4], blocks[4:]])
+    return np.clip(np.rint(img), 0, 65535).astype(np.uint16) if dt == "u16" else img.astype(np.float32)
+
+
+@pytest.mark.parametrize("dt", ["f32", "u16"])
+@pytest.mark.parametrize("m", [31, 32, 64, 90, 127, 128])
+def test_mesh_statistics_of_large_bins(P, m, dt):
+    """medians inside bins of more than 256 values, where they come from parts
+    of the bin's range or from a value that many pixels share"""
+    _say("large bins", m, dt)
+    img = _large_bin_meshes(m, dt, m)
+    p = _params("c1", mesh_w=m, mesh_h=m, mesh_filter=1)
+    ph = P.Photometry([_dev(img)], p, p.kernel(), capacity=64)
+    ph.background()
+    g = ph.grids(0)
+    check_meshes(img, g, p)
+    ph.background()
+    h = ph.grids(0)
+    for k in ("back_raw", "rms_raw", "iters"):
+        np.testing.assert_array_equal(g[k], h[k])
+    ph.close()
+
+
 def _exact_mesh(v, p):
     """(mean or mode, sigma, passes, largest |survivor|) of one mesh from
     correctly rounded sums (math.fsum)"""
