@@ -502,6 +502,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
         if (v[k] == v[k]) sh.val[start[pk[k] >> 16] + (pk[k] & 0xffffu)] = (T)v[k];
     __syncthreads();
     if (wv != 0) return;
+    if (!kInt) {
+        // a pixel that is not a number lies in no bin: no statistics
+        uint32_t binned = 0u;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) binned += sh.wc[i];
+        if (binned != (uint32_t)n) {
+            if (lane == 0) {
+                d.back_raw[out_idx] = (double)NAN;
+                d.rms_raw[out_idx] = 0.0;
+                d.iters[out_idx] = 0;
+            }
+            return;
+        }
+    }
     __builtin_amdgcn_s_setprio(3);   // one wavefront's chain of latencies from here on
     t1 = sh.w1[0];
     tu = sh.wu[0];

@@ -156,6 +156,29 @@ def test_mesh_statistics_at_the_edges_of_the_launch_shapes(P, mw, mh, dt):
     ph.close()
 
 
+@pytest.mark.parametrize("m", [32, 64, 128])
+def test_mesh_statistics_of_pixels_that_are_no_numbers(P, m):
+    """A mesh with a NaN or an infinite pixel has no background (NaN, rms 0),
+    every time; its neighbours are not touched."""
+    rng = np.random.default_rng(m)
+    img = (1000.0 + 10.0 * rng.standard_normal((2 * m, 4 * m))).astype(np.float32)
+    img[5, 7] = np.nan
+    img[3, 2 * m:2 * m + m // 2] = np.nan
+    img[m + 1, m + 2] = np.inf
+    img[m + 4, 3 * m + 9] = -np.inf
+    bad = np.zeros((2, 4), bool)
+    bad[0, [0, 2]] = bad[1, [1, 3]] = True
+    p = _params("c1", mesh_w=m, mesh_h=m, mesh_filter=1)
+    ph = P.Photometry([_dev(img)], p, p.kernel(), capacity=64)
+    for _ in range(3):
+        ph.background()
+        g = ph.grids(0)
+        np.testing.assert_array_equal(np.isnan(g["back_raw"]), bad)
+        assert np.all(g["rms_raw"][bad] == 0.0)
+        check_meshes(img, g, p, picks=[(j, i) for j in range(2) for i in range(4) if not bad[j, i]])
+    ph.close()
+
+
 def _large_bin_meshes(m, dt, seed):
     """Eight meshes whose median lies among hundreds or thousands of values of
     one bin: a quiet third at a low level fixes the bins (their steps are its
