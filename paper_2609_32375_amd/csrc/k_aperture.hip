@@ -166,7 +166,10 @@ k_aperture(const FrameDesc* __restrict__ desc, FrameDesc d1, ApArgs a, ApCat cat
         const int f = lo, k = o - __builtin_amdgcn_readfirstlane(fpre[f]);
         const int row = f * a.capacity + k;
         const FrameDesc& d = ONE ? d1 : desc[f];
-        const double xc = lane_d(cat.x[row], 0), yc = lane_d(cat.y[row], 0);
+        // (a centre far off the frame, infinite or not a number: one whose
+        // integers are in range, and that no circle reaches the frame from)
+        const double xc = lane_d(fmin(fmax(cat.x[row], -1000.0), (double)d.W + 1000.0), 0);
+        const double yc = lane_d(fmin(fmax(cat.y[row], -1000.0), (double)d.H + 1000.0), 0);
         const int cxi = (int)floor(xc), cyi = (int)floor(yc);
         const Real fx = (Real)(xc - (double)cxi), fy = (Real)(yc - (double)cyi);
         const int bx0 = cxi - R, by0 = cyi - R;

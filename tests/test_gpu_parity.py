@@ -702,6 +702,35 @@ def test_aperture_box_and_queue_edges(P, m, radii, r_in, r_out, prec):
     ph.close()
 
 
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "fp64"])
+def test_aperture_of_centres_far_off_the_frame(P, prec):
+    """Positions no circle reaches the frame from, also beyond 32-bit integers,
+    infinite or not a number: nothing summed, APER_TRUNC; the sources between
+    them keep their values."""
+    W, H = 150, 120
+    img = np.full((H, W), 9.0, np.float32)
+    p = _params("c1", radii=(3.0, 6.0), r_in=10.0, r_out=15.0)
+    far = [np.inf, -np.inf, np.nan, 1e300, -1e300, 3e9, -3e9, 2.0 ** 31, -2.0 ** 31 - 1, W + 15.6, -16.1, 1e6]
+    pos = [(60.0, 50.0)] + [q for f in far for q in ((f, 50.0), (60.0, f), (f, f))] + [(60.0, 50.0)]
+    keep = np.array([i in (0, len(pos) - 1) for i in range(len(pos))])
+    pos[1 + 3 * far.index(W + 15.6) + 1] = (60.0, H + 15.6)   # (just off in y)
+    xs, ys = (np.array(q) for q in zip(*pos))
+    nx, ny = -(-W // p.mesh_w), -(-H // p.mesh_h)
+    ph = P.Photometry([_dev(img)], p, p.kernel(), capacity=len(xs), precision=prec)
+    ph.set_grids(0, np.full((ny, nx), 2.0), np.full((ny, nx), 1.0))
+    ph.background(grid_given=True)
+    ph.set_catalog(0, xs, ys)
+    ph.aperture()
+    r = ph.results(0)
+    q = r["phot"]
+    for k in ("flux", "area", "fluxerr", "bkg"):
+        assert np.all(q[k][~keep] == 0.0), (k, q[k][~keep])
+    assert np.all(r["cat"]["flags"][~keep] & 8 == 8) and np.all(r["cat"]["flags"][keep] & 8 == 0)
+    np.testing.assert_allclose(q["area"][keep], np.pi * np.array([[9.0, 36.0]] * 2), rtol=1e-6)
+    np.testing.assert_allclose(q["bkg"][keep], 7.0, rtol=1e-6)
+    ph.close()
+
+
 def test_aperture_constant_image_closed_form(P):
     c = 7.25
     W = H = 120
