@@ -20,7 +20,6 @@
 
 namespace gpk {
 
-constexpr int kApBox = 2 * 66; // widest box (r <= 64)
 constexpr int kApWaves = 4;
 constexpr int kApCubics = 80;  // row cubics (rows x spline pieces) of a band
 constexpr int kApList = 256;   // queued (pixel, circle) cuts per wavefront

@@ -1096,7 +1096,7 @@ __global__ __launch_bounds__(kSplCols) void k_spline_x_small(const FrameDesc* __
 }
 
 // ---------------------------------------------------------------------------
-// Grids of at most kPcrMax knots per axis: one wavefront per spline, lane k =
+// Grids of at most kPcrMax knots on the solved axis: one wavefront per spline, lane k =
 // knot k.  The tridiagonal system of the natural spline's second derivatives
 // (interior rows h_{k-1} m_{k-1} + 2 (h_{k-1} + h_k) m_k + h_k m_{k+1} =
 // 6 (f_{k+1} - f_k) / h_k - 6 (f_k - f_{k-1}) / h_{k-1}, m_0 = m_{n-1} = 0)
@@ -1462,7 +1462,7 @@ void launch_grid_filter(const FrameDesc* desc, int nframes, int total_meshes, in
 }
 
 // mesh filter of size fsize (0: none, the grids are given) and the splines
-// in two launches, for grids of at most kPcrMax knots per axis and filters of
+// in two launches, for grids of at most kPcrBlkMax knots per axis and filters of
 // at most 5 x 5 (filter_spline_fits)
 bool filter_spline_fits(int max_nx, int max_ny, int fsize) {
     return max_nx <= kPcrBlkMax && max_ny <= kPcrBlkMax && fsize <= 5;

@@ -41,20 +41,6 @@ namespace gpk {
 // 445 -> 326 from blocks of 8 outputs whose window was moved by copies, with
 // uniform row addresses, stores of 64 neighbours and a shorter C.
 
-// the frame of a flattened workgroup index: base[] ascending from 0, so the
-// bases <= item form a prefix (one ballot per 64 frames; all lanes active)
-__device__ __forceinline__ int cv_frame_of(const int32_t* __restrict__ base, int n, int item) {
-    const int lane = threadIdx.x & 63;
-    int f = -1;
-    for (int i0 = 0; i0 < n; i0 += 64) {
-        const int i = i0 + lane;
-        const uint64_t m = __ballot(i < n && base[i] <= item);
-        f += __popcll(m);
-        if (m != ~0ull) break;
-    }
-    return f;
-}
-
 __device__ __forceinline__ FrameDesc cv_desc(const CvFrame& F) {
     FrameDesc d{};
     d.data = F.data;
@@ -182,7 +168,7 @@ __global__ __launch_bounds__(kCvThreads) void k_conv_h(CvWork w, int nframes, in
     __shared__ int bfl[kCvSeg / kCvCols];
     const int item = xcd_item(blockIdx.x, (total + kXcds - 1) / kXcds);
     if (item >= total) return;
-    const int f = cv_frame_of(w.hbase, nframes, item);
+    const int f = frame_of_wave(nframes, item, [&](int i) { return w.hbase[i]; });
     const CvFrame F = w.tab[f];
     const CvSeg S(item - w.hbase[f], F.W, a.lx);
     const int tid = threadIdx.x, hx = a.lx >> 1, nb = (F.W + kCvCols - 1) / kCvCols;
@@ -209,7 +195,7 @@ __global__ __launch_bounds__(kCvThreads) void k_conv_h_fill(CvWork w, int nframe
     extern __shared__ __align__(16) unsigned char cv_dyn[];
     const int item = xcd_item(blockIdx.x, (total + kXcds - 1) / kXcds);
     if (item >= total) return;
-    const int f = cv_frame_of(w.hbase, nframes, item);
+    const int f = frame_of_wave(nframes, item, [&](int i) { return w.hbase[i]; });
     if (w.fflag[f] == 0) return;   // nothing to fill in this frame
     const CvFrame F = w.tab[f];
     const CvSeg S(item - w.hbase[f], F.W, a.lx);
@@ -405,7 +391,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     __shared__ int ninv;
     const int item = xcd_item(blockIdx.x, (total + kXcds - 1) / kXcds);
     if (item >= total) return;
-    const int f = cv_frame_of(w.vbase, nframes, item);
+    const int f = frame_of_wave(nframes, item, [&](int i) { return w.vbase[i]; });
     const int local = item - w.vbase[f];
     const CvFrame F = w.tab[f];
     uint8_t* late_tile = w.tiles + F.tiles;

@@ -137,13 +137,6 @@ __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
     float bb = s - a;
     e = (a - (s - bb)) + (b - bb);
 }
-__device__ __forceinline__ F2 f2_add(F2 a, F2 b) {
-    float s, e;
-    two_sum(a.hi, b.hi, s, e);
-    e += a.lo + b.lo;
-    float h = s + e;
-    return F2{h, e - (h - s)};
-}
 // running compensated sum of single values
 __device__ __forceinline__ void f2_acc(F2& a, float v) {
     float s, e;
@@ -185,24 +178,6 @@ __device__ __forceinline__ float lane_f(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-// deterministic wavefront reductions (fixed butterfly order)
-__device__ __forceinline__ F2 wave_sum_f2(F2 v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        F2 w{__shfl_xor(v.hi, o), __shfl_xor(v.lo, o)};
-        // order the operands by lane so both partners compute the same value
-        v = ((threadIdx.x & o) == 0) ? f2_add(v, w) : f2_add(w, v);
-    }
-    return v;
-}
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        double w = __shfl_xor(v, o);
-        v = ((threadIdx.x & o) == 0) ? v + w : w + v;
-    }
-    return v;
-}
 // lanes exchanged between the halves of the wavefront (or, 16, of each half),
 // added: the low half gets a's sum over the pair, the high half b's
 __device__ __forceinline__ double swap_add32(double a, double b) {
@@ -218,16 +193,6 @@ __device__ __forceinline__ double swap_add16(double a, double b) {
     const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
     return __longlong_as_double((long long)((uint64_t)l[0] | ((uint64_t)h[0] << 32))) +
            __longlong_as_double((long long)((uint64_t)l[1] | ((uint64_t)h[1] << 32)));
-}
-// the sum of one value over the wavefront in every lane, without LDS
-__device__ __forceinline__ double wave_total_d(double v) {
-    v = swap_add32(v, v);
-    v = swap_add16(v, v);
-    v += dpp_d<0xB1>(v);
-    v += dpp_d<0x4E>(v);
-    v += dpp_d<0x141>(v);
-    v += dpp_d<0x140>(v);
-    return v;
 }
 // Sums of N (16 or 32) values over the wavefront's lanes, in a fixed order.
 // The halves of the wavefront exchange halves of the list, then the 16-lane
@@ -255,11 +220,6 @@ struct WaveTotals {
     }
 };
 
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
 __device__ __forceinline__ float wave_min(float v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v = fminf(v, __shfl_xor(v, o));

@@ -1002,8 +1002,9 @@ __global__ __launch_bounds__(256) void k_merge_records(DetWork wk, int minarea) 
     }
 }
 
-// Ranks of the bitmap's bits.  k_popc_scan: each workgroup takes kScanChunk
-// consecutive 1024-bit blocks, counts their bits and writes the exclusive
+// Ranks of the bitmap's bits.  popc_scan (for peaks a launch of its own,
+// k_popc_scan; for components part of k_merge_sums): each workgroup takes
+// kScanChunk consecutive 1024-bit blocks, counts their bits and writes the exclusive
 // prefix of the counts within the chunk to blockcnt; the chunk's total goes to
 // chunksum.  The exclusive prefix of the chunk totals (formed by every
 // catalogue workgroup in LDS, chunk_prefix) then gives the prefix of block b
