@@ -944,6 +944,36 @@ def test_peaks_of_equal_values(P, sep, cw, dt):
         ph.close()
 
 
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("dt", ["f32", "u16"])
+def test_peaks_of_ties_every_column(P, dt, prec):
+    """Peaks among ties and saturated pixels, in regions with and without a
+    saturated pixel: as many rows as the oracle's, and each of its whole-number
+    columns, the flags among them, the same."""
+    W, H = 200, 150
+    _say("peak columns", dt, prec)
+    rng = np.random.default_rng(17)
+    img = 500.0 + 100.0 * rng.integers(0, 3, (H, W))
+    img[:, :64][rng.random((H, 64)) < 0.02] = 3000.0
+    img[70, 127] = img[10, 130] = img[149, 199] = 3000.0
+    I = img.astype(np.uint16 if dt == "u16" else np.float32)
+    p = _params("c1", mesh_w=64, mesh_h=64, thresh=1.0, sat_level=3000.0)
+    nx, ny = -(-W // 64), -(-H // 64)
+    ph = P.Photometry([_dev(I)], p, np.ones((1, 1), np.float32), capacity=W * H, precision=prec)
+    ph.set_grids(0, np.full((ny, nx), 500.0), np.full((ny, nx), 10.0))
+    ph.background(grid_given=True)
+    for sep, cw in ((1, 1), (2, 6), (4, 2)):
+        ph.peaks(sep, cw)
+        c = ph.results(0)["cat"]
+        M = img - 500.0
+        o = oracle.peaks(img, M, M, np.full((H, W), 10.0), 1.0, sep, cw, 3000.0)
+        assert len(c["npix"]) == len(o["npix"]) > 0
+        for k in ("npix", "xmin", "xmax", "ymin", "ymax", "pmin", "flags"):
+            np.testing.assert_array_equal(np.asarray(c[k]).astype(np.int64), np.asarray(o[k]).astype(np.int64), err_msg=k)
+        assert (o["flags"] & 1).any() and not (o["flags"] & 1).all()
+    ph.close()
+
+
 # ----------------------------------------------------------------------------
 # growth curves on top-hat kernels, stage-isolated
 # ----------------------------------------------------------------------------
