@@ -88,6 +88,11 @@ __host__ __device__ __forceinline__ int ap_prefix_bytes(int nframes) { return (4
 // reduced in a fixed order, so an object's result does not depend on what
 // else runs.
 //
+// (No test whether a circle holds any of the 64 pixels before its sums: ten
+// such branches in a row cost more than ten pairs of additions.  500 objects
+// with eight radii up to 40 and r_out 64: 365 us with them, now 278; 20000 with
+// two and r_out 15: 173, now 164.)
+//
 // Bound by VALU issue and the latency between an object's LDS tables, its
 // pixels and its queue, at four wavefronts per SIMD (9 KB of LDS each).
 // Keeping the sums of every lane in LDS bins, finding a pixel's row by 17
@@ -338,10 +343,8 @@ k_aperture(const FrameDesc* __restrict__ desc, FrameDesc d1, ApArgs a, ApCat cat
                     kin += cut ? 1 : 0;
                     kout += use && cr2[j] <= dmin2 ? 1 : 0;
                     notin[j] += cut ? 1 : 0;
-                    if (__ballot(in) != 0ull) {   // (the inner circles: the rows near the centre)
-                        S[j] += (double)(in ? m : (Real)0);
-                        V[j] += (double)(in ? var : (Real)0);
-                    }
+                    S[j] += (double)(in ? m : (Real)0);
+                    V[j] += (double)(in ? var : (Real)0);
                 }
                 // circles that cut the pixel: queue (pixel, circle) pairs; the
                 // queue is worked off when full and at the object's last round
