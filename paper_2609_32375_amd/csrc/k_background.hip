@@ -537,7 +537,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
     int ncur = n, rank0 = 0;              // surviving values, and how many lie below them
     // survivors: L <= v < H (at first the whole range, so that an end that
     // stays beyond it reads no bin)
-    float L = mn, H = kInt ? mx + 1.0f : mx < INFINITY ? ord2f(f2ord(mx) + 1u) : INFINITY;
+    float L = mn, H = kInt ? mx + 1.0f : mx < INFINITY ? ord2f(f2ord(mx + 0.0f) + 1u) : INFINITY;   // (past +0 for -0)
     int pL = 0, pH = n;                   // positions of the bins that hold them
     constexpr int G = NB / 64;
     const int top = start[lane * G];      // every G-th bin start

@@ -179,6 +179,26 @@ def test_mesh_statistics_of_pixels_that_are_no_numbers(P, m):
     ph.close()
 
 
+@pytest.mark.parametrize("m", [16, 32, 64, 128])
+def test_mesh_statistics_of_signed_zeros(P, m):
+    """zeros of either sign as the largest, the smallest and the middle values"""
+    rng = np.random.default_rng(m)
+    n = m * m
+    z = lambda k: np.where(rng.random(k) < 0.5, -0.0, 0.0)
+    top, only, bottom, mid = (c + 3.0 * rng.standard_normal(n) for c in (-1000.0, -800.0, 900.0, 0.0))
+    k = n // 20
+    top[:k] = z(k)
+    only[:k] = -0.0
+    bottom[:k] = z(k)
+    mid[:3 * k] = z(3 * k)
+    img = np.concatenate([rng.permutation(b).reshape(m, m) for b in (top, only, bottom, mid)], axis=1).astype(np.float32)
+    p = _params("c1", mesh_w=m, mesh_h=m, mesh_filter=1)
+    ph = P.Photometry([_dev(img)], p, p.kernel(), capacity=64)
+    ph.background()
+    check_meshes(img, ph.grids(0), p)
+    ph.close()
+
+
 def _large_bin_meshes(m, dt, seed):
     """Eight meshes whose median lies among hundreds or thousands of values of
     one bin: a quiet third at a low level fixes the bins (their steps are its
