@@ -25,13 +25,56 @@
 
 namespace gpk {
 
+// the value of lane ^ J, and the least and the greatest of the lanes' values,
+// by DPP and permutes of registers: a shuffle through LDS waits some 100 cycles
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_xor(float v, int j, int lane) {
+    if (j == 1) return dpp_f<0xB1>(v);
+    if (j == 2) return dpp_f<0x4E>(v);
+    if (j == 4) return dpp_f<0x1B>(dpp_f<0x141>(v));   // 7 - lane of each 8, then 3 - lane of each 4
+    if (j == 8) return dpp_f<0x128>(v);
+    const uint32_t u = __float_as_uint(v);
+    if (j == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // rows 0 0 2 2 | 1 1 3 3
+        return __uint_as_float((lane & 16) ? r[0] : r[1]);
+    }
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // low low | high high
+    return __uint_as_float((lane & 32) ? r[0] : r[1]);
+}
+__device__ __forceinline__ float wave_least(float v) {
+    v = fminf(v, dpp_f<0xB1>(v));
+    v = fminf(v, dpp_f<0x4E>(v));
+    v = fminf(v, dpp_f<0x141>(v));
+    v = fminf(v, dpp_f<0x140>(v));
+    return fminf(fminf(lane_f(v, 0), lane_f(v, 16)), fminf(lane_f(v, 32), lane_f(v, 48)));
+}
+__device__ __forceinline__ float wave_greatest(float v) { return -wave_least(-v); }
+
+// inclusive prefix sums over the lanes
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
+    v += dpp_from<0x111, 0xf>(v);   // 1, 2, 4, 8 lanes down inside a row
+    v += dpp_from<0x112, 0xf>(v);
+    v += dpp_from<0x114, 0xf>(v);
+    v += dpp_from<0x118, 0xf>(v);
+    v += dpp_from<0x142, 0xa>(v);   // a row's last lane to the next row (1 and 3)
+    v += dpp_from<0x143, 0xc>(v);   // lane 31 to rows 2 and 3
+    return v;
+}
+
 // Ascending bitonic sort of one value per lane of a wavefront.
 __device__ __forceinline__ float wave_sort(float x, int lane) {
 #pragma unroll
     for (int k = 2; k <= 64; k <<= 1) {
 #pragma unroll
         for (int j = k >> 1; j > 0; j >>= 1) {
-            const float o = __shfl_xor(x, j);
+            const float o = lane_xor(x, j, lane);
             const bool up = (lane & k) == 0, lower = (lane & j) == 0;
             x = (lower == up) ? fminf(x, o) : fmaxf(x, o);
         }
@@ -203,12 +246,7 @@ __device__ __attribute__((noinline)) float2 mesh_large_bin(const lds_t<T>* val, 
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d);
         const int c = (int)part[lane] + ((uint32_t)lane == hot ? mine : 0);
-        int incl = c;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int y = __shfl_up(incl, d);
-            if (lane >= d) incl += y;
-        }
+        const int incl = (int)wave_prefix((uint32_t)c);
         const int q = __builtin_ctzll(__ballot(incl > j));
         mm = __builtin_amdgcn_readlane(c, q);
         j -= __builtin_amdgcn_readlane(incl, q) - mm;
@@ -234,22 +272,9 @@ __device__ __attribute__((noinline)) float2 mesh_large_bin(const lds_t<T>* val, 
         // the next value lies above the part
         x2 = INFINITY;
         each([&](uint32_t z) __attribute__((always_inline)) { x2 = z > a1 ? fminf(x2, mesh_value<T>(z)) : x2; });
-        x2 = wave_min(x2);
+        x2 = wave_least(x2);
     }
     return make_float2(x1, x2);
-}
-
-// the least of the lanes' values
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float wave_least(float v) {
-    v = fminf(v, dpp_f<0xB1>(v));
-    v = fminf(v, dpp_f<0x4E>(v));
-    v = fminf(v, dpp_f<0x141>(v));
-    v = fminf(v, dpp_f<0x140>(v));
-    return fminf(fminf(lane_f(v, 0), lane_f(v, 16)), fminf(lane_f(v, 32), lane_f(v, 48)));
 }
 
 // One workgroup per mesh.  Whatever was clipped before, the surviving values
@@ -350,18 +375,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
         mn = fminf(mn, v[k]);   // (NaN is passed over)
         mx = fmaxf(mx, v[k]);
     }
-    mn = wave_min(mn);
-    mx = wave_max(mx);
+    mn = wave_least(mn);
+    mx = wave_greatest(mx);
     for (int b = tid; b < NB / 2; b += NT) sh.start[b] = 0u;
     if (lane == 0) {
         sh.wmin[wv] = mn;
         sh.wmax[wv] = mx;
     }
     if (wv == 0) {
+        // (spread over the pixels the lane has: all of the 64 in a narrow mesh too)
+        const int at = (lane * ((n - min(lane, n - 1) + NT - 1) / NT)) >> 6;
         float s = v[0];
 #pragma unroll
         for (int k = 1; k < PPT; ++k)
-            if ((lane & (PPT - 1)) == k) s = v[k];
+            if (at == k) s = v[k];
         const uint64_t have = __ballot(s == s);   // (lane 0 always has its first pixel)
         s = wave_sort(s == s ? s : INFINITY, lane);
         const int m = __popcll(have);
@@ -426,8 +453,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
         mq = lane_d(ldexp(1.5, 2 * ex - 38 + 52), 0);
         ng = lane_d(ldexp(1.5, ex - 76 + 52), 0);
         nq = lane_d(ldexp(1.5, 2 * ex - 76 + 52), 0);
+        return ex;
     };
-    units(fmax((double)mx - cs, cs - (double)mn));
+    const int ex0 = units(fmax((double)mx - cs, cs - (double)mn));
     auto accum = [&](double e, double& s1, double& su, double& sq, double& sl) __attribute__((always_inline)) {
         if (kInt) {
             s1 += e;
@@ -441,6 +469,32 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
         }
     };
     double t1 = 0.0, tu = 0.0, th = 0.0, tl = 0.0;
+    // Positive floats that lie within 2^14 of each other's size (a sky with its
+    // level and its stars): each (v - c) is itself a multiple of 2^-38 of the
+    // range, so its sum needs no parts, and the rest of its square no rounding;
+    // the same sums by 7 FP64 operations a pixel for 15.
+    int en;
+    (void)frexp(mn, &en);
+    const bool plain = !kInt && mn > 0.0f && mx < INFINITY && ex0 - __builtin_amdgcn_readfirstlane(en) <= 14;
+    // (four pixels of a thread at a time: a small mesh has no others)
+    auto sums = [&](auto&& add) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k0 = 0; k0 < PPT; k0 += 4) {
+            if (k0 * NT >= n) break;
+#pragma unroll
+            for (int k = k0; k < k0 + 4; ++k) add(v[k] == v[k] ? (double)v[k] - cs : 0.0);
+        }
+    };
+    if (plain) {
+        sums([&](double e) __attribute__((always_inline)) {
+            const double hq = fma(e, e, mq) - mq;
+            t1 += e;
+            th += hq;
+            tl += fma(e, e, -hq);
+        });
+    } else if (!kInt) {
+        sums([&](double e) __attribute__((always_inline)) { accum(e, t1, tu, th, tl); });
+    }
     uint32_t pk[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
@@ -450,7 +504,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
             const uint32_t sft = (b & 1u) * 16u;
             const uint32_t old = atomicAdd((uint32_t*)&sh.start[b >> 1], 1u << sft);
             pk[k] = (b << 16) | ((old >> sft) & 0xffffu);
-            accum((double)v[k] - cs, t1, tu, th, tl);
+            if (kInt) accum((double)v[k] - cs, t1, tu, th, tl);
         }
     }
     t1 = wave_total(t1);
@@ -475,12 +529,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
             c[q] = (i < NB / 2) ? sh.start[i] : 0u;
             tot += (c[q] & 0xffffu) + (c[q] >> 16);
         }
-        uint32_t incl = tot;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(incl, o);
-            if (lane >= o) incl += y;
-        }
+        const uint32_t incl = wave_prefix(tot);
         if (lane == 63) sh.wc[wv] = incl;
         __syncthreads();
         uint32_t run = incl - tot;
@@ -568,8 +617,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
                         lmx = fmaxf(lmx, x);
                     }
                 }
-                lmn = wave_min(lmn);
-                lmx = wave_max(lmx);
+                lmn = wave_least(lmn);
+                lmx = wave_greatest(lmx);
                 flat = lmn == lmx;
                 cs = lane_d((double)fminf(fmaxf(iters > 0 ? med_h : (float)(cs + q1), lmn), lmx), 0);
                 t1 = tu = th = tl = 0.0;
@@ -645,7 +694,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
                             x2 = INFINITY;
 #pragma unroll
                             for (int u = 0; u < 4; ++u) x2 = y[u] > x1 ? fminf(x2, y[u]) : x2;
-                            x2 = wave_min(x2);
+                            x2 = wave_least(x2);
                         }
                         o[1] = x2;
                     }

@@ -220,17 +220,6 @@ struct WaveTotals {
     }
 };
 
-__device__ __forceinline__ float wave_min(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fminf(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
-
 // ---------------------------------------------------------------------------
 // frame lookup by flattened index: the last frame whose base <= idx
 template <typename Get>
