@@ -110,10 +110,22 @@ __device__ __forceinline__ void cv_columns(const CvSeg& S, int W, int hx, Fn&& f
 }
 
 // the sums of a staged segment, stored through LDS, so that a store
-// instruction writes 64 neighbours
+// instruction writes 64 neighbours.  A segment of at most one output a thread
+// goes that way (16 each would leave all but 8 threads idle), with the same
+// sums: 50 x 20000 pixels, 33 x 33 taps 81 us a pass, now 53; 128 wide, 129 taps
+// 30 and 23; 200 wide, two rounds of single outputs, 23.6 and 24.9.
 template <typename Real>
 __device__ __forceinline__ void cv_hsum(const CvSeg& S, const CvArgs& a, unsigned char* dyn, Real* o0) {
     Real* so = reinterpret_cast<Real*>(dyn);
+    if (S.nseg <= kCvThreads) {
+        const int i = threadIdx.x;
+        if (i >= S.nseg) return;
+        double sum = 0.0;
+#pragma unroll 8
+        for (int b = 0; b < a.lx; ++b) sum = fma(a.kx[b], (double)so[cv_hpos<Real>(i + b)], sum);
+        o0[i] = (Real)sum;
+        return;
+    }
     const int i0 = threadIdx.x * kCvN;
     double acc[kCvN];
     if (i0 < S.nseg) cv_sum16<true>(so + cv_hpos<Real>(i0), a.kx, a.lx, acc);

@@ -1374,6 +1374,29 @@ def test_background_conv_fills_do_not_depend_on_the_tile(P, lx, ly, signed, prec
         assert out[0][2] == (few.sum() if lx == ly == 1 else 0)
 
 
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("W,lx,ly", [(1, 5, 3), (63, 129, 5), (127, 33, 9), (128, 17, 17), (129, 17, 17), (2049, 65, 3), (2176, 7, 7), (2177, 7, 7)])
+def test_background_conv_of_narrow_rows(P, W, lx, ly, prec):
+    """rows (and last segments of rows, 2048 pixels on) of at most one output a
+    thread and one more, fills among them, against the oracle"""
+    H = 70
+    _say("conv narrow", W, lx, ly, prec)
+    rng = np.random.default_rng(W)
+    I = (500.0 + 20.0 * rng.standard_normal((H, W))).astype(np.float32)
+    kx, ky = ((0.2 + rng.random(k)).astype(np.float32) for k in (lx, ly))
+    mask = (rng.random((H, W)) < 0.01).astype(np.uint8)
+    Bo, Ro, no = oracle.background_conv(I, kx.astype(np.float64), ky.astype(np.float64), mask=mask, sat=np.inf,
+                                        gain=1.5, rn=5.0, dark=0.0, texp=0.0)
+    cb = P.ConvBackground([_dev(I)], kx, ky, 1.5, 5.0, precision=prec)
+    cb.run([_dev(mask)])
+    torch.cuda.synchronize()
+    assert int(cb.unfilled[0].item()) == no
+    tol = _conv_tolerances(I, kx, ky, mask, np.inf, Bo, prec, 1.5)
+    B = cb.back[0].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(B - Bo) <= tol), float(np.max(np.abs(B - Bo) - tol))
+    cb.close()
+
+
 def test_background_conv_constant_frame_and_batch(P):
     """A constant frame comes back unchanged; a batch of frames (uint16 and
     float32, several sizes) equals per-frame calls bit for bit."""
