@@ -24,7 +24,9 @@ constexpr int kApWaves = 4;
 constexpr int kApCubics = 80;  // row cubics (rows x spline pieces) of a band
 constexpr int kApList = 256;   // queued (pixel, circle) cuts per wavefront
 // wavefronts per SIMD the registers are held to (FP32): more circles keep more
-// sums, and would spill at four
+// sums.  At four, 128 registers: batches spill 16 bytes a lane for five
+// circles, one-frame calls 32 for four and 48 for five, nothing from six on
+// (151 registers at three)
 constexpr int ap_occ(int nc) { return nc <= 5 ? 4 : nc <= 7 ? 3 : 2; }
 static_assert(kApCubics <= 2 * 64, "two row cubics per lane");
 
@@ -94,13 +96,13 @@ __host__ __device__ __forceinline__ int ap_prefix_bytes(int nframes) { return (4
 // two and r_out 15: 173, now 164.)
 //
 // Bound by VALU issue and the latency between an object's LDS tables, its
-// pixels and its queue, at four wavefronts per SIMD (9 KB of LDS each).
+// pixels and its queue, at four wavefronts per SIMD (r_out 15: 6.7 KB of LDS each).
 // Keeping the sums of every lane in LDS bins, finding a pixel's row by 17
 // compares, two bands per box, pieces of straddling pixels one after another
 // and the object's descriptor in vector registers took: 106,344 objects of
-// 371 MP uint16 (r_out 15, two apertures) 1605 us, now 912; 60,243 of a
-// crowded 12300^2 frame (r_out 18, three) 1255, now 684; 13,233 of 6144^2 289,
-// now 153; FP64, 1092 objects, 73, now 33.
+// 371 MP uint16 (r_out 15, two apertures) 1605 us, now 860; 60,243 of a
+// crowded 12300^2 frame (r_out 18, three) 1255, now 636; 13,233 of 6144^2 289,
+// now 137; FP64, 1092 objects, 73, now 33.
 // ONE: a one-frame call, whose descriptor comes with the launch (d1) instead
 // of from the workspace table
 template <typename Real, int NC, bool ONE>

@@ -2,9 +2,11 @@
 //
 //  k_mesh_stats   one workgroup per mesh.  The values of a mesh are grouped by
 //                 bins in LDS once; a clipping pass then takes the dropped ends
-//                 off exact sums and finds the median in its bin, all in one
-//                 wavefront.  Every sum is exact, so a mesh gives bit-identical
-//                 results wherever it is scheduled.
+//                 off running sums and finds the median in its bin, all in one
+//                 wavefront.  The sums are exact over terms that are whole
+//                 numbers (floats: of two fixed units, one far below the
+//                 other), so a mesh gives bit-identical results wherever it is
+//                 scheduled.
 //  k_spline_y_pcr, k_spline_x_pcr (and the *_blk variants)
 //                 grids of at most 511 knots per axis: the f x f median over
 //                 the mesh grid (truncated at the edges) and the natural cubic
@@ -297,19 +299,20 @@ __device__ __attribute__((noinline)) float2 mesh_large_bin(const lds_t<T>* val, 
 // their median, in units of their own range.  A mesh gives bit-identical
 // results wherever it runs.
 //
-// Bound by latency: a mesh of 64^2 (128^2) float pixels takes about 6000
-// (8000) cycles to arrive, 7000 (15000) for the histogram's LDS atomics, 4000
-// (7500) to scan and store, then 1500-2000 per clipping pass, 3-14 of them.
-// What hides it is meshes per CU: 7 of 64^2, two of 128^2 (74 KB of LDS).
+// Bound by latency: loads, the histogram's LDS atomics, scan and stores, then
+// a chain of 3-14 clipping passes in one wavefront.  What hides it is meshes
+// per CU: 7 of 64^2, two of 128^2 (74 KB of LDS).
 // A pass over all pixels in registers per iteration, with a sorted window for
 // the median (float) or prefix sums of a histogram (uint16), took: 12300^2
-// crowded float in 128^2 meshes 2222 us, now 985; 6144^2 260, now 135;
-// 2048^2 in 64^2 meshes 40, now 22; 371 MP of uint16 1122, now 680.
+// crowded float in 128^2 meshes 2222 us, now 1083; 6144^2 260, now 143;
+// 2048^2 in 64^2 meshes 40, now 24; 371 MP of uint16 1122, now 648.  (Floats
+// with one part of 2^-38 and no second: 981, 131 and 22.)
 //
 // ONE: a one-frame call, whose descriptor comes with the launch (d1);
 // workgroup 0 stores it in the table for the launches that follow.
 // (Registers for seven wavefronts per SIMD up to 8192 pixels: the float ones
-// spill three in the clipping loop for it.)
+// take 67, no vector register spilled; the 16 bytes of scratch hold scalar ones
+// across the call of mesh_large_bin.)
 template <typename T, int NT, int PPT, bool ONE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8192 ? 4 : 7))) void k_mesh_stats(FrameDesc* __restrict__ desc, FrameDesc d1, int nframes,
                                                    BkgArgs a) {

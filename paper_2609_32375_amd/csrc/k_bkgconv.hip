@@ -24,7 +24,8 @@
 // the unit-sum FP64 taps read as uniform kernel arguments.  Each pass stages
 // its rows (or a column band) in LDS with the reflection applied on load, and
 // every thread keeps 16 consecutive outputs in registers and slides a window
-// over the staged data: one LDS read and conversion per 16 FMAs.
+// over the staged data: one LDS read and conversion per 16 FMAs.  (A row of up
+// to 128 outputs goes one output a thread.)
 // Each output's sum runs over the taps in order.  Each pass is one
 // launch over every frame of the call: a frame table in the workspace gives
 // each frame's slices of the planes and flags and its first workgroup of
@@ -39,7 +40,9 @@ namespace gpk {
 // each; the vertical pass also moves 1 GB), the waits for the rows of the next
 // workgroups and the traffic take the rest: horizontal 260 -> 222 us, vertical
 // 445 -> 326 from blocks of 8 outputs whose window was moved by copies, with
-// uniform row addresses, stores of 64 neighbours and a shorter C.
+// uniform row addresses, stores of 64 neighbours and C at a few invalid pixels
+// alone.  (The first vertical pass spills at four wavefronts per SIMD: 40 bytes
+// of scratch a lane in FP32, 80 in FP64, nearly all where a tile forms C.)
 
 __device__ __forceinline__ FrameDesc cv_desc(const CvFrame& F) {
     FrameDesc d{};

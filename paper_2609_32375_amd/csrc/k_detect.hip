@@ -48,7 +48,7 @@ struct LocalRec {
 };
 
 // LDS regions are reused phase by phase (REG: region width and height, the
-// tile plus the filter halo; NIX: spline pieces of a region row; 29 KB for
+// tile plus the filter halo; NIX: spline pieces of a region row; 30,400 bytes for
 // FP32, REG = 68 and NIX = 4, five workgroups per compute unit):
 //   u1: row cubics (build M, R) -> the pixels' labels -> piece ids
 //   u2: M over tile + halo (the horizontal pass in place) -> labels -> piece
