@@ -310,9 +310,8 @@ __device__ __attribute__((noinline)) float2 mesh_large_bin(const lds_t<T>* val, 
 //
 // ONE: a one-frame call, whose descriptor comes with the launch (d1);
 // workgroup 0 stores it in the table for the launches that follow.
-// (Registers for seven wavefronts per SIMD up to 8192 pixels: the float ones
-// take 67, no vector register spilled; the 16 bytes of scratch hold scalar ones
-// across the call of mesh_large_bin.)
+// (Registers for seven wavefronts per SIMD up to 8192 pixels; nothing spilled to
+// memory.)
 template <typename T, int NT, int PPT, bool ONE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8192 ? 4 : 7))) void k_mesh_stats(FrameDesc* __restrict__ desc, FrameDesc d1, int nframes,
                                                    BkgArgs a) {
@@ -649,7 +648,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
         // then the order statistic inside the bin
         {
             const int r2 = rank0 + ncur / 2, r1 = (ncur & 1) ? r2 : r2 - 1;
-            float o[2] = {0.0f, 0.0f};
+            float o0 = 0.0f, o1 = 0.0f;   // (no array: an index at run time puts it in scratch memory)
             int have = 0;
 #pragma unroll 1
             while (have < 2) {
@@ -662,15 +661,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
                 const int s = __builtin_amdgcn_readlane(k > 0 ? in : top, k > 0 ? k - 1 : g);
                 const int m = e - s, j = r - s;
                 const bool both = r2 < e;   // the upper middle value lies here too
+                float x1, x2;               // the values of rank r and, if it lies here, r2
                 if (kInt && bscale == 1.0f && b > 0 && b < NB - NB / 4) {
-                    o[have] = blo + (float)b;   // a bin of one value
-                    if (both) o[1] = o[have];
+                    x1 = x2 = blo + (float)b;   // a bin of one value
                 } else if (m <= 64) {
                     // the value with j smaller ones (or, among equals, fewer)
                     const float x = (lane < m) ? (float)sh.val[s + lane] : INFINITY;
                     const int q = wave_rank(x, m);
-                    o[have] = wave_kth(x, q, m, j);
-                    if (both) o[1] = (r2 == r) ? o[have] : wave_kth(x, q, m, j + 1);
+                    x1 = x2 = wave_kth(x, q, m, j);
+                    if (both && r2 != r) x2 = wave_kth(x, q, m, j + 1);
                 } else if (m <= 256) {
                     // the smallest value with more than j at or below it, by
                     // bisection, and the next one up
@@ -689,31 +688,28 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * PPT > 8
                         if (upto(mesh_value<T>(mid)) > j) a1 = mid;
                         else a0 = mid + 1;
                     }
-                    const float x1 = mesh_value<T>(a0);
-                    o[have] = x1;
-                    if (both) {
-                        float x2 = x1;
-                        if (r2 != r && upto(x1) == j + 1) {
-                            x2 = INFINITY;
+                    x1 = x2 = mesh_value<T>(a0);
+                    if (both && r2 != r && upto(x1) == j + 1) {
+                        x2 = INFINITY;
 #pragma unroll
-                            for (int u = 0; u < 4; ++u) x2 = y[u] > x1 ? fminf(x2, y[u]) : x2;
-                            x2 = wave_least(x2);
-                        }
-                        o[1] = x2;
+                        for (int u = 0; u < 4; ++u) x2 = y[u] > x1 ? fminf(x2, y[u]) : x2;
+                        x2 = wave_least(x2);
                     }
                 } else {
                     const float2 x = mesh_large_bin<T>((const lds_t<T>*)&sh.val[s], (lds_t<uint32_t>*)sh.part, m, j);
-                    o[have] = x.x;
-                    if (both) o[1] = (r2 == r) ? x.x : x.y;
+                    x1 = x.x;
+                    x2 = (r2 == r) ? x.x : x.y;
                 }
+                if (!have) o0 = x1;
+                o1 = have ? x1 : x2;
                 have = both ? 2 : have + 1;
             }
             if (r1 == r2) {
-                med_h = o[0];
+                med_h = o0;
                 med_l = 0.0f;
             } else {
                 float s, e;
-                two_sum(o[0], o[1], s, e);
+                two_sum(o0, o1, s, e);
                 med_h = 0.5f * s;
                 med_l = 0.5f * e;
             }
