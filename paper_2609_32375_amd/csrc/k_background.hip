@@ -304,8 +304,8 @@ __device__ __attribute__((noinline)) float2 mesh_large_bin(const lds_t<T>* val, 
 // per CU: 7 of 64^2, two of 128^2 (74 KB of LDS).
 // A pass over all pixels in registers per iteration, with a sorted window for
 // the median (float) or prefix sums of a histogram (uint16), took: 12300^2
-// crowded float in 128^2 meshes 2222 us, now 1083; 6144^2 260, now 143;
-// 2048^2 in 64^2 meshes 40, now 24; 371 MP of uint16 1122, now 648.  (Floats
+// crowded float in 128^2 meshes 2222 us, now 1067; 6144^2 260, now 143;
+// 2048^2 in 64^2 meshes 40, now 24; 371 MP of uint16 1122, now 645.  (Floats
 // with one part of 2^-38 and no second: 981, 131 and 22.)
 //
 // ONE: a one-frame call, whose descriptor comes with the launch (d1);
