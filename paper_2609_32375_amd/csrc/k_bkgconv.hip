@@ -116,7 +116,8 @@ __device__ __forceinline__ void cv_columns(const CvSeg& S, int W, int hx, Fn&& f
 // instruction writes 64 neighbours.  A segment of at most one output a thread
 // goes that way (16 each would leave all but 8 threads idle), with the same
 // sums: 50 x 20000 pixels, 33 x 33 taps 81 us a pass, now 53; 128 wide, 129 taps
-// 30 and 23; 200 wide, two rounds of single outputs, 23.6 and 24.9.
+// 30 and 23.  Wider rows lose by it: 200 wide, two rounds, 129 taps 26.0 and
+// 29.3, 300 wide, three, 23.7 and 30.7.
 template <typename Real>
 __device__ __forceinline__ void cv_hsum(const CvSeg& S, const CvArgs& a, unsigned char* dyn, Real* o0) {
     Real* so = reinterpret_cast<Real*>(dyn);
